@@ -165,6 +165,7 @@ fv3_status fv3_ensemble_create(fv3_state *const *states, const fv3_grid *const *
     e->n_split = n_split;
     e->use_graph = (flags & FV3_ENSEMBLE_GRAPH) != 0;
     (void)hipGetDevice(&e->device);
+    for (int m = 0; m < members; m++) e->rec.short_columns = e->rec.short_columns && fv3::column_short(grids[m]);
     for (int m = 0; m < members; m++) {
         e->rec.member = m;
         fv3_status r = fv3::record_substeps(states[m], grids[m], dt / n_split, &e->rec);

@@ -89,6 +89,7 @@ struct Recorder {
     std::vector<size_t> marks;   // site indices: end of the entry part, end of one substep
     size_t pos = 0, mark = 0;
     int member = 0;
+    bool short_columns = true;   // every member's column solves take the short-chunk kernel
     bool bad = false;
 };
 
@@ -160,6 +161,8 @@ fv3_status run_halo_cells(const fv3_grid *g, void *const *f, int nf, int levels,
 // halo of a cell-centred vector (x, y components in tile coordinates)
 fv3_status run_halo_pair_cells(const fv3_grid *g, void *fx, void *fy, int levels, int fp64,
                                hipStream_t st);
+// column.hip: whether the grid's column solves take the short-chunk kernel
+bool column_short(const fv3_grid *g);
 // remap.hip: vertical remapping of a state to the coordinate ak + bk ps
 fv3_status run_remap(fv3_state *s, const fv3_grid *g, const double *ak, const double *bk,
                      void *const *q, int nq, hipStream_t st);

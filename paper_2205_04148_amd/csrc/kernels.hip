@@ -30,126 +30,10 @@
 #include <vector>
 
 #include "fv3_internal.hpp"
-#include "flog.hpp"
+#include "column.hpp"
+#include "launch.hpp"
 
 namespace fv3 {
-
-#define DEVI __device__ __forceinline__
-
-// ------------------------------------------------------------ indexing
-DEVI long pidx(const Geo &G, int L, int t, int k) { return G.off0 + ((long)t * L + k) * G.lev; }
-// Element (i, j) of a plane whose interior origin is P (i, j >= -3): the
-// address is the plane's halo corner (-3, -3) plus a non-negative 32-bit
-// byte offset, so that a block-uniform P becomes a scalar base with one
-// 32-bit vector offset instead of per-lane 64-bit address arithmetic.
-template <class T>
-DEVI T &at_(T *p, int i, int j, int pitch)
-{
-    char *b = (char *)(p - (3 * pitch + 3));
-    return *(T *)(b + (unsigned)((j + 3) * pitch + (i + 3)) * (unsigned)sizeof(T));
-}
-#define AT(P, i, j) at_((P), (int)(i), (int)(j), (int)G.pitch)
-
-// a / b in the FP32 bulk through the hardware reciprocal (about 1 ulp, far
-// below the FP32 bulk's rounding), FP64 exact
-template <class T>
-DEVI T rdiv(T a, T b)
-{
-    if constexpr (std::is_same<T, float>::value) return a * __builtin_amdgcn_rcpf(b);
-    else return a / b;
-}
-
-DEVI int stx_(int st) { return (st == SC || st == SY) ? 1 : 0; }
-DEVI int sty_(int st) { return (st == SC || st == SX) ? 1 : 0; }
-DEVI int floor2(int a) { return a >= 0 ? (a >> 1) : -((1 - a) >> 1); }
-
-DEVI bool in_corner(const Geo &G, int st, int i, int j)
-{
-    int x2 = 2 * i + stx_(st), y2 = 2 * j + sty_(st), n2 = 2 * G.n;
-    return G.cube && (x2 < 0 || x2 > n2) && (y2 < 0 || y2 > n2);
-}
-
-// Corner view: the edge-halo point a corner-block point (i, j) of stagger st
-// reads in sweep mode `mode` (0 x, 1 y); cw reports the rotation sense.
-DEVI void corner_src(const Geo &G, int st, int i, int j, int mode, int &qi, int &qj, bool &cw)
-{
-    int n2 = 2 * G.n;
-    int x2 = 2 * i + stx_(st), y2 = 2 * j + sty_(st);
-    int vx = x2 < 0 ? 0 : n2, vy = y2 < 0 ? 0 : n2;
-    int c = (x2 < 0 ? 0 : 1) + (y2 < 0 ? 0 : 2);
-    cw = mode == 0 ? (c == 0 || c == 3) : (c == 1 || c == 2);
-    int dx = x2 - vx, dy = y2 - vy;
-    int qx2 = cw ? vx + dy : vx - dy;
-    int qy2 = cw ? vy - dx : vy + dx;
-    qi = floor2(qx2);
-    qj = floor2(qy2);
-}
-
-// scalar read through the corner view
-template <class T>
-DEVI T sv(const Geo &G, const T *P, int st, int i, int j, int mode)
-{
-    if (in_corner(G, st, i, j)) {
-        int qi, qj;
-        bool cw;
-        corner_src(G, st, i, j, mode, qi, qj, cw);
-        return AT(P, qi, qj);
-    }
-    return AT(P, i, j);
-}
-// x component of a pair (X at stagger stx, Y its partner) through the view;
-// sgn = false for unsigned pairs (lengths)
-template <class T>
-DEVI T pvx(const Geo &G, const T *X, const T *Y, int stx, int i, int j, int mode, bool sgn)
-{
-    if (in_corner(G, stx, i, j)) {
-        int qi, qj;
-        bool cw;
-        corner_src(G, stx, i, j, mode, qi, qj, cw);
-        T v = AT(Y, qi, qj);
-        return (cw && sgn) ? -v : v;
-    }
-    return AT(X, i, j);
-}
-template <class T>
-DEVI T pvy(const Geo &G, const T *X, const T *Y, int sty, int i, int j, int mode, bool sgn)
-{
-    if (in_corner(G, sty, i, j)) {
-        int qi, qj;
-        bool cw;
-        corner_src(G, sty, i, j, mode, qi, qj, cw);
-        T v = AT(X, qi, qj);
-        return (!cw && sgn) ? -v : v;
-    }
-    return AT(Y, i, j);
-}
-
-DEVI bool is_vertex(const Geo &G, int i, int j)
-{
-    return G.cube && (i == 0 || i == G.n) && (j == 0 || j == G.n);
-}
-
-#define KBEGIN(L)                                                    \
-    int i = ib + (int)(bk.x * blockDim.x + threadIdx.x);       \
-    int j = jlo + (int)(bk.y * blockDim.y + threadIdx.y);      \
-    if (i < ilo || i > ihi || j > jhi) return;                       \
-    int t = (int)bk.z / (L), k = (int)bk.z % (L);        \
-    (void)t; (void)k;
-
-// Plane kernels: point range [ilo, ihi] x [jlo, jhi]; thread columns start at
-// ib <= ilo, a multiple of 32 elements from the interior origin, so that every
-// wavefront's 64 columns begin on a 128-byte line (interior column 0 is
-// line-aligned in the layout).
-#define KARGS Bk bk, int ib, int ilo, int ihi, int jlo, int jhi
-
-template <class R>
-struct Mets {
-    const R *m[M_ALL];
-};
-typedef Mets<double> MetD;
-
-// plane pointer of a 2-D metric for tile t
-#define MP(M, name) ((M).m[name] + G.off0 + (long)t * G.lev)
 
 // ---------------------------------------------------------- launch timing
 static struct {
@@ -175,117 +59,7 @@ void timing_end(hipStream_t st, TimingRec &r)
     g_timing.recs.push_back(r);
 }
 
-// ---------------------------------------------------------- kernel launch
-// Every kernel of the substep path is a device function that takes its block
-// index explicitly.  It is launched either alone (k_one: the block index is
-// the hardware one), or for an ensemble of grids in one launch (k_multi: grid
-// z runs over the planes of all members, each block looks its member up in a
-// small table and reads that member's arguments from device memory; blocks
-// outside the member's own x/y extent exit at once).  Both paths run the same
-// device code, so an ensemble member computes exactly what it computes alone.
-template <class... A>
-struct Tup;
-template <>
-struct Tup<> {
-};
-template <class H, class... R>
-struct Tup<H, R...> {
-    H h;
-    Tup<R...> r;
-};
-static inline Tup<> tup() { return {}; }
-template <class H, class... R>
-static Tup<H, R...> tup(H h, R... r)
-{
-    return Tup<H, R...>{h, tup(r...)};
-}
-template <size_t I, class H, class... R>
-DEVI const auto &tget(const Tup<H, R...> &t)
-{
-    if constexpr (I == 0) return t.h;
-    else return tget<I - 1>(t.r);
-}
-template <auto F, class... A, size_t... I>
-DEVI void tcall(Bk bk, const Tup<A...> &t, std::index_sequence<I...>)
-{
-    F(bk, tget<I>(t)...);
-}
-
-// MI355X hands consecutive workgroups of a launch to its eight XCDs in turn,
-// and each XCD has its own L2.  The block index a kernel body sees is
-// therefore permuted so that every XCD works on one contiguous range of the
-// grid (x fastest, then y, then z): neighbouring tiles, which share halo
-// lines, and the planes of one tile, which share the 2-D metric terms, then
-// meet in the same L2.  The permutation is a bijection of the grid.
-constexpr unsigned NXCD = 8;
-DEVI Bk xcd_block()
-{
-    const unsigned gx = gridDim.x, gy = gridDim.y, total = gx * gy * gridDim.z;
-    const unsigned id = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
-    const unsigned q = total / NXCD, rem = total % NXCD, xcd = id % NXCD, local = id / NXCD;
-    const unsigned lid = xcd * q + (xcd < rem ? xcd : rem) + local;
-    return Bk{lid % gx, (lid / gx) % gy, lid / (gx * gy)};
-}
-
-// Minimum wavefronts per SIMD a kernel body is compiled for (its register
-// budget: at most 512 / waves VGPRs); 1 leaves the choice to the compiler.
-template <auto F>
-constexpr int kocc = 1;
-
-template <auto F, class... A>
-__global__ void __launch_bounds__(256, kocc<F>) k_one(A... a)
-{
-    F(xcd_block(), a...);
-}
-
-template <auto F, class... A>
-__global__ void __launch_bounds__(256, kocc<F>) k_multi(const Tup<A...> *__restrict__ args, const MemberBlk *__restrict__ tab,
-                                               int members)
-{
-    // one-dimensional grid over every member's own blocks back to back (no
-    // block outside a member's extent): find the member, then its block
-    const int L = (int)xcd_block().x;
-    int lo = 0, hi = members - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (tab[mid].b0 <= L) lo = mid;
-        else hi = mid - 1;
-    }
-    const MemberBlk mb = tab[lo];
-    const int gxy = mb.gx * mb.gy, local = L - mb.b0;
-    if (gxy <= 0) return;
-    const int bz = local / gxy, rem = local - bz * gxy, by = rem / mb.gx, bx = rem - by * mb.gx;
-    if (bz >= mb.gz) return;
-    tcall<F>(Bk{(unsigned)bx, (unsigned)by, (unsigned)bz}, args[lo], std::index_sequence_for<A...>{});
-}
-
-// Recording of the launch sequence of one call per member (ensemble mode).
-static thread_local Recorder *g_rec = nullptr;
-
-template <class Tp>
-static void rec_site(const char *name, const void *km, bool tunable, dim3 blk, int ex, int ey, int ez, const Tp &t)
-{
-    Recorder &R = *g_rec;
-    if (R.member == 0) {
-        Site s;
-        s.name = name;
-        s.kmulti = km;
-        s.argsz = sizeof(Tp);
-        s.tunable = tunable;
-        s.blk = blk;
-        R.sites.push_back(std::move(s));
-    }
-    if (R.pos >= R.sites.size() || R.sites[R.pos].kmulti != km) {
-        R.bad = true;
-        return;
-    }
-    Site &s = R.sites[R.pos++];
-    const char *b = (const char *)&t;
-    s.blob.insert(s.blob.end(), b, b + sizeof(Tp));
-    s.ex.push_back(ex);
-    s.ey.push_back(ey);
-    s.ez.push_back(ez);
-}
+thread_local Recorder *g_rec = nullptr;
 
 // marks the boundaries entry | substep | exit of the recorded sequence
 static void rec_mark()
@@ -295,58 +69,6 @@ static void rec_mark()
     if (R.member == 0) R.marks.push_back(R.pos);
     else if (R.mark >= R.marks.size() || R.marks[R.mark] != R.pos) R.bad = true;
     R.mark++;
-}
-
-// plane kernels: 64 x 4 threads, one point each, grid z = planes
-// Block shape of a plane kernel: 256 threads, bx consecutive points along i
-// (a multiple of 16, so that a wavefront's row segments are whole 64-byte
-// lines for FP32 and 128-byte lines for FP64).
-struct Shape {
-    int x, y;
-};
-constexpr Shape SH_DEFAULT{64, 4};
-
-template <auto F, class... A>
-static void launch2d_sh(const char *name, Shape sh, int ilo, int ihi, int jlo, int jhi, int planes,
-                        hipStream_t st, A... a)
-{
-    // columns start at an aligned point: ilo itself, or -min(bx, 32) for halo ranges
-    const int ib = ilo >= 0 ? ilo : -(sh.x < 32 ? sh.x : 32);
-    if (g_rec) {
-        rec_site(name, (const void *)k_multi<F, int, int, int, int, int, A...>, true, dim3(sh.x, sh.y, 1),
-                 ihi - ib + 1, jhi - jlo + 1, planes, tup(ib, ilo, ihi, jlo, jhi, a...));
-        return;
-    }
-    dim3 blk((unsigned)sh.x, (unsigned)sh.y, 1);
-    dim3 grd((unsigned)((ihi - ib + sh.x) / sh.x), (unsigned)((jhi - jlo + sh.y) / sh.y), (unsigned)planes);
-    bool tm = timing_wanted(name);
-    TimingRec r;
-    if (tm) timing_begin(name, st, r);
-    hipLaunchKernelGGL((k_one<F, int, int, int, int, int, A...>), grd, blk, 0, st, ib, ilo, ihi, jlo, jhi, a...);
-    if (tm) timing_end(st, r);
-}
-template <auto F, class... A>
-static void launch2d_fn(const char *name, int ilo, int ihi, int jlo, int jhi, int planes, hipStream_t st, A... a)
-{
-    launch2d_sh<F>(name, SH_DEFAULT, ilo, ihi, jlo, jhi, planes, st, a...);
-}
-#define launch2d(kern, ...) launch2d_fn<kern>(#kern, __VA_ARGS__)
-// with a block shape chosen per kernel (measured on MI355X at C192 x 79)
-#define launch2d_s(kern, shape, ...) launch2d_sh<kern>(#kern, shape, __VA_ARGS__)
-
-// generic launch with explicit shape (timed under `name`)
-template <auto F, class... A>
-static void launch_fn(const char *name, dim3 grd, dim3 blk, hipStream_t st, A... a)
-{
-    if (g_rec) {
-        rec_site(name, (const void *)k_multi<F, A...>, false, blk, (int)grd.x, (int)grd.y, (int)grd.z, tup(a...));
-        return;
-    }
-    bool tm = timing_wanted(name);
-    TimingRec r;
-    if (tm) timing_begin(name, st, r);
-    hipLaunchKernelGGL((k_one<F, A...>), grd, blk, 0, st, a...);
-    if (tm) timing_end(st, r);
 }
 
 // plain __global__ kernels outside the substep path (reductions)
@@ -1094,481 +816,8 @@ template <> constexpr int kocc<k_csw<float, false>> = FV3_CSW_OCC;
 template <> constexpr int kocc<k_csw<float, true>> = FV3_CSW_OCC;
 
 // ====================================================================
-// Vertical column work (one thread per column, k marching in FP64).
+// Pressure gradients
 // ====================================================================
-DEVI double zs_at(const Geo &G, const double *phis, int t, int i, int j, int mode)
-{
-    if (!phis) return 0.0;
-    const double *P = phis + pidx(G, 1, t, 0);
-    return sv(G, P, SC, i, j, mode) / GRAV;
-}
-
-// dz_c and the equation-of-state passes of riem_solver_c run over the
-// half-step cells i, j in [-1, n] flattened row by row (one thread per
-// column, 256 per block, grid x ceil((n + 2)^2 / 256) per tile): with
-// wavefronts aligned to the interior origin a row of n + 2 columns takes
-// ceil((n + 2) / 64) + 1 wavefronts (four at C192, two of them a third full),
-// and these walks are bound by their arithmetic, which a wavefront issues
-// whatever its active lanes.  A flattened wavefront covers at most two row
-// segments.  (The two light passes of the solve are bound by memory and keep
-// the aligned rows.)
-inline __host__ __device__ int sim1c_flat_blocks(int n) { return ((n + 2) * (n + 2) + 255) / 256; }
-
-// dz_c: half-step interface heights by first-order upwind transport of the
-// interface heights with layer-averaged area fluxes (top interface: top
-// layer), advective form, surface fixed; output the half-step thicknesses.
-template <class B>
-DEVI void k_dzc(KARGS, Geo G, MetD M, const double *delz, const double *phis, const B *ax,
-                      const B *ay, double *delzc)
-{
-    const int w = G.n + 2, p = (int)(bk.x * blockDim.x + threadIdx.x);
-    if (p >= w * w) return;
-    const int j = -1 + p / w, i = -1 + p % w;
-    (void)ib; (void)ilo; (void)ihi; (void)jlo; (void)jhi;
-    int n = G.n, nz = G.nz, t = bk.z;
-    if (!((i >= 0 && i < n) || (j >= 0 && j < n))) return;
-    double area = AT(MP(M, M_AREA), i, j);
-    double zc = zs_at(G, phis, t, i, j, 0);
-    double zw = zs_at(G, phis, t, i - 1, j, 0), ze = zs_at(G, phis, t, i + 1, j, 0);
-    double zsou = zs_at(G, phis, t, i, j - 1, 1), znor = zs_at(G, phis, t, i, j + 1, 1);
-    double zprev = zc;   // new height of the interface below
-    // Walk bottom-up.  Level K needs the thicknesses of layer K at the cell
-    // and its four neighbours and the area fluxes of layers K and K - 1 (the
-    // interface mean); the layer K - 1 values are loaded one step ahead and
-    // carried, so every value is loaded once and the next level's loads are
-    // in flight while the current one computes.
-    long o = pidx(G, nz, t, nz - 1);
-    const double *D = delz + o;
-    double dc = AT(D, i, j), dw = sv(G, D, SC, i - 1, j, 0), de = sv(G, D, SC, i + 1, j, 0);
-    double ds = sv(G, D, SC, i, j - 1, 1), dn = sv(G, D, SC, i, j + 1, 1);
-    double ax0 = (double)AT(ax + o, i, j), ax1 = (double)AT(ax + o, i + 1, j);
-    double ay0 = (double)AT(ay + o, i, j), ay1 = (double)AT(ay + o, i, j + 1);
-    for (int K = nz - 1; K >= 0; K--) {
-        double ndc = 0, ndw = 0, nde = 0, nds = 0, ndn = 0, nax0 = 0, nax1 = 0, nay0 = 0, nay1 = 0;
-        const long on = K > 0 ? pidx(G, nz, t, K - 1) : o;
-        if (K > 0) {
-            const double *Dn = delz + on;
-            ndc = AT(Dn, i, j);
-            ndw = sv(G, Dn, SC, i - 1, j, 0);
-            nde = sv(G, Dn, SC, i + 1, j, 0);
-            nds = sv(G, Dn, SC, i, j - 1, 1);
-            ndn = sv(G, Dn, SC, i, j + 1, 1);
-            nax0 = (double)AT(ax + on, i, j);
-            nax1 = (double)AT(ax + on, i + 1, j);
-            nay0 = (double)AT(ay + on, i, j);
-            nay1 = (double)AT(ay + on, i, j + 1);
-        }
-        zc -= dc;
-        zw -= dw;
-        ze -= de;
-        zsou -= ds;
-        znor -= dn;
-        double a0 = K == 0 ? ax0 : 0.5 * (nax0 + ax0);
-        double a1 = K == 0 ? ax1 : 0.5 * (nax1 + ax1);
-        double b0 = K == 0 ? ay0 : 0.5 * (nay0 + ay0);
-        double b1 = K == 0 ? ay1 : 0.5 * (nay1 + ay1);
-        double z0 = a0 > 0 ? zw : zc, z1 = a1 > 0 ? zc : ze;
-        double y0 = b0 > 0 ? zsou : zc, y1 = b1 > 0 ? zc : znor;
-        double zn = (zc * area + a0 * z0 - a1 * z1 + b0 * y0 - b1 * y1) / (area + a0 - a1 + b0 - b1);
-        AT(delzc + o, i, j) = zprev - zn;
-        zprev = zn;
-        o = on;
-        dc = ndc; dw = ndw; de = nde; ds = nds; dn = ndn;
-        ax0 = nax0; ax1 = nax1; ay0 = nay0; ay1 = nay1;
-    }
-}
-
-// Semi-implicit column solve (riem_solver_c / riem_solver3, Sec. IX-B):
-// hydrostatic interface pressure from delp (top down), nonhydrostatic
-// pressure from the equation of state, mass-weighted interface perturbation,
-// backward-Euler tridiagonal system in w (Thomas), new perturbation by a
-// top-down scan, thickness by inverting the equation of state, heights by a
-// bottom-up scan.  Elimination coefficients live in FP64 scratch columns.
-// The four passes are four launches (PASS = 1..4): one thread per column
-// each, so that the light passes run at high occupancy and the two passes
-// with the equation of state are not limited by the registers of the others.
-// Every pass walks the column in groups of levels and issues the next
-// group's loads before computing the current one.
-#ifndef FV3_SIM1_SU
-#define FV3_SIM1_SU 2
-#endif
-constexpr int SU = FV3_SIM1_SU;   // levels per prefetch group, passes 1 and 3
-constexpr int SU2 = 8;            // levels per prefetch group, passes 2 and 4
-
-// Moist column solves: the equation of state takes the virtual potential
-// temperature theta (1 + (Rv/Rd - 1) q), q the specific humidity (none: dry).
-constexpr double RVGAS = 461.5;
-constexpr double EPSV = RVGAS / RDGAS - 1.0;
-template <class B>
-DEVI double virt(const B *qv, long o)
-{
-    return qv ? 1.0 + EPSV * (double)qv[o] : 1.0;
-}
-
-// Interface value at x = 0 of the cubic whose means over four consecutive
-// layers of thicknesses da, db | dc, dd (the interface between db and dc)
-// are qa, qb | qc, qd: the derivative at the middle node of the quartic
-// through the cumulative contents at the five layer boundaries (Lagrange
-// form, contents and nodes measured from the interface).  Exact for cubics.
-DEVI double cubic_iface(double da, double db, double dc, double dd, double qa, double qb, double qc, double qd)
-{
-    const double x0 = -(da + db), x1 = -db, x3 = dc, x4 = dc + dd;
-    const double Q0 = -(qa * da + qb * db), Q1 = -qb * db, Q3 = qc * dc, Q4 = qc * dc + qd * dd;
-    const double l0 = -(x1 * x3 * x4) / ((x0 - x1) * x0 * (x0 - x3) * (x0 - x4));
-    const double l1 = -(x0 * x3 * x4) / ((x1 - x0) * x1 * (x1 - x3) * (x1 - x4));
-    const double l3 = -(x0 * x1 * x4) / ((x3 - x0) * (x3 - x1) * x3 * (x3 - x4));
-    const double l4 = -(x0 * x1 * x3) / ((x4 - x0) * (x4 - x1) * x4 * (x4 - x3));
-    return Q0 * l0 + Q1 * l1 + Q3 * l3 + Q4 * l4;
-}
-
-// SITE tells the two solves apart in profiles (0 riem_solver_c, 1 riem_solver3);
-// OFFC: off-centred solve (beta < 1), a separate instantiation so that the
-// backward-Euler passes keep their registers; PPO: interface perturbation
-// (2 mass-linear, 4 cubic where two layers lie on each side; pass 1 only);
-// MOIST: humidity in the equation of state (passes 1 and 3)
-template <class B, class TW, int PASS, int SITE, bool OFFC = false, int PPO = 2, bool MOIST = false>
-DEVI void k_sim1(KARGS, Geo G, double dt, double beta, double ptop, const B *dpi,
-                                              const B *theta, const B *qv_, const double *delz, const TW *w,
-                                              const double *phis, double *cpv, double *dpv,
-                                              double *wnv, TW *w_out, double *delz_out,
-                                              double *pfull, double *phi, int need_cross)
-{
-    int i, j;
-    if constexpr (SITE == 0 && (PASS == 1 || PASS == 3)) {
-        const int w = G.n + 2, p = (int)(bk.x * blockDim.x + threadIdx.x);
-        if (p >= w * w) return;
-        j = -1 + p / w;
-        i = -1 + p % w;
-    } else {
-        i = ib + (int)(bk.x * blockDim.x + threadIdx.x);
-        j = jlo + (int)(bk.y * blockDim.y + threadIdx.y);
-        if (i < ilo || i > ihi || j > jhi) return;
-    }
-    int n = G.n, nz = G.nz, t = bk.z;
-    if (need_cross && !((i >= 0 && i < n) || (j >= 0 && j < n))) return;
-    const double kap = RDGAS / CP_AIR, gam = 1.0 / (1.0 - kap), rgam = 1.0 / gam;
-    const long base = pidx(G, nz, t, 0) + (long)j * G.pitch + i, lev = G.lev;
-    const long basei = pidx(G, nz + 1, t, 0) + (long)j * G.pitch + i;
-    const double dt2x = dt * dt;
-    // humidity only in the moist instantiation: the dry one folds the factor away
-    const B *qv = MOIST ? qv_ : nullptr;
-    // Each pass walks the column in groups of SU levels and issues the loads
-    // of the next group before computing the current one, so that SU levels
-    // of every input are in flight per thread (the column recurrences are
-    // sequential; this is what hides HBM latency).
-    struct G4 {
-        double a[SU], b[SU], c[SU], d[SU], e[SU];   // e: humidity of the layer (0 when dry)
-    };
-    struct G2 {
-        double a[SU2], b[SU2];
-    };
-    (void)dt2x;
-    (void)rgam;
-
-    // ---- pass 1: top-down elimination; step k consumes layer k + 1
-    if constexpr (PASS == 1 && PPO == 2) {
-    double lpi_k = flog(ptop);
-    double dp0 = (double)dpi[base], th0 = (double)theta[base] * virt(qv, base), h0 = -delz[base], w0 = (double)w[base];
-    double pi_k1 = ptop + dp0, lpi_k1 = flog(pi_k1);
-    double m0 = dp0 / GRAV;
-    double pp0 = P_REF * exp(gam * flog(RDGAS * th0 * m0 / (h0 * P_REF))) - dp0 / (lpi_k1 - lpi_k);
-    double pps_k = 0.0, A_k = 0.0, cprev = 0.0, dprev = 0.0, wprev = 0.0;
-    // off-centring: coupling scaled by beta^2, the explicit part of the
-    // pressure response on the right-hand side; P* kept at the interfaces
-    // (in the interface-pressure output) for pass 3
-    const double bb = OFFC ? beta * beta : 1.0, ex = (1.0 - beta) / beta;
-    {
-        G4 cur, nxt;
-#pragma unroll
-        for (int u = 0; u < SU; u++) {
-            int kk = 1 + u;
-            long o = base + (long)kk * lev;
-            bool in = kk < nz;
-            cur.a[u] = in ? (double)dpi[o] : 0.0;
-            cur.b[u] = in ? (double)theta[o] : 0.0;
-            cur.e[u] = (in && qv) ? (double)qv[o] : 0.0;
-            cur.c[u] = in ? -delz[o] : 0.0;
-            cur.d[u] = in ? (double)w[o] : 0.0;
-        }
-        for (int k0 = 0; k0 < nz; k0 += SU) {
-            if (k0 + SU < nz) {
-#pragma unroll
-                for (int u = 0; u < SU; u++) {
-                    int kk = k0 + SU + 1 + u;
-                    long o = base + (long)kk * lev;
-                    bool in = kk < nz;
-                    nxt.a[u] = in ? (double)dpi[o] : 0.0;
-                    nxt.b[u] = in ? (double)theta[o] : 0.0;
-                    nxt.e[u] = (in && qv) ? (double)qv[o] : 0.0;
-                    nxt.c[u] = in ? -delz[o] : 0.0;
-                    nxt.d[u] = in ? (double)w[o] : 0.0;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < SU; u++) {
-                int k = k0 + u;
-                if (k < nz) {
-                    double dp1 = cur.a[u], th1 = cur.b[u] * (1.0 + EPSV * cur.e[u]), h1 = cur.c[u], w1 = cur.d[u];
-                    double pps_k1, A_k1, pi_k2 = 0, lpi_k2 = 0, m1 = 0, pp1 = 0;
-                    if (k < nz - 1) {
-                        pi_k2 = pi_k1 + dp1;
-                        lpi_k2 = flog(pi_k2);
-                        m1 = dp1 / GRAV;
-                        pp1 = P_REF * exp(gam * flog(RDGAS * th1 * m1 / (h1 * P_REF))) - dp1 / (lpi_k2 - lpi_k1);
-                        pps_k1 = (dp1 * pp0 + dp0 * pp1) / (dp0 + dp1);
-                        A_k1 = bb * gam * (pi_k1 + pps_k1) * dt2x / (0.5 * (h0 + h1));
-                    } else {
-                        pps_k1 = pp0;
-                        A_k1 = bb * gam * (pi_k1 + pps_k1) * dt2x / (0.5 * h0);
-                    }
-                    double lower = k > 0 ? -A_k : 0.0;
-                    double diag = m0 + A_k + A_k1;
-                    double upper = k < nz - 1 ? -A_k1 : 0.0;
-                    double rhs = m0 * w0 + dt * (pps_k1 - pps_k);
-                    if constexpr (OFFC) {
-                        double wa = k > 0 ? wprev : 0.0, wb = k < nz - 1 ? w1 : 0.0;
-                        rhs -= ex * (A_k1 * (w0 - wb) - A_k * (wa - w0));
-                        pfull[basei + (long)(k + 1) * lev] = pps_k1;
-                    }
-                    double piv = diag - lower * cprev;
-                    double rpiv = 1.0 / piv;
-                    double ck = upper * rpiv;
-                    double dk = (rhs - lower * dprev) * rpiv;
-                    cpv[base + (long)k * lev] = ck;
-                    dpv[base + (long)k * lev] = dk;
-                    cprev = ck;
-                    dprev = dk;
-                    wprev = w0;
-                    pi_k1 = pi_k2; lpi_k1 = lpi_k2; dp0 = dp1; m0 = m1; h0 = h1; pp0 = pp1; w0 = w1;
-                    pps_k = pps_k1; A_k = A_k1;
-                }
-            }
-            cur = nxt;
-        }
-    }
-    }
-    // ---- pass 1 with the cubic interface perturbation: step k consumes
-    // layer k + 2 (its equation of state), so that the perturbations of the
-    // layers k - 1 .. k + 2 around interface k + 1 are at hand
-    if constexpr (PASS == 1 && PPO == 4) {
-    const double bb = OFFC ? beta * beta : 1.0, ex = (1.0 - beta) / beta;
-    double dp0 = (double)dpi[base], th0 = (double)theta[base] * virt(qv, base), h0 = -delz[base], w0 = (double)w[base];
-    double pi1 = ptop + dp0, lpi1 = flog(pi1);
-    double m0 = dp0 / GRAV;
-    double pp0 = P_REF * exp(gam * flog(RDGAS * th0 * m0 / (h0 * P_REF))) - dp0 / (lpi1 - flog(ptop));
-    double dp1 = 0.0, h1 = 0.0, w1 = 0.0, pp1 = 0.0, pi2 = 0.0, lpi2 = 0.0, m1 = 0.0;
-    if (nz > 1) {
-        const long o = base + lev;
-        dp1 = (double)dpi[o];
-        const double th1 = (double)theta[o] * virt(qv, o);
-        h1 = -delz[o];
-        w1 = (double)w[o];
-        pi2 = pi1 + dp1;
-        lpi2 = flog(pi2);
-        m1 = dp1 / GRAV;
-        pp1 = P_REF * exp(gam * flog(RDGAS * th1 * m1 / (h1 * P_REF))) - dp1 / (lpi2 - lpi1);
-    }
-    double dpm = 0.0, ppm = 0.0;   // layer k - 1
-    double pps_k = 0.0, A_k = 0.0, cprev = 0.0, dprev = 0.0, wprev = 0.0;
-    {
-        G4 cur, nxt;
-#pragma unroll
-        for (int u = 0; u < SU; u++) {
-            int kk = 2 + u;
-            long o = base + (long)kk * lev;
-            bool in = kk < nz;
-            cur.a[u] = in ? (double)dpi[o] : 0.0;
-            cur.b[u] = in ? (double)theta[o] : 0.0;
-            cur.e[u] = (in && qv) ? (double)qv[o] : 0.0;
-            cur.c[u] = in ? -delz[o] : 0.0;
-            cur.d[u] = in ? (double)w[o] : 0.0;
-        }
-        for (int k0 = 0; k0 < nz; k0 += SU) {
-            if (k0 + SU < nz) {
-#pragma unroll
-                for (int u = 0; u < SU; u++) {
-                    int kk = k0 + SU + 2 + u;
-                    long o = base + (long)kk * lev;
-                    bool in = kk < nz;
-                    nxt.a[u] = in ? (double)dpi[o] : 0.0;
-                    nxt.b[u] = in ? (double)theta[o] : 0.0;
-                    nxt.e[u] = (in && qv) ? (double)qv[o] : 0.0;
-                    nxt.c[u] = in ? -delz[o] : 0.0;
-                    nxt.d[u] = in ? (double)w[o] : 0.0;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < SU; u++) {
-                int k = k0 + u;
-                if (k < nz) {
-                    const double dp2 = cur.a[u], th2 = cur.b[u] * (1.0 + EPSV * cur.e[u]), h2 = cur.c[u], w2 = cur.d[u];
-                    double pi3 = 0.0, lpi3 = 0.0, m2 = 0.0, pp2 = 0.0;
-                    if (k + 2 < nz) {
-                        pi3 = pi2 + dp2;
-                        lpi3 = flog(pi3);
-                        m2 = dp2 / GRAV;
-                        pp2 = P_REF * exp(gam * flog(RDGAS * th2 * m2 / (h2 * P_REF))) - dp2 / (lpi3 - lpi2);
-                    }
-                    double pps_k1, A_k1;
-                    if (k < nz - 1) {
-                        if (k >= 1 && k <= nz - 3) pps_k1 = cubic_iface(dpm, dp0, dp1, dp2, ppm, pp0, pp1, pp2);
-                        else pps_k1 = (dp1 * pp0 + dp0 * pp1) / (dp0 + dp1);
-                        A_k1 = bb * gam * (pi1 + pps_k1) * dt2x / (0.5 * (h0 + h1));
-                    } else {
-                        pps_k1 = pp0;
-                        A_k1 = bb * gam * (pi1 + pps_k1) * dt2x / (0.5 * h0);
-                    }
-                    double lower = k > 0 ? -A_k : 0.0;
-                    double diag = m0 + A_k + A_k1;
-                    double upper = k < nz - 1 ? -A_k1 : 0.0;
-                    double rhs = m0 * w0 + dt * (pps_k1 - pps_k);
-                    if constexpr (OFFC) {
-                        double wa = k > 0 ? wprev : 0.0, wb = k < nz - 1 ? w1 : 0.0;
-                        rhs -= ex * (A_k1 * (w0 - wb) - A_k * (wa - w0));
-                        pfull[basei + (long)(k + 1) * lev] = pps_k1;
-                    }
-                    double piv = diag - lower * cprev;
-                    double rpiv = 1.0 / piv;
-                    double ck = upper * rpiv;
-                    double dk = (rhs - lower * dprev) * rpiv;
-                    cpv[base + (long)k * lev] = ck;
-                    dpv[base + (long)k * lev] = dk;
-                    cprev = ck;
-                    dprev = dk;
-                    wprev = w0;
-                    dpm = dp0; ppm = pp0;
-                    dp0 = dp1; m0 = m1; h0 = h1; pp0 = pp1; w0 = w1; pi1 = pi2;
-                    dp1 = dp2; m1 = m2; h1 = h2; pp1 = pp2; w1 = w2; pi2 = pi3; lpi2 = lpi3;
-                    pps_k = pps_k1; A_k = A_k1;
-                }
-            }
-            cur = nxt;
-        }
-    }
-    }
-    // ---- pass 2: back substitution (bottom-up)
-    if constexpr (PASS == 2) {
-        double wv = 0.0;
-        G2 cur, nxt;
-#pragma unroll
-        for (int u = 0; u < SU2; u++) {
-            int kk = nz - 1 - u;
-            long o = base + (long)kk * lev;
-            cur.a[u] = kk >= 0 ? cpv[o] : 0.0;
-            cur.b[u] = kk >= 0 ? dpv[o] : 0.0;
-        }
-        for (int k0 = nz - 1; k0 >= 0; k0 -= SU2) {
-            if (k0 - SU2 >= 0) {
-#pragma unroll
-                for (int u = 0; u < SU2; u++) {
-                    int kk = k0 - SU2 - u;
-                    long o = base + (long)kk * lev;
-                    nxt.a[u] = kk >= 0 ? cpv[o] : 0.0;
-                    nxt.b[u] = kk >= 0 ? dpv[o] : 0.0;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < SU2; u++) {
-                int k = k0 - u;
-                if (k >= 0) {
-                    wv = cur.b[u] - cur.a[u] * wv;
-                    wnv[base + (long)k * lev] = wv;
-                }
-            }
-            cur = nxt;
-        }
-    }
-    // ---- pass 3: new perturbation (top down), thicknesses, interface pressure
-    if constexpr (PASS == 3) {
-        const double lpref = flog(P_REF);
-        double ppn = 0.0, pnk = 0.0, pik = ptop, lpik = flog(ptop);
-        if (pfull) pfull[basei] = ptop;
-        G4 cur, nxt;
-#pragma unroll
-        for (int u = 0; u < SU; u++) {
-            int kk = u;
-            long o = base + (long)kk * lev;
-            bool in = kk < nz;
-            cur.a[u] = in ? (double)dpi[o] : 0.0;
-            cur.b[u] = in ? (double)theta[o] : 0.0;
-            cur.e[u] = (in && qv) ? (double)qv[o] : 0.0;
-            cur.c[u] = in ? wnv[o] : 0.0;
-            cur.d[u] = in ? (double)w[o] : 0.0;
-        }
-        for (int k0 = 0; k0 < nz; k0 += SU) {
-            if (k0 + SU < nz) {
-#pragma unroll
-                for (int u = 0; u < SU; u++) {
-                    int kk = k0 + SU + u;
-                    long o = base + (long)kk * lev;
-                    bool in = kk < nz;
-                    nxt.a[u] = in ? (double)dpi[o] : 0.0;
-                    nxt.b[u] = in ? (double)theta[o] : 0.0;
-                    nxt.e[u] = (in && qv) ? (double)qv[o] : 0.0;
-                    nxt.c[u] = in ? wnv[o] : 0.0;
-                    nxt.d[u] = in ? (double)w[o] : 0.0;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < SU; u++) {
-                int k = k0 + u;
-                if (k < nz) {
-                    double dp = cur.a[u], th = cur.b[u] * (1.0 + EPSV * cur.e[u]), wk = cur.c[u], wo = cur.d[u];
-                    double m = dp / GRAV;
-                    double pik1 = pik + dp, lpik1 = flog(pik1);
-                    double pib = dp / (lpik1 - lpik);
-                    // the scan gives the off-centred perturbation; the new one follows
-                    double ppn1 = ppn + m * (wk - wo) / dt;
-                    double pnk1 = ppn1;
-                    if constexpr (OFFC) pnk1 = (ppn1 - (1.0 - beta) * pfull[basei + (long)(k + 1) * lev]) / beta;
-                    double pn = pib + 0.5 * (pnk + pnk1);
-                    double hn = RDGAS * th * m / P_REF * exp(rgam * (lpref - flog(pn)));
-                    cpv[base + (long)k * lev] = hn;   // reuse as the new thickness
-                    if (pfull) pfull[basei + (long)(k + 1) * lev] = pik1 + pnk1;
-                    if (w_out) w_out[base + (long)k * lev] = (TW)wk;
-                    ppn = ppn1;
-                    pnk = pnk1;
-                    pik = pik1;
-                    lpik = lpik1;
-                }
-            }
-            cur = nxt;
-        }
-    }
-    // ---- pass 4: heights (bottom up)
-    if constexpr (PASS == 4) {
-        double z = phis ? phis[pidx(G, 1, t, 0) + (long)j * G.pitch + i] / GRAV : 0.0;
-        if (phi) phi[basei + (long)nz * lev] = GRAV * z;
-        double cur[SU2], nxt[SU2];
-#pragma unroll
-        for (int u = 0; u < SU2; u++) {
-            int kk = nz - 1 - u;
-            cur[u] = kk >= 0 ? cpv[base + (long)kk * lev] : 0.0;
-        }
-        for (int k0 = nz - 1; k0 >= 0; k0 -= SU2) {
-            if (k0 - SU2 >= 0) {
-#pragma unroll
-                for (int u = 0; u < SU2; u++) {
-                    int kk = k0 - SU2 - u;
-                    nxt[u] = kk >= 0 ? cpv[base + (long)kk * lev] : 0.0;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < SU2; u++) {
-                int k = k0 - u;
-                if (k >= 0) {
-                    double hn = cur[u];
-                    z += hn;
-                    if (phi) phi[basei + (long)k * lev] = GRAV * z;
-                    if (delz_out) delz_out[base + (long)k * lev] = -hn;
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < SU2; u++) cur[u] = nxt[u];
-        }
-    }
-}
-
 // Finite-volume pressure gradient between two columns W, E over one layer:
 // contour integral of p dPhi around the quadrilateral of the two columns'
 // interfaces k, k+1, over the mean layer mass and the distance L.
@@ -2428,15 +1677,13 @@ DEVI void k_clap(KARGS, Geo G, Mets<B> M, const B *d, B *out)
                         AT(MP(M, M_RAREA_C), i, j);
 }
 
-// D-grid wind update from kinetic-energy differences and vorticity fluxes;
-// commit the transported delp, pt, w.
+// D-grid wind update from kinetic-energy differences and vorticity fluxes.
 // Optional del-2 vorticity damping (nuv > 0): the diffusive flux of the
 // relative vorticity (om - f) across each face joins the vorticity flux, so
 // u gains nuv (w(i, j-1) - w(i, j)) / dyc and v loses nuv (w(i-1, j) - w(i, j)) / dxc.
 template <class B>
 DEVI void k_dsw_update(KARGS, Geo G, Mets<B> M, const B *ke, const B *VX, const B *VY,
-                             const B *dn, const B *pn, const B *wn, const B *om, B nuv, B *u, B *v, B *delp,
-                             B *pt, B *w)
+                             const B *om, B nuv, B *u, B *v)
 {
     KBEGIN(G.nz);
     int n = G.n;
@@ -2451,60 +1698,56 @@ DEVI void k_dsw_update(KARGS, Geo G, Mets<B> M, const B *ke, const B *VX, const 
     }
     if (i < n) AT(u + o, i, j) = AT(u + o, i, j) + (AT(KE, i, j) - AT(KE, i + 1, j) + AT(VY + o, i, j)) * AT(MP(M, M_RDX), i, j) + du;
     if (j < n) AT(v + o, i, j) = AT(v + o, i, j) + (AT(KE, i, j) - AT(KE, i, j + 1) - AT(VX + o, i, j)) * AT(MP(M, M_RDY), i, j) + dv;
-    if (i < n && j < n) {
-        AT(delp + o, i, j) = AT(dn + o, i, j);
-        AT(pt + o, i, j) = AT(pn + o, i, j);
-        AT(w + o, i, j) = AT(wn + o, i, j);
-    }
 }
 
 // ====================================================================
-// dz_d: interface heights transported by fv_tp_2d (EPI_ADV, interface
-// averaged Courant numbers), surface fixed.
+// dz_d: the interface heights (kept from substep to substep, column.hip) are
+// transported by fv_tp_2d (EPI_ADV, interface averaged Courant numbers),
+// surface fixed.
 // ====================================================================
-DEVI void k_heights(KARGS, Geo G, const double *delz, const double *phis, double *zh)
+// Halo of the interface heights.  A halo column stands on the surface height
+// the caller's phis holds at that halo point, which is the neighbour cell's
+// where phis is consistent.
+DEVI void k_halo_z(Bk bk, Geo G, const HaloEnt *__restrict__ plan, int count, const double *phis, double *z, int L)
 {
-    int i = ib + (int)(bk.x * blockDim.x + threadIdx.x);
-    int j = jlo + (int)(bk.y * blockDim.y + threadIdx.y);
-    if (i < ilo || i > ihi || j > jhi) return;
-    int nz = G.nz, t = bk.z;
-    if (in_corner(G, SC, i, j)) return;
-    long c = (long)j * G.pitch + i;
-    double z = phis ? phis[pidx(G, 1, t, 0) + c] / GRAV : 0.0;
-    zh[pidx(G, nz + 1, t, nz) + c] = z;
-    for (int k = nz - 1; k >= 0; k--) {
-        z -= delz[pidx(G, nz, t, k) + c];
-        zh[pidx(G, nz + 1, t, k) + c] = z;
+    const int e = (int)(bk.x * blockDim.x + threadIdx.x);
+    if (e >= count) return;
+    const int k = (int)bk.y;
+    const HaloEnt h = plan[e];
+    double v = z[pidx(G, L, h.st, k) + h.si];
+    if (phis) {
+        const double zs = phis[pidx(G, 1, h.st, 0) + h.si] / GRAV, zd = phis[pidx(G, 1, h.dt, 0) + h.di] / GRAV;
+        if (zs != zd) v = (v - zs) + zd;
     }
+    z[pidx(G, L, h.dt, k) + h.di] = v;
 }
 
 // Mixed precision: the heights travel as FP32 deviations from a reference
 // per (tile, interface), the height at cell (0, 0).  The transport is exactly
 // translation-equivariant (PPM faces, advective inner and outer updates), so
-// only the deviations' rounding enters, not that of the full height.  Every
-// thread scans the reference column beside its own (the same loads for the
-// whole tile, served by the cache); the thread of cell (0, 0) stores it.
-DEVI void k_heights_dev(KARGS, Geo G, const double *delz, const double *phis, double *zref, float *zd)
+// only the deviations' rounding enters, not that of the full height.  The
+// thread of cell (0, 0) stores the reference.
+DEVI void k_zdev(KARGS, Geo G, const double *z, double *zref, float *zd)
 {
-    int i = ib + (int)(bk.x * blockDim.x + threadIdx.x);
-    int j = jlo + (int)(bk.y * blockDim.y + threadIdx.y);
-    if (i < ilo || i > ihi || j > jhi) return;
-    int nz = G.nz, t = bk.z;
+    KBEGIN(G.nz + 1);
     if (in_corner(G, SC, i, j)) return;
-    long c = (long)j * G.pitch + i;
-    const bool keep = i == 0 && j == 0;
-    double z = phis ? phis[pidx(G, 1, t, 0) + c] / GRAV : 0.0;
-    double zr = phis ? phis[pidx(G, 1, t, 0)] / GRAV : 0.0;
-    zd[pidx(G, nz + 1, t, nz) + c] = (float)(z - zr);
-    if (keep) zref[t * (nz + 1) + nz] = zr;
-    for (int k = nz - 1; k >= 0; k--) {
-        z -= delz[pidx(G, nz, t, k) + c];
-        zr -= delz[pidx(G, nz, t, k)];
-        zd[pidx(G, nz + 1, t, k) + c] = (float)(z - zr);
-        if (keep) zref[t * (nz + 1) + k] = zr;
-    }
+    const long o = pidx(G, G.nz + 1, t, k);
+    const double zr = AT(z + o, 0, 0);
+    AT(zd + o, i, j) = (float)(AT(z + o, i, j) - zr);
+    if (i == 0 && j == 0) zref[t * (G.nz + 1) + k] = zr;
 }
 
+// The substep commits the transported fields in the second column solve;
+// these two do it where a debug call stops before it.
+template <class B>
+DEVI void k_commit(KARGS, Geo G, const B *dn, const B *pn, const B *wn, B *delp, B *pt, B *w)
+{
+    KBEGIN(G.nz);
+    const long o = pidx(G, G.nz, t, k);
+    AT(delp + o, i, j) = AT(dn + o, i, j);
+    AT(pt + o, i, j) = AT(pn + o, i, j);
+    AT(w + o, i, j) = AT(wn + o, i, j);
+}
 DEVI void k_delz_from_zdev(KARGS, Geo G, const float *zn, const double *zref, const double *phis, double *delz)
 {
     KBEGIN(G.nz);
@@ -2962,7 +2205,7 @@ struct Work {
     B *ax, *ay, *delpc, *ptc, *wc, *ke;
     B *ut, *vt, *crx, *cry, *xfx, *yfx, *FX, *FY, *VX, *VY, *dn, *pn, *wn, *om, *qo;
     // FP64 fields
-    double *delzc, *s1, *s2, *s3, *dp1, *dp2, *mxs, *mys;
+    double *s1, *s2, *dp1, *dp2, *mxs, *mys;
     double *pkc, *gz, *zh, *zn;   // interfaces
     unsigned long long *umax;
     double *part;
@@ -2988,7 +2231,7 @@ static size_t carve(const fv3_grid *g, char *base, Work<B> *w)
     B **bulk[] = {&w->ax, &w->ay, &w->delpc, &w->ptc, &w->wc, &w->ke, &w->ut, &w->vt, &w->crx, &w->cry,
                   &w->xfx, &w->yfx, &w->FX, &w->FY, &w->VX, &w->VY, &w->dn, &w->pn, &w->wn, &w->om, &w->qo};
     for (auto p : bulk) *p = (B *)take(el * sizeof(B));
-    double **f64[] = {&w->delzc, &w->s1, &w->s2, &w->s3, &w->dp1, &w->dp2, &w->mxs, &w->mys};
+    double **f64[] = {&w->s1, &w->s2, &w->dp1, &w->dp2, &w->mxs, &w->mys};
     for (auto p : f64) *p = (double *)take(el * sizeof(double));
     double **f64i[] = {&w->pkc, &w->gz, &w->zh, &w->zn};
     for (auto p : f64i) *p = (double *)take(ei * sizeof(double));
@@ -3073,39 +2316,6 @@ static MetD metrics_d(const fv3_grid *g) { return metrics_b<double>(g); }
 // ====================================================================
 // Host orchestration of one call
 // ====================================================================
-// The first column-solve pass in the instantiation the grid's options ask
-// for: off-centring (beta < 1) and the cubic interface perturbation.
-template <class F>
-static void sim1_pass1(const fv3_grid *g, bool moist, F &&launch)
-{
-    using T_ = std::true_type;
-    using F_ = std::false_type;
-    using P2 = std::integral_constant<int, 2>;
-    using P4 = std::integral_constant<int, 4>;
-    const bool offc = g->p.beta != 1.0, cubic = g->p.pp_order == 4;
-    auto go = [&](auto m) {
-        if (offc && cubic) launch(T_{}, P4{}, m);
-        else if (offc) launch(T_{}, P2{}, m);
-        else if (cubic) launch(F_{}, P4{}, m);
-        else launch(F_{}, P2{}, m);
-    };
-    if (moist) go(T_{});
-    else go(F_{});
-}
-
-// the third column-solve pass: off-centring and humidity
-template <class F>
-static void sim1_pass3(const fv3_grid *g, bool moist, F &&launch)
-{
-    using T_ = std::true_type;
-    using F_ = std::false_type;
-    const bool offc = g->p.beta != 1.0;
-    if (offc && moist) launch(T_{}, T_{});
-    else if (offc) launch(T_{}, F_{});
-    else if (moist) launch(F_{}, T_{});
-    else launch(F_{}, F_{});
-}
-
 template <class B>
 static fv3_status substeps_t(fv3_state *s, const fv3_grid *g, double dt, int n_split, int stop_stage,
                              hipStream_t st)
@@ -3133,6 +2343,10 @@ static fv3_status substeps_t(fv3_state *s, const fv3_grid *g, double dt, int n_s
     fill(cx, el, (B)0, st);
     fill(cy, el, (B)0, st);
     copy(delp, s->dp0, el, st);
+    // interface heights: from the thicknesses once, then by every substep's
+    // second column solve
+    double *zI = W.zh;
+    column_heights(g, delz, phis, zI, st);
     rec_mark();
 
     for (int it = 0; it < n_split; it++) {
@@ -3140,12 +2354,10 @@ static fv3_status substeps_t(fv3_state *s, const fv3_grid *g, double dt, int n_s
 #define STOP(x) if (last && stop_stage == (x)) goto done
         // H-A
         halo_pair(g, g->planD, u, v, nz, st);
-        if constexpr (std::is_same<B, double>::value) {
-            halo_set<double>(g, FieldSet<double>{{delp, pt, w, delz}}, 4, nz, st);
-        } else {
-            halo_set<B>(g, FieldSet<B>{{delp, pt, w, nullptr}}, 3, nz, st);
-            halo_scalar(g, delz, nz, st);
-        }
+        halo_set<B>(g, FieldSet<B>{{delp, pt, w, nullptr}}, 3, nz, st);
+        if (g->planC.count > 0)
+            launch_fn<k_halo_z>("k_halo_z", dim3((g->planC.count + 255) / 256, nz + 1), dim3(256), st, G,
+                                (const HaloEnt *)g->planC.d, g->planC.count, phis, zI, nz + 1);
         STOP(1);
         // c_sw
         {
@@ -3162,27 +2374,13 @@ static fv3_status substeps_t(fv3_state *s, const fv3_grid *g, double dt, int n_s
         }
         STOP(2);
         // dz_c + riem_solver_c on the half-step cells
-        launch_fn<k_dzc<B>>("k_dzc<B>", dim3((unsigned)sim1c_flat_blocks(n), 1, (unsigned)T), dim3(256), st, 0, -1, n,
-                            -1, n, G, Md, (const double *)delz, phis, (const B *)W.ax, (const B *)W.ay, W.delzc);
-        const dim3 fgrd((unsigned)sim1c_flat_blocks(n), 1, (unsigned)T);
-        sim1_pass1(g, qvp != nullptr, [&](auto offc, auto ppo, auto moist) {
-            launch_fn<k_sim1<B, B, 1, 0, decltype(offc)::value, decltype(ppo)::value, decltype(moist)::value>>(
-                "k_sim1_c.p1", fgrd, dim3(256), st, 0, -1, n, -1, n, G, dt2, g->p.beta, g->p.ptop, (const B *)W.delpc,
-                (const B *)W.ptc, qvp, (const double *)W.delzc, (const B *)W.wc, phis, W.s1, W.s2, W.s3, (B *)nullptr,
-                (double *)nullptr, W.pkc, W.gz, 1);
-        });
-        launch2d_sh<k_sim1<B, B, 2, 0>>("k_sim1_c.p2", Shape{128, 2}, -1, n, -1, n, T, st, G, dt2, g->p.beta, g->p.ptop, (const B *)W.delpc,
-                       (const B *)W.ptc, qvp, (const double *)W.delzc, (const B *)W.wc, phis, W.s1, W.s2, W.s3,
-                       (B *)nullptr, (double *)nullptr, W.pkc, W.gz, 1);
-        sim1_pass3(g, qvp != nullptr, [&](auto offc, auto moist) {
-            launch_fn<k_sim1<B, B, 3, 0, decltype(offc)::value, 2, decltype(moist)::value>>(
-                "k_sim1_c.p3", fgrd, dim3(256), st, 0, -1, n, -1, n, G, dt2, g->p.beta, g->p.ptop, (const B *)W.delpc,
-                (const B *)W.ptc, qvp, (const double *)W.delzc, (const B *)W.wc, phis, W.s1, W.s2, W.s3, (B *)nullptr,
-                (double *)nullptr, W.pkc, W.gz, 1);
-        });
-        launch2d_sh<k_sim1<B, B, 4, 0>>("k_sim1_c.p4", Shape{128, 2}, -1, n, -1, n, T, st, G, dt2, g->p.beta, g->p.ptop, (const B *)W.delpc,
-                       (const B *)W.ptc, qvp, (const double *)W.delzc, (const B *)W.wc, phis, W.s1, W.s2, W.s3,
-                       (B *)nullptr, (double *)nullptr, W.pkc, W.gz, 1);
+        {
+            ColArgs<B> a{};
+            a.dt = dt2; a.beta = g->p.beta; a.ptop = g->p.ptop; a.cubic = g->p.pp_order == 4;
+            a.dpi = W.delpc; a.theta = W.ptc; a.w = W.wc; a.qv = qvp; a.phis = phis;
+            a.z = zI; a.ax = W.ax; a.ay = W.ay; a.pfull = W.pkc; a.phi = W.gz;
+            column_solve<B, 0>(g, a, st);
+        }
         STOP(3);
         launch2d_s(k_pgradc<B>, (Shape{32, 8}), 0, n, 0, n, T * ((nz + PGK - 1) / PGK), st, G, Md, dt2, (const B *)W.delpc, (const double *)W.pkc,
                  (const double *)W.gz, uc, vc);
@@ -3258,57 +2456,47 @@ static fv3_status substeps_t(fv3_state *s, const fv3_grid *g, double dt, int n_s
             fvtp(g, P, a, st);
         }
         launch2d_s(k_dsw_update<B>, (Shape{32, 8}), 0, n, 0, n, P, st, G, M, (const B *)W.ke, (const B *)W.VX, (const B *)W.VY,
-                 (const B *)W.dn, (const B *)W.pn, (const B *)W.wn, (const B *)W.om, (B)(g->p.vtdm * g->da_min), u, v,
-                 delp, pt, w);
+                 (const B *)W.om, (B)(g->p.vtdm * g->da_min), u, v);
         if (efix)
             launch_fn<k_edgefix_dsw<B>>("k_edgefix", dim3((g->edge_count + 255) / 256, nz), dim3(256), st, G,
                                         (const EdgeCell *)g->edge_cells, g->edge_count, areaB, (const B *)W.FX,
                                         (const B *)W.FY, (const B *)W.delpc, (const B *)W.ptc, (const B *)W.wc,
-                                        (const B *)W.qo, delp, pt, w, s->mfx, s->mfy);
+                                        (const B *)W.qo, W.dn, W.pn, W.wn, s->mfx, s->mfy);
+        if (last && (stop_stage == 6 || stop_stage == 7))
+            launch2d(k_commit<B>, 0, n - 1, 0, n - 1, P, st, G, (const B *)W.dn, (const B *)W.pn, (const B *)W.wn, delp,
+                     pt, w);
         STOP(6);
         // dz_d
+        // (mixed: the deviations and their references in the scratch columns)
+        float *zd = (float *)W.s1;
+        double *zref = W.s2;
         if constexpr (std::is_same<B, float>::value) {
-            // FP32 deviations from per-interface reference heights: the input
-            // and the references in the FP64 height scratch zh (the input
-            // fills half of it), the output in zn
-            const long ei = alloc_elems(g, nz + 1);
-            float *zd = (float *)W.zh, *zdn = (float *)W.zn;
-            double *zref = (double *)((float *)W.zh + ((ei + 63) / 64) * 64);
-            launch2d(k_heights_dev, -3, n + 2, -3, n + 2, T, st, G, (const double *)delz, phis, zref, zd);
+            launch2d(k_zdev, -3, n + 2, -3, n + 2, g->T * (nz + 1), st, G, (const double *)zI, zref, zd);
             FvArgs<float, B, double> a{};
             a.q = zd; a.Lq = nz + 1; a.crx = W.crx; a.cry = W.cry; a.xfx = W.xfx; a.yfx = W.yfx; a.Lc = nz;
-            a.iface = 1; a.area = M.m[M_AREA]; a.epi = EPI_ADV; a.qout = zdn;
+            a.iface = 1; a.area = M.m[M_AREA]; a.epi = EPI_ADV; a.qout = (float *)W.zn;
             fvtp(g, P, a, st);
-            launch2d(k_delz_from_zdev, 0, n - 1, 0, n - 1, P, st, G, (const float *)zdn, (const double *)zref, phis,
-                     delz);
+            if (last && stop_stage == 7)
+                launch2d(k_delz_from_zdev, 0, n - 1, 0, n - 1, P, st, G, (const float *)W.zn, (const double *)zref,
+                         phis, delz);
         } else {
-            launch2d(k_heights, -3, n + 2, -3, n + 2, T, st, G, (const double *)delz, phis, W.zh);
             FvArgs<double, B, double> a{};
-            a.q = W.zh; a.Lq = nz + 1; a.crx = W.crx; a.cry = W.cry; a.xfx = W.xfx; a.yfx = W.yfx; a.Lc = nz;
+            a.q = zI; a.Lq = nz + 1; a.crx = W.crx; a.cry = W.cry; a.xfx = W.xfx; a.yfx = W.yfx; a.Lc = nz;
             a.iface = 1; a.area = Md.m[M_AREA]; a.epi = EPI_ADV; a.qout = W.zn;
             fvtp(g, P, a, st);
-            launch2d(k_delz_from_zh, 0, n - 1, 0, n - 1, P, st, G, (const double *)W.zn, phis, delz);
+            if (last && stop_stage == 7)
+                launch2d(k_delz_from_zh, 0, n - 1, 0, n - 1, P, st, G, (const double *)W.zn, phis, delz);
         }
         STOP(7);
-        // riem_solver3
-        sim1_pass1(g, qvp != nullptr, [&](auto offc, auto ppo, auto moist) {
-            launch2d_fn<k_sim1<B, B, 1, 1, decltype(offc)::value, decltype(ppo)::value, decltype(moist)::value>>(
-                "k_sim1_3.p1", 0, n - 1, 0, n - 1, T, st, G, bdt, g->p.beta, g->p.ptop, (const B *)delp,
-                (const B *)pt, qvp, (const double *)delz, (const B *)w, phis, W.s1, W.s2, W.s3, w, delz, s->pfull,
-                s->phi, 0);
-        });
-        launch2d_fn<k_sim1<B, B, 2, 1>>("k_sim1_3.p2", 0, n - 1, 0, n - 1, T, st, G, bdt, g->p.beta, g->p.ptop, (const B *)delp,
-                       (const B *)pt, qvp, (const double *)delz, (const B *)w, phis, W.s1, W.s2, W.s3, w, delz,
-                       s->pfull, s->phi, 0);
-        sim1_pass3(g, qvp != nullptr, [&](auto offc, auto moist) {
-            launch2d_fn<k_sim1<B, B, 3, 1, decltype(offc)::value, 2, decltype(moist)::value>>(
-                "k_sim1_3.p3", 0, n - 1, 0, n - 1, T, st, G, bdt, g->p.beta, g->p.ptop, (const B *)delp,
-                (const B *)pt, qvp, (const double *)delz, (const B *)w, phis, W.s1, W.s2, W.s3, w, delz, s->pfull,
-                s->phi, 0);
-        });
-        launch2d_fn<k_sim1<B, B, 4, 1>>("k_sim1_3.p4", 0, n - 1, 0, n - 1, T, st, G, bdt, g->p.beta, g->p.ptop, (const B *)delp,
-                       (const B *)pt, qvp, (const double *)delz, (const B *)w, phis, W.s1, W.s2, W.s3, w, delz,
-                       s->pfull, s->phi, 0);
+        // riem_solver3; commits delp, pt, w, delz
+        {
+            ColArgs<B> a{};
+            a.dt = bdt; a.beta = g->p.beta; a.ptop = g->p.ptop; a.cubic = g->p.pp_order == 4;
+            a.dpi = W.dn; a.theta = W.pn; a.w = W.wn; a.qv = qvp; a.phis = phis;
+            a.zt = W.zn; a.zref = zref; a.pfull = s->pfull; a.phi = s->phi;
+            a.w_out = w; a.delp_out = delp; a.pt_out = pt; a.delz_out = delz; a.z_out = zI;
+            column_solve<B, 1>(g, a, st);
+        }
         STOP(8);
         // H-C
         halo_set<double>(g, FieldSet<double>{{s->pfull, s->phi, nullptr, nullptr}}, 2, nz + 1, st);
