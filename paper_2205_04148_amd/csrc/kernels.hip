@@ -32,6 +32,7 @@
 #include "fv3_internal.hpp"
 #include "column.hpp"
 #include "launch.hpp"
+#include "transport.hpp"
 
 namespace fv3 {
 
@@ -1364,19 +1365,15 @@ static void fvtp(const fv3_grid *g, int planes, const FvArgs<T, C, M> &a, hipStr
 {
     int ord = g->p.hord;
     if (a.epi == EPI_TRACER && g->p.hord_tr != 0) ord = g->p.hord_tr;
-    if (g->p.edge_ppm && g->p.kind == FV3_GRID_CUBED_SPHERE) {
-        FvArgs<T, C, M> b = a;
-        if constexpr (std::is_same<T, double>::value) {
-            b.dxa = g->met[M_DXA];
-            b.dya = g->met[M_DYA];
-        } else {
-            b.dxa = g->metf[M_DXA];
-            b.dya = g->metf[M_DYA];
-        }
-        fvtp_ord<T, C, M, 1>(g, ord, planes, b, st);
+    FvArgs<T, C, M> b = a;
+    if constexpr (std::is_same<T, double>::value) {
+        b.dxa = g->met[M_DXA];
+        b.dya = g->met[M_DYA];
     } else {
-        fvtp_ord<T, C, M, 0>(g, ord, planes, a, st);
+        b.dxa = g->metf[M_DXA];
+        b.dya = g->metf[M_DYA];
     }
+    fvtp_ord<T, C, M, 1>(g, ord, planes, b, st);
 }
 
 // ====================================================================
@@ -2075,6 +2072,7 @@ DEVI void k_check_finite(KARGS, Geo G, int L, const T *f, int *flags)
 }
 
 // tracer: area fluxes from the accumulated Courant numbers, scaled by 1/nsplt
+// (and the mass fluxes where mxs, mys are given)
 template <class B>
 DEVI void k_tracer_flux(KARGS, Geo G, MetD M, double rs, const B *cx, const B *cy,
                               const double *mfx, const double *mfy, B *crs, B *crys, B *xfx,
@@ -2090,7 +2088,7 @@ DEVI void k_tracer_flux(KARGS, Geo G, MetD M, double rs, const B *cx, const B *c
         AT(xfx + o, i, j) = (B)(c * pvx(G, dxa, dya, SC, up, j, 0, false) * AT(MP(M, M_DY), i, j) *
                                 AT(MP(M, M_SIN_U), i, j) / rs);
         AT(crs + o, i, j) = (B)(c / rs);
-        AT(mxs + o, i, j) = AT(mfx + o, i, j) / rs;
+        if (mxs) AT(mxs + o, i, j) = AT(mfx + o, i, j) / rs;
     }
     if (i >= -3 && i <= n + 2 && j >= 0 && j <= n) {
         double c = (double)AT(cy + o, i, j);
@@ -2098,8 +2096,19 @@ DEVI void k_tracer_flux(KARGS, Geo G, MetD M, double rs, const B *cx, const B *c
         AT(yfx + o, i, j) = (B)(c * pvy(G, dxa, dya, SC, i, up, 1, false) * AT(MP(M, M_DX), i, j) *
                                 AT(MP(M, M_SIN_V), i, j) / rs);
         AT(crys + o, i, j) = (B)(c / rs);
-        AT(mys + o, i, j) = AT(mfy + o, i, j) / rs;
+        if (mys) AT(mys + o, i, j) = AT(mfy + o, i, j) / rs;
     }
+}
+
+// interior of up to four fields, plane z of field z / planes
+template <class B>
+DEVI void k_copy_back(KARGS, Geo G, int planes, FieldSet<B> src, FieldSet<B> dst)
+{
+    KBEGIN(planes);   // t: field, k: plane
+    const B *a = t == 0 ? src.p[0] : t == 1 ? src.p[1] : t == 2 ? src.p[2] : src.p[3];
+    B *b = t == 0 ? dst.p[0] : t == 1 ? dst.p[1] : t == 2 ? dst.p[2] : dst.p[3];
+    const long o = G.off0 + (long)k * G.lev;
+    AT(b + o, i, j) = AT(a + o, i, j);
 }
 
 DEVI void k_tracer_dp(KARGS, Geo G, MetD M, const double *dp1, const double *mxs,
@@ -2390,7 +2399,23 @@ static fv3_status substeps_t(fv3_state *s, const fv3_grid *g, double dt, int n_s
         // d_sw
         launch2d_s(k_dsw_courant<B>, (Shape{16, 16}), -3, n + 2, -3, n + 2, P, st, G, M, (B)bdt, (const B *)uc, (const B *)vc, W.ut,
                  W.vt, W.crx, W.cry, W.xfx, W.yfx, g->flags);
-        {
+        const bool eppm = g->p.edge_ppm && g->p.kind == FV3_GRID_CUBED_SPHERE;
+        // the marching transports' common arguments
+        MarchArgs<B> ma{};
+        ma.crx = W.crx; ma.cry = W.cry; ma.xfx = W.xfx; ma.yfx = W.yfx; ma.area = areaB;
+        if (!eppm) {
+            MarchArgs<B> a = ma;
+            a.q[0] = delp; a.q[1] = pt; a.q[2] = w;
+            a.out[0] = W.dn; a.out[1] = W.pn; a.out[2] = W.wn;
+            a.mfx = s->mfx; a.mfy = s->mfy; a.cxa = cx; a.cya = cy;
+            // edge-flux fix-up: keep the tile-edge fluxes (the C-grid half-step
+            // arrays are free after p_grad_c)
+            if (efix) {
+                a.FX[0] = W.FX; a.FX[1] = W.delpc; a.FX[2] = W.wc;
+                a.FY[0] = W.FY; a.FY[1] = W.ptc; a.FY[2] = W.qo;
+            }
+            march_mass(g, a, st);
+        } else {
             FvArgs<B, B, B> a{};
             a.q = delp; a.Lq = nz; a.crx = W.crx; a.cry = W.cry; a.xfx = W.xfx; a.yfx = W.yfx;
             a.Lc = nz; a.area = areaB; a.epi = EPI_DELP; a.FX = W.FX; a.FY = W.FY; a.qout = W.dn;
@@ -2422,7 +2447,6 @@ static fv3_status substeps_t(fv3_state *s, const fv3_grid *g, double dt, int n_s
             hd = a;
             hc = (g->p.nord % 2 ? 1.0 : -1.0) * std::pow(g->p.d4_bg * g->da_min, g->p.nord + 1);
         }
-        const bool eppm = g->p.edge_ppm && g->p.kind == FV3_GRID_CUBED_SPHERE;
         auto omke = [&](auto lim) {
             if constexpr (sizeof(B) == 4)
                 launch_fn<k_dsw_omke<B, decltype(lim)::value>>(
@@ -2449,14 +2473,21 @@ static fv3_status substeps_t(fv3_state *s, const fv3_grid *g, double dt, int n_s
             else if (g->p.hord == 5) kee(std::integral_constant<int, 5>{});
             else kee(std::integral_constant<int, 8>{});
         }
-        {
+        if (!eppm) {
+            MarchArgs<B> a = ma;
+            a.q[0] = W.om;
+            a.ke = W.ke; a.u = u; a.v = v;
+            a.rdx = M.m[M_RDX]; a.rdy = M.m[M_RDY]; a.rdxc = M.m[M_RDXC]; a.rdyc = M.m[M_RDYC]; a.fc = M.m[M_FC];
+            a.nuv = (B)(g->p.vtdm * g->da_min);
+            march_wind(g, a, st);
+        } else {
             FvArgs<B, B, B> a{};
             a.q = W.om; a.Lq = nz; a.crx = W.crx; a.cry = W.cry; a.xfx = W.xfx; a.yfx = W.yfx; a.Lc = nz;
             a.area = areaB; a.epi = EPI_FLUX; a.FX = W.VX; a.FY = W.VY;
             fvtp(g, P, a, st);
-        }
-        launch2d_s(k_dsw_update<B>, (Shape{32, 8}), 0, n, 0, n, P, st, G, M, (const B *)W.ke, (const B *)W.VX, (const B *)W.VY,
+            launch2d_s(k_dsw_update<B>, (Shape{32, 8}), 0, n, 0, n, P, st, G, M, (const B *)W.ke, (const B *)W.VX, (const B *)W.VY,
                  (const B *)W.om, (B)(g->p.vtdm * g->da_min), u, v);
+        }
         if (efix)
             launch_fn<k_edgefix_dsw<B>>("k_edgefix", dim3((g->edge_count + 255) / 256, nz), dim3(256), st, G,
                                         (const EdgeCell *)g->edge_cells, g->edge_count, areaB, (const B *)W.FX,
@@ -2468,23 +2499,29 @@ static fv3_status substeps_t(fv3_state *s, const fv3_grid *g, double dt, int n_s
         STOP(6);
         // dz_d
         // (mixed: the deviations and their references in the scratch columns)
-        float *zd = (float *)W.s1;
         double *zref = W.s2;
-        if constexpr (std::is_same<B, float>::value) {
+        if (!eppm) {
+            MarchArgs<B> a = ma;
+            a.z = zI; a.zref = zref; a.out[0] = (B *)W.zn;
+            march_height(g, a, st);
+        } else if constexpr (std::is_same<B, float>::value) {
+            float *zd = (float *)W.s1;
             launch2d(k_zdev, -3, n + 2, -3, n + 2, g->T * (nz + 1), st, G, (const double *)zI, zref, zd);
             FvArgs<float, B, double> a{};
             a.q = zd; a.Lq = nz + 1; a.crx = W.crx; a.cry = W.cry; a.xfx = W.xfx; a.yfx = W.yfx; a.Lc = nz;
             a.iface = 1; a.area = M.m[M_AREA]; a.epi = EPI_ADV; a.qout = (float *)W.zn;
             fvtp(g, P, a, st);
-            if (last && stop_stage == 7)
-                launch2d(k_delz_from_zdev, 0, n - 1, 0, n - 1, P, st, G, (const float *)W.zn, (const double *)zref,
-                         phis, delz);
         } else {
             FvArgs<double, B, double> a{};
             a.q = zI; a.Lq = nz + 1; a.crx = W.crx; a.cry = W.cry; a.xfx = W.xfx; a.yfx = W.yfx; a.Lc = nz;
             a.iface = 1; a.area = Md.m[M_AREA]; a.epi = EPI_ADV; a.qout = W.zn;
             fvtp(g, P, a, st);
-            if (last && stop_stage == 7)
+        }
+        if (last && stop_stage == 7) {
+            if constexpr (std::is_same<B, float>::value)
+                launch2d(k_delz_from_zdev, 0, n - 1, 0, n - 1, P, st, G, (const float *)W.zn, (const double *)zref,
+                         phis, delz);
+            else
                 launch2d(k_delz_from_zh, 0, n - 1, 0, n - 1, P, st, G, (const double *)W.zn, phis, delz);
         }
         STOP(7);
@@ -2595,8 +2632,58 @@ static fv3_status tracer_t(void *const *q, int nq, fv3_state *s, const fv3_grid 
     }
     double rs = (double)nsplt;
     const bool efix = g->p.edge_fix && g->edge_count > 0;
+    const bool eppm = g->p.edge_ppm && g->p.kind == FV3_GRID_CUBED_SPHERE;
     launch2d_s(k_tracer_flux<B>, (Shape{128, 2}), -3, n + 3, -3, n + 3, P, st, G, Md, rs, (const B *)cx, (const B *)cy,
-             (const double *)s->mfx, (const double *)s->mfy, W.crx, W.cry, W.xfx, W.yfx, W.mxs, W.mys);
+             (const double *)s->mfx, (const double *)s->mfy, W.crx, W.cry, W.xfx, W.yfx, eppm ? W.mxs : (double *)nullptr,
+             eppm ? W.mys : (double *)nullptr);
+    if (!eppm) {
+        // up to MARCH_TRACERS fields at a time through all sub-cycles, each
+        // sub-cycle from the fields to scratch or back
+        B *scr[MARCH_TRACERS] = {W.qo, W.dn, W.pn, W.wn};
+        B *efx[MARCH_TRACERS] = {W.delpc, W.wc, W.ut, W.VX}, *efy[MARCH_TRACERS] = {W.ptc, W.ke, W.vt, W.VY};
+        for (int m0 = 0, nf = 0; m0 < nq; m0 += nf) {
+            MarchArgs<B> a{};
+            a.crx = W.crx; a.cry = W.cry; a.xfx = W.xfx; a.yfx = W.yfx; a.area = M.m[M_AREA];
+            a.mx = s->mfx; a.my = s->mfy; a.area64 = Md.m[M_AREA]; a.rs = rs;
+            FieldSet<B> src{}, dst{};
+            for (nf = 0; nf < (sizeof(B) == 4 ? MARCH_TRACERS : 3) && m0 + nf < nq; nf++) {
+                // a field given twice is transported twice, one after the other
+                bool again = false;
+                for (int f = 0; f < nf; f++) again |= src.p[f] == (B *)q[m0 + nf];
+                if (again) break;
+                src.p[nf] = (B *)q[m0 + nf];
+                dst.p[nf] = scr[nf];
+                if (efix) {
+                    a.FX[nf] = efx[nf];
+                    a.FY[nf] = efy[nf];
+                }
+            }
+            a.dp1 = s->dp0;
+            for (int itr = 0; itr < nsplt; itr++) {
+                halo_set<B>(g, src, nf, nz, st);
+                for (int f = 0; f < nf; f++) {
+                    a.q[f] = src.p[f];
+                    a.out[f] = dst.p[f];
+                }
+                a.dp2 = itr + 1 < nsplt || efix ? (itr % 2 ? W.dp2 : W.dp1) : nullptr;
+                march_tracer(g, nf, a, st);
+                if (efix)
+                    for (int f = 0; f < nf; f++)
+                        launch_fn<k_edgefix_q<B>>("k_edgefix_q", dim3((g->edge_count + 255) / 256, nz), dim3(256), st, G,
+                                                  (const EdgeCell *)g->edge_cells, g->edge_count,
+                                                  (const B *)M.m[M_AREA], (const B *)a.FX[f], (const B *)a.FY[f],
+                                                  (const double *)a.dp2, dst.p[f]);
+                a.dp1 = a.dp2;
+                std::swap(src, dst);
+            }
+            if (nsplt % 2) {
+                launch2d_s(k_copy_back<B>, (Shape{128, 2}), 0, n - 1, 0, n - 1, P * nf, st, G, P, src, dst);
+                std::swap(src, dst);
+            }
+            halo_set<B>(g, src, nf, nz, st);   // leave consistent halos
+        }
+        return hipGetLastError() == hipSuccess ? FV3_OK : FV3_EDEVICE;
+    }
     copy(s->dp0, W.dp1, el, st);
     double *dp1 = W.dp1, *dp2 = W.dp2;
     for (int itr = 0; itr < nsplt; itr++) {
