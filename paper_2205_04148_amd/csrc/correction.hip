@@ -86,31 +86,44 @@ __global__ void k_coarsen_winds(Geo F, Geo C, int r, const double *__restrict__ 
 // X[row][c] = (x - mean[c]) * inv_std[c]; rows ordered (tile, j, i), columns
 // (field, level) with fields ua, va, pt, w, delp.  A value outside
 // [lo - 6, hi + 6] (normalised units) or not finite sets bit 0 of *flag.
+// The fields are contiguous along i, X along the columns: a block takes 64
+// rows x 64 columns through LDS, reading along the rows and writing along the
+// columns (48 us with every lane of a wavefront on another level's plane, 21
+// us so, at 13824 x 395).
 template <class B>
-__global__ void k_features(Geo G, const B *__restrict__ u, const B *__restrict__ v, const B *__restrict__ pt,
-                           const B *__restrict__ w, const B *__restrict__ delp, const float *__restrict__ mean,
-                           const float *__restrict__ inv_std, const float *__restrict__ lo,
-                           const float *__restrict__ hi, float *X, int *flag)
+__global__ void __launch_bounds__(256) k_features(Geo G, const B *__restrict__ u, const B *__restrict__ v,
+                                                  const B *__restrict__ pt, const B *__restrict__ w,
+                                                  const B *__restrict__ delp, const float *__restrict__ mean,
+                                                  const float *__restrict__ inv_std, const float *__restrict__ lo,
+                                                  const float *__restrict__ hi, float *X, int *flag)
 {
-    const int n = G.n, nz = G.nz, F = 5 * nz;
-    long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    long total = (long)G.T * n * n * F;
-    if (e >= total) return;
-    long row = e / F;
-    int c = (int)(e % F);
-    int f = c / nz, k = c % nz;
-    int i = (int)(row % n), j = (int)((row / n) % n), t = (int)(row / ((long)n * n));
-    double x;
-    switch (f) {
-    case 0: x = 0.5 * ((double)u[at(G, nz, t, k, j, i)] + (double)u[at(G, nz, t, k, j + 1, i)]); break;
-    case 1: x = 0.5 * ((double)v[at(G, nz, t, k, j, i)] + (double)v[at(G, nz, t, k, j, i + 1)]); break;
-    case 2: x = (double)pt[at(G, nz, t, k, j, i)]; break;
-    case 3: x = (double)w[at(G, nz, t, k, j, i)]; break;
-    default: x = (double)delp[at(G, nz, t, k, j, i)]; break;
+    __shared__ float tl[64][65];
+    const int n = G.n, nz = G.nz, F = 5 * nz, tx = (int)threadIdx.x & 63, ty = (int)threadIdx.x >> 6;
+    const long rows = (long)G.T * n * n, r0 = (long)blockIdx.x * 64;
+    const int c0 = (int)blockIdx.y * 64;
+    const long row = r0 + tx < rows ? r0 + tx : rows - 1;
+    const int i = (int)(row % n), j = (int)((row / n) % n), t = (int)(row / ((long)n * n));
+    bool out = false;
+#pragma unroll
+    for (int q = 0; q < 16; q++) {
+        // one column per wavefront: a scalar, its plane and coefficients too
+        const int c = min(__builtin_amdgcn_readfirstlane(c0 + ty + 4 * q), F - 1);
+        const int f = c / nz, k = c - f * nz;
+        const B *p = f == 0 ? u : f == 1 ? v : f == 2 ? pt : f == 3 ? w : delp;
+        const long e = at(G, nz, t, k, j, i);
+        double x = (double)p[e];
+        if (f < 2) x = 0.5 * (x + (double)p[e + (f == 0 ? G.pitch : 1)]);   // mean of the cell's two faces
+        const float z = (float)((x - (double)mean[c]) * (double)inv_std[c]);
+        tl[ty + 4 * q][tx] = z;
+        if (flag && !(z >= lo[c] - 6.0f && z <= hi[c] + 6.0f)) out = true;
     }
-    float z = (float)((x - (double)mean[c]) * (double)inv_std[c]);
-    X[e] = z;
-    if (flag && !(z >= lo[c] - 6.0f && z <= hi[c] + 6.0f)) atomicOr(flag, 1);
+    if (out) atomicOr(flag, 1);
+    __syncthreads();
+#pragma unroll 4
+    for (int q = 0; q < 16; q++) {
+        const long r = r0 + ty + 4 * q;
+        if (r < rows && c0 + tx < F) X[r * F + c0 + tx] = tl[tx][ty + 4 * q];
+    }
 }
 
 __global__ void k_corr_check(const float *__restrict__ Y, long count, int *flag)
@@ -121,26 +134,44 @@ __global__ void k_corr_check(const float *__restrict__ Y, long count, int *flag)
 }
 
 // physical tendencies from normalised outputs; pt updated in place, the wind
-// increments (tile components, at cells) stored for the face pass
+// increments (tile components, at cells) stored for the face pass.  A block
+// takes 64 rows of Y x 32 levels of the three fields through LDS, reading
+// along Y's columns and updating along i.
 template <class B>
-__global__ void k_corr_cells(Geo G, const float *__restrict__ Y, const float *__restrict__ ymean,
-                             const float *__restrict__ ystd, double seconds, const int *__restrict__ flag,
-                             B *pt, double *dU, double *dV)
+__global__ void __launch_bounds__(256) k_corr_cells(Geo G, const float *__restrict__ Y,
+                                                    const float *__restrict__ ymean, const float *__restrict__ ystd,
+                                                    double seconds, const int *__restrict__ flag, B *pt, double *dU,
+                                                    double *dV)
 {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    int j = blockIdx.y * blockDim.y + threadIdx.y;
-    if (i >= G.n || j >= G.n) return;
+    __shared__ float tl[3][32][65];
     if (*flag) return;
-    int t = blockIdx.z / G.nz, k = blockIdx.z % G.nz, nz = G.nz;
-    long row = ((long)t * G.n + j) * G.n + i;
-    const float *y = Y + row * 3 * nz;
-    double du = (double)y[k] * ystd[k] + ymean[k];
-    double dv = (double)y[nz + k] * ystd[nz + k] + ymean[nz + k];
-    double dp = (double)y[2 * nz + k] * ystd[2 * nz + k] + ymean[2 * nz + k];
-    long e = at(G, nz, t, k, j, i);
-    dU[e] = seconds * du;
-    dV[e] = seconds * dv;
-    pt[e] = (B)((double)pt[e] + seconds * dp);
+    const int n = G.n, nz = G.nz, k0 = (int)blockIdx.y * 32, tid = (int)threadIdx.x;
+    const long rows = (long)G.T * n * n, r0 = (long)blockIdx.x * 64;
+#pragma unroll 4
+    for (int q = 0; q < 8; q++) {
+        const int kk = tid & 31, rr = (tid >> 5) + 8 * q;
+        const bool in = k0 + kk < nz && r0 + rr < rows;
+        const float *y = Y + (r0 + rr) * 3 * nz + k0 + kk;
+#pragma unroll
+        for (int f = 0; f < 3; f++) tl[f][kk][rr] = in ? y[f * nz] : 0.f;
+    }
+    __syncthreads();
+    const int tx = tid & 63, ty = tid >> 6;
+    const long row = r0 + tx;
+    if (row >= rows) return;
+    const int i = (int)(row % n), j = (int)((row / n) % n), t = (int)(row / ((long)n * n));
+#pragma unroll 4
+    for (int q = 0; q < 8; q++) {
+        const int k = k0 + ty + 4 * q;
+        if (k >= nz) break;
+        const double du = (double)tl[0][k - k0][tx] * ystd[k] + ymean[k];
+        const double dv = (double)tl[1][k - k0][tx] * ystd[nz + k] + ymean[nz + k];
+        const double dp = (double)tl[2][k - k0][tx] * ystd[2 * nz + k] + ymean[2 * nz + k];
+        const long e = at(G, nz, t, k, j, i);
+        dU[e] = seconds * du;
+        dV[e] = seconds * dv;
+        pt[e] = (B)((double)pt[e] + seconds * dp);
+    }
 }
 
 // D-grid u on y-faces and v on x-faces take the mean increment of the two
@@ -180,8 +211,8 @@ template <class B>
 void features_t(const fv3_state *s, const fv3_grid *g, const fv3_feature_norm *nm, float *X, int *flag,
                 hipStream_t st)
 {
-    long total = (long)g->T * g->n * g->n * 5 * g->nz;
-    hipLaunchKernelGGL(k_features<B>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, g->geo,
+    const long rows = (long)g->T * g->n * g->n;
+    hipLaunchKernelGGL(k_features<B>, dim3((unsigned)((rows + 63) / 64), (unsigned)((5 * g->nz + 63) / 64)), dim3(256), 0, st, g->geo,
                        (const B *)s->u, (const B *)s->v, (const B *)s->pt, (const B *)s->w, (const B *)s->delp,
                        nm->mean, nm->inv_std, nm->lo, nm->hi, X, flag);
 }
@@ -195,8 +226,8 @@ fv3_status correct_t(fv3_state *s, const fv3_grid *g, const float *Y, const floa
     long rows = (long)g->T * g->n * g->n, count = rows * 3 * g->nz;
     hipLaunchKernelGGL(k_corr_check, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, Y, count, flag);
     dim3 blk(64, 4);
-    dim3 gc((unsigned)((g->n + 63) / 64), (unsigned)((g->n + 3) / 4), (unsigned)(g->T * g->nz));
-    hipLaunchKernelGGL(k_corr_cells<B>, gc, blk, 0, st, g->geo, Y, ymean, ystd, seconds, (const int *)flag,
+    dim3 gc((unsigned)((rows + 63) / 64), (unsigned)((g->nz + 31) / 32));
+    hipLaunchKernelGGL(k_corr_cells<B>, gc, dim3(256), 0, st, g->geo, Y, ymean, ystd, seconds, (const int *)flag,
                        (B *)s->pt, dU, dV);
     fv3_status r = run_halo_pair_cells(g, dU, dV, g->nz, 1, st);
     if (r != FV3_OK) return r;

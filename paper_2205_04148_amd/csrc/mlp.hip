@@ -4,14 +4,18 @@
 // tendencies to a coarse state.
 //
 // Matrix products use gfx950's v_mfma_f32_16x16x32_bf16: one instruction
-// adds a 16 x 32 by 32 x 16 BF16 product to a 16 x 16 FP32 tile.  Operand strides are explicit so the
-// transposed products of the backward pass (X^T dZ, dZ W^T) read the stored
-// row-major matrices in place.  The network is small (395 -> 256 -> 256 ->
-// 237), so these are plain register-tiled products, not a library GEMM.
+// adds a 16 x 32 by 32 x 16 BF16 product to a 16 x 16 FP32 tile.  Every
+// operand is kept with its contraction index contiguous and padded to 32
+// (activations and errors also transposed, for the weight gradients; weights
+// in both orders), so that a lane reads its eight values of an MFMA operand as
+// one 16-byte word straight from memory: the network is small (395 -> 256 ->
+// 256 -> 237), its operands stay in L2, and what bounds a product is the
+// latency of its loads, which are issued several chunks ahead.
 #include <cmath>
 #include <cstdint>
 #include <algorithm>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -37,198 +41,341 @@ DEVI bf16_t to_bf16(float f)
 }
 DEVI float from_bf16(bf16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
-// --------------------------------------------------------------- GEMM
-// C(m, n) = sum_k A(m, k) B(k, n) [+ bias(n)], with A(m, k) = A[m*sam + k*sak]
-// and B(k, n) = B[k*sbk + n*sbn] (BF16), C row-major FP32 (ldc).  Optional
-// epilogue: tanh, and a BF16 copy of the result (ldcb).
-enum { GE_NONE = 0, GE_TANH = 1 };
+// ------------------------------------------------------------- products
+constexpr int PADK = 32;   // widths and the transposed row count are padded to this
+constexpr int pad32(int x) { return (x + PADK - 1) / PADK * PADK; }
 
-// Block tile 64 x 64 (four wavefronts, 32 x 32 each = 2 x 2 MFMA tiles), K
-// staged through LDS 32 at a time.  Operands are loaded with the thread
-// index running along whichever of their two dimensions is contiguous, and
-// stored in LDS k-contiguous (A as [m][k], B as [n][k]) so that each lane
-// reads its eight k-consecutive values of an MFMA operand (lane group g of
-// 16 lanes holds k = 8g .. 8g + 7 of its row or column) as one 16-byte word.
-// Accumulation runs over K in ascending chunks of 32, one MFMA per chunk
-// and output tile.
-constexpr int GBM = 64, GBN = 64, GBK = 32, GKP = GBK + 8;
-
-__global__ void __launch_bounds__(256) k_gemm_bf16(int M, int N, int K, const bf16_t *A, long sam, long sak,
-                                                   const bf16_t *Bm, long sbk, long sbn, const float *bias,
-                                                   int epi, float *C, long ldc, bf16_t *Cb, long ldcb)
+// acc[x][y] += A rows m0 + 16 x .. by B rows n0 + 16 y .. over K (a multiple
+// of 32), both with k contiguous.  Chunks of 32 in ascending order, one MFMA
+// per chunk and tile; the loads of PF chunks are in flight ahead of them.
+template <int TM, int TN, int PF>
+DEVI void product(const bf16_t *A, long lda, const bf16_t *B, long ldb, int m0, int n0, int K, v4f (&acc)[TM][TN])
 {
-    __shared__ __align__(16) bf16_t sA[GBM * GKP];
-    __shared__ __align__(16) bf16_t sB[GBN * GKP];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int m0 = blockIdx.y * GBM, n0 = blockIdx.x * GBN;
-    const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
-    const int r = lane & 15, g = lane >> 4;
-    v4f acc[2][2];
-    for (int x = 0; x < 2; x++)
-        for (int y = 0; y < 2; y++) acc[x][y] = v4f{0.f, 0.f, 0.f, 0.f};
-    const bool a_kc = sak == 1, b_nc = sbn == 1;
-    for (int k0 = 0; k0 < K; k0 += GBK) {
-        // A tile: 64 x 32, eight values per thread
-        if (a_kc) {
-            int m = tid >> 2, kq = (tid & 3) * 8;
-            int gm = m0 + m;
+    const int lane = (int)threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    const bf16_t *pa[TM], *pb[TN];
 #pragma unroll
-            for (int q = 0; q < 8; q++) {
-                int gk = k0 + kq + q;
-                sA[m * GKP + kq + q] = (gm < M && gk < K) ? A[(long)gm * sam + gk] : (bf16_t)0;
-            }
-        } else {
-            int kk = tid >> 3, mq = (tid & 7) * 8;
-            int gk = k0 + kk;
+    for (int x = 0; x < TM; x++) pa[x] = A + (long)(m0 + 16 * x + r) * lda + 8 * g;
 #pragma unroll
-            for (int q = 0; q < 8; q++) {
-                int gm = m0 + mq + q;
-                sA[(mq + q) * GKP + kk] = (gm < M && gk < K) ? A[(long)gm * sam + (long)gk * sak] : (bf16_t)0;
+    for (int y = 0; y < TN; y++) pb[y] = B + (long)(n0 + 16 * y + r) * ldb + 8 * g;
+    const int nc = K / 32;
+    v8s ca[PF][TM], cb[PF][TN], na[PF][TM], nb_[PF][TN];
+    auto load = [&](int c0, v8s (&a)[PF][TM], v8s (&b)[PF][TN]) {
+#pragma unroll
+        for (int q = 0; q < PF; q++) {
+            const long o = 32L * min(c0 + q, nc - 1);   // chunks past the end repeat the last and are not used
+#pragma unroll
+            for (int x = 0; x < TM; x++) a[q][x] = *(const v8s *)(pa[x] + o);
+#pragma unroll
+            for (int y = 0; y < TN; y++) b[q][y] = *(const v8s *)(pb[y] + o);
+        }
+    };
+    load(0, ca, cb);
+    for (int c0 = 0; c0 < nc; c0 += PF) {
+        if (c0 + PF < nc) load(c0 + PF, na, nb_);
+#pragma unroll
+        for (int q = 0; q < PF; q++) {
+            if (c0 + q < nc) {
+#pragma unroll
+                for (int x = 0; x < TM; x++)
+#pragma unroll
+                    for (int y = 0; y < TN; y++)
+                        acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(v8bf, ca[q][x]), __builtin_bit_cast(v8bf, cb[q][y]), acc[x][y], 0, 0, 0);
             }
         }
-        // B tile: 32 x 64, stored [n][k]
-        if (b_nc) {
-            int kk = tid >> 3, nq = (tid & 7) * 8;
-            int gk = k0 + kk;
 #pragma unroll
-            for (int q = 0; q < 8; q++) {
-                int gn = n0 + nq + q;
-                sB[(nq + q) * GKP + kk] = (gn < N && gk < K) ? Bm[(long)gk * sbk + gn] : (bf16_t)0;
-            }
-        } else {
-            int nn = tid >> 2, kq = (tid & 3) * 8;
-            int gn = n0 + nn;
+        for (int q = 0; q < PF; q++) {
 #pragma unroll
-            for (int q = 0; q < 8; q++) {
-                int gk = k0 + kq + q;
-                sB[nn * GKP + kq + q] = (gn < N && gk < K) ? Bm[(long)gk * sbk + (long)gn * sbn] : (bf16_t)0;
-            }
+            for (int x = 0; x < TM; x++) ca[q][x] = na[q][x];
+#pragma unroll
+            for (int y = 0; y < TN; y++) cb[q][y] = nb_[q][y];
         }
-        __syncthreads();
-        static_assert(GBK == 32, "one 16x16x32 MFMA per K chunk");
-        {
-            v8bf a[2], b[2];
-#pragma unroll
-            for (int x = 0; x < 2; x++) {
-                const v8s va = *(const v8s *)(sA + (wm + 16 * x + r) * GKP + 8 * g);
-                const v8s vb = *(const v8s *)(sB + (wn + 16 * x + r) * GKP + 8 * g);
-                a[x] = __builtin_bit_cast(v8bf, va);
-                b[x] = __builtin_bit_cast(v8bf, vb);
-            }
-#pragma unroll
-            for (int x = 0; x < 2; x++)
-#pragma unroll
-                for (int y = 0; y < 2; y++) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[x], b[y], acc[x][y], 0, 0, 0);
-        }
-        __syncthreads();
     }
-    // lane holds rows 4g..4g+3 of column r of each 16 x 16 tile
-#pragma unroll
-    for (int x = 0; x < 2; x++)
-#pragma unroll
-        for (int y = 0; y < 2; y++)
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                int m = m0 + wm + 16 * x + 4 * g + q, n = n0 + wn + 16 * y + r;
-                if (m >= M || n >= N) continue;
-                float v = acc[x][y][q] + (bias ? bias[n] : 0.f);
-                if (epi == GE_TANH) v = tanhf(v);
-                if (C) C[(long)m * ldc + n] = v;
-                if (Cb) Cb[(long)m * ldcb + n] = to_bf16(v);
-            }
 }
 
-static void gemm(int M, int N, int K, const bf16_t *A, long sam, long sak, const bf16_t *B, long sbk, long sbn,
-                 const float *bias, int epi, float *C, long ldc, bf16_t *Cb, long ldcb, hipStream_t st)
+// Epilogue outputs of a layer product; null pointers are skipped.  Rows from
+// `rows` up to the next multiple of 32 are zero in the transposed copies (they
+// are contracted over).
+struct LayerOut {
+    float *f;          // FP32 [row][ld]
+    bf16_t *b, *bt;    // BF16 [row][ld] and [column][ldt]
+    int ld;
+    long ldt;
+};
+enum { LY_TANH = 0, LY_OUT = 1, LY_LOSS = 2, LY_BACK = 3 };
+
+// One layer over all rows: 64 x 64 per block, 32 x 32 per wavefront (1024
+// wavefronts at 4096 x 256).
+//   LY_TANH  tanh(x W + b)
+//   LY_OUT   x W + b into Y (rows x out)
+//   LY_LOSS  error of the mean squared loss, scale (x W + b - T), and the
+//            squared residuals summed per row and 16 columns
+//   LY_BACK  (error W^T) (1 - h^2), h the layer's FP32 activation
+// One wavefront tile takes four chunks ahead: 13 chunks are 4 load latencies
+// instead of 13 with two barriers each (55 -> 24 us at 13824 x 256 x 400).
+template <int KIND>
+__global__ void __launch_bounds__(256) k_layer(int rows, int N, int K, const bf16_t *A, long lda, const bf16_t *B,
+                                               long ldb, const float *bias, const float *h, LayerOut O, float *Y,
+                                               const float *T, int out, float scale, float *sq)
 {
-    dim3 grd((unsigned)((N + GBN - 1) / GBN), (unsigned)((M + GBM - 1) / GBM));
-    hipLaunchKernelGGL(k_gemm_bf16, grd, dim3(256), 0, st, M, N, K, A, sam, sak, B, sbk, sbn, bias, epi, C, ldc,
-                       Cb, ldcb);
+    const int lane = (int)threadIdx.x & 63, w = (int)threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
+    const int m0 = (int)blockIdx.y * 64 + (w >> 1) * 32, n0 = (int)blockIdx.x * 64 + (w & 1) * 32;
+    if (m0 >= pad32(rows) || n0 >= N) return;
+    v4f acc[2][2];
+#pragma unroll
+    for (int x = 0; x < 2; x++)
+#pragma unroll
+        for (int y = 0; y < 2; y++) acc[x][y] = v4f{0.f, 0.f, 0.f, 0.f};
+    product<2, 2, 4>(A, lda, B, ldb, m0, n0, K, acc);
+    // a lane holds rows 4g .. 4g + 3 of column r of each 16 x 16 tile
+#pragma unroll
+    for (int x = 0; x < 2; x++)
+#pragma unroll
+        for (int y = 0; y < 2; y++) {
+            const int n = n0 + 16 * y + r;
+            const float bn = KIND == LY_BACK ? 0.f : bias[n];
+            bf16_t tb[4];
+            float s4[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const int m = m0 + 16 * x + 4 * g + q;
+                const bool in = m < rows;
+                float v = acc[x][y][q];
+                s4[q] = 0.f;
+                if constexpr (KIND == LY_TANH) v = tanhf(v + bn);
+                if constexpr (KIND == LY_OUT) {
+                    if (in && n < out) Y[(long)m * out + n] = v + bn;
+                }
+                if constexpr (KIND == LY_LOSS) {
+                    const bool real = in && n < out;
+                    const float res = real ? v + bn - T[(long)m * out + n] : 0.f;
+                    v = scale * res;
+                    s4[q] = res * res;
+                }
+                if constexpr (KIND == LY_BACK) {
+                    const float a = in ? h[(long)m * O.ld + n] : 0.f;
+                    v = v * (1.f - a * a);
+                }
+                if constexpr (KIND != LY_OUT) {
+                    const bf16_t hb = to_bf16(v);
+                    if (in) {
+                        if (O.f) O.f[(long)m * O.ld + n] = v;
+                        if (O.b) O.b[(long)m * O.ld + n] = hb;
+                    }
+                    tb[q] = in ? hb : (bf16_t)0;
+                }
+            }
+            if constexpr (KIND != LY_OUT) {
+                typedef bf16_t b4 __attribute__((ext_vector_type(4)));
+                if (O.bt) *(b4 *)(O.bt + (long)n * O.ldt + m0 + 16 * x + 4 * g) = b4{tb[0], tb[1], tb[2], tb[3]};
+            }
+            if constexpr (KIND == LY_LOSS) {
+#pragma unroll
+                for (int q = 0; q < 4; q++) {
+                    float s = s4[q];
+                    for (int d = 8; d > 0; d >>= 1) s += __shfl_xor(s, d, 16);
+                    const int m = m0 + 16 * x + 4 * g + q;
+                    if (r == 0 && m < rows) sq[(long)m * (N / 16) + (n0 + 16 * y) / 16] = s;
+                }
+            }
+        }
+}
+
+// Weight gradients of the three layers in one launch: gW = (inputs)^T
+// (errors), contracted over the rows, one 16 x 16 tile per wavefront (about
+// 930 wavefronts; whole 64 x 64 tiles would be 16 blocks a layer, each with
+// the serial walk of all rows), eight chunks of loads ahead.
+struct GradW {
+    const bf16_t *a[3], *b[3];
+    float *g[3];
+    int mt[3], nt[3];   // 16 x 16 tiles
+};
+__global__ void __launch_bounds__(256) k_wgrad(int K, long ldt, GradW G)
+{
+    const int lane = (int)threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    int u = (int)blockIdx.x * 4 + ((int)threadIdx.x >> 6), l = 0;
+    while (l < 3 && u >= G.mt[l] * G.nt[l]) {
+        u -= G.mt[l] * G.nt[l];
+        l++;
+    }
+    if (l == 3) return;
+    const bf16_t *a = l == 0 ? G.a[0] : l == 1 ? G.a[1] : G.a[2], *b = l == 0 ? G.b[0] : l == 1 ? G.b[1] : G.b[2];
+    float *c = l == 0 ? G.g[0] : l == 1 ? G.g[1] : G.g[2];
+    const int nt = l == 0 ? G.nt[0] : l == 1 ? G.nt[1] : G.nt[2];
+    const int m0 = 16 * (u / nt), n0 = 16 * (u % nt);
+    v4f acc[1][1] = {{v4f{0.f, 0.f, 0.f, 0.f}}};
+    product<1, 1, 8>(a, ldt, b, ldt, m0, n0, K, acc);
+#pragma unroll
+    for (int q = 0; q < 4; q++) c[(long)(m0 + 4 * g + q) * (16 * nt) + n0 + r] = acc[0][0][q];
 }
 
 // ------------------------------------------------------------ elementwise
-__global__ void k_to_bf16(const float *x, long ldx, int rows, int cols, int cols_pad, bf16_t *y, long ldy)
+// rows x cols FP32 to BF16 [row][ldy], columns padded with zeros, and (yt)
+// transposed [column][ldt] with zeros in rows .. pad32(rows)
+__global__ void __launch_bounds__(256) k_to_bf16(const float *x, int rows, int cols, bf16_t *y, int ldy, bf16_t *yt,
+                                                 long ldt)
 {
-    long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (long)rows * cols_pad) return;
-    int r = (int)(e / cols_pad), c = (int)(e % cols_pad);
-    y[(long)r * ldy + c] = c < cols ? to_bf16(x[(long)r * ldx + c]) : (bf16_t)0;
-}
-
-// dY = 2 (Y - T) / count on the true output columns, its BF16 copy, and the
-// per-row squared error
-__global__ void k_loss_grad(const float *Y, const float *T, int rows, int out, int out_pad, float scale,
-                            float *dY, bf16_t *dYb, float *sq)
-{
-    long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (long)rows * out_pad) return;
-    int r = (int)(e / out_pad), c = (int)(e % out_pad);
-    float d = 0.f;
-    if (c < out) {
-        float res = Y[(long)r * out_pad + c] - T[(long)r * out + c];
-        d = scale * res;
-        atomicAdd(sq + (r & 1023), res * res);
+    __shared__ bf16_t t[64][66];
+    const int r0 = (int)blockIdx.y * 64, c0 = (int)blockIdx.x * 64, tx = (int)threadIdx.x & 63, ty = (int)threadIdx.x >> 6;
+#pragma unroll 4
+    for (int q = 0; q < 16; q++) {
+        const int r = r0 + ty + 4 * q, c = c0 + tx;
+        const bf16_t v = r < rows && c < cols ? to_bf16(x[(long)r * cols + c]) : (bf16_t)0;
+        if (r < rows && c < ldy) y[(long)r * ldy + c] = v;
+        t[ty + 4 * q][tx] = v;
     }
-    dY[e] = d;
-    dYb[e] = to_bf16(d);
+    if (!yt) return;
+    __syncthreads();
+#pragma unroll 4
+    for (int q = 0; q < 16; q++) {
+        const int c = c0 + ty + 4 * q, r = r0 + tx;
+        if (c < ldy && r < pad32(rows)) yt[(long)c * ldt + r] = t[tx][ty + 4 * q];
+    }
 }
 
-// dZ = dH * (1 - H^2) (tanh derivative) and its BF16 copy
-__global__ void k_tanh_back(const float *dH, const float *Hh, long count, float *dZ, bf16_t *dZb)
+// Bias gradients: column sums of the errors of the three layers in two
+// deterministic passes: partial sums of 256-row chunks in row order (threads
+// along columns, 16 rows of loads ahead of the sum), then the chunks in order.
+struct ColSum {
+    const float *x[3];
+    int ld[3], cb[3];   // width, blocks of 64 columns
+    float *part;        // [layer][chunk][column], layers `stride` apart
+    long stride;
+};
+__global__ void __launch_bounds__(64) k_colsum_partial(ColSum S, int rows)
 {
-    long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= count) return;
-    float h = Hh[e];
-    float d = dH[e] * (1.f - h * h);
-    dZ[e] = d;
-    dZb[e] = to_bf16(d);
-}
-
-// column sums (bias gradients) in two deterministic passes: partial sums of
-// 256-row chunks (threads along columns, coalesced), then the chunks in order
-__global__ void k_colsum_partial(const float *x, int rows, int cols, long ld, float *part)
-{
-    int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cols) return;
-    int r0 = blockIdx.y * 256, r1 = min(rows, r0 + 256);
+    int b = (int)blockIdx.x, l = 0;
+    while (b >= (l == 0 ? S.cb[0] : l == 1 ? S.cb[1] : S.cb[2])) {
+        b -= l == 0 ? S.cb[0] : S.cb[1];
+        l++;
+    }
+    const float *x = l == 0 ? S.x[0] : l == 1 ? S.x[1] : S.x[2];
+    const int ld = l == 0 ? S.ld[0] : l == 1 ? S.ld[1] : S.ld[2];
+    const int c = b * 64 + (int)threadIdx.x;
+    if (c >= ld) return;
+    const int r0 = (int)blockIdx.y * 256, r1 = min(rows, r0 + 256);
     float s = 0.f;
-    for (int r = r0; r < r1; r++) s += x[(long)r * ld + c];
-    part[(long)blockIdx.y * cols + c] = s;
+    for (int r = r0; r < r1; r += 16) {
+        float v[16];
+#pragma unroll
+        for (int q = 0; q < 16; q++) v[q] = x[(long)min(r + q, r1 - 1) * ld + c];
+#pragma unroll
+        for (int q = 0; q < 16; q++)
+            if (r + q < r1) s += v[q];
+    }
+    S.part[l * S.stride + (long)blockIdx.y * ld + c] = s;
 }
-
-__global__ void k_colsum_final(const float *part, int chunks, int cols, float *out)
+DEVI float colsum_final(const float *part, int chunks, int ld, int c)
 {
-    int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cols) return;
     float s = 0.f;
-    for (int q = 0; q < chunks; q++) s += part[(long)q * cols + c];
-    out[c] = s;
+    for (int q = 0; q < chunks; q++) s += part[(long)q * ld + c];
+    return s;
 }
 
-// Adam on FP32 master parameters; refresh the BF16 copy
-__global__ void k_adam(float *p, const float *g, float *m, float *v, long count, float lr, float b1, float b2,
-                       float eps, float c1, float c2, bf16_t *pb)
+// The parameters of the three layers as one list of elements: per layer the
+// padded weight matrix, then the bias.
+struct Params {
+    float *W[3], *b[3], *mW[3], *vW[3], *mb[3], *vb[3], *gW[3], *gb[3];
+    bf16_t *Wb[3], *WbT[3];
+    int kp[3], np[3];      // padded input and output widths
+    int in[3], on[3];      // true widths
+    const float *part;     // bias gradient partials (or null: gb is given)
+    long stride;
+    int chunks;
+};
+// bias gradients from their partials
+__global__ void k_bias_final(Params P)
 {
-    long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= count) return;
-    float gg = g[e];
-    float mm = b1 * m[e] + (1.f - b1) * gg;
-    float vv = b2 * v[e] + (1.f - b2) * gg * gg;
-    m[e] = mm;
-    v[e] = vv;
+    const int l = (int)blockIdx.y, c = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (c < P.np[l]) P.gb[l][c] = colsum_final(P.part + l * P.stride, P.chunks, P.np[l], c);
+}
+// Adam on the FP32 master parameters (all layers, one launch); refreshes both
+// BF16 copies of the weights; bias gradients are summed from their partials
+__global__ void __launch_bounds__(256) k_adam(Params P, float lr, float b1, float b2, float eps, float c1, float c2)
+{
+    const int l = (int)blockIdx.y;
+    const long wc = (long)P.kp[l] * P.np[l], e = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= wc + P.np[l]) return;
+    const bool isw = e < wc;
+    const long q = isw ? e : e - wc;
+    float gg;
+    if (isw) {
+        gg = P.gW[l][q];
+    } else {
+        gg = colsum_final(P.part + l * P.stride, P.chunks, P.np[l], (int)q);
+        P.gb[l][q] = gg;
+    }
+    float *p = isw ? P.W[l] : P.b[l], *m = isw ? P.mW[l] : P.mb[l], *v = isw ? P.vW[l] : P.vb[l];
+    float mm = b1 * m[q] + (1.f - b1) * gg;
+    float vv = b2 * v[q] + (1.f - b2) * gg * gg;
+    m[q] = mm;
+    v[q] = vv;
     float mh = mm / c1, vh = vv / c2;
-    float pn = p[e] - lr * mh / (sqrtf(vh) + eps);
-    p[e] = pn;
-    if (pb) pb[e] = to_bf16(pn);
+    float pn = p[q] - lr * mh / (sqrtf(vh) + eps);
+    p[q] = pn;
+    if (isw) {
+        const bf16_t h = to_bf16(pn);
+        const int r = (int)(q / P.np[l]), c = (int)(q - (long)r * P.np[l]);
+        P.Wb[l][q] = h;
+        P.WbT[l][(long)c * P.kp[l] + r] = h;
+    }
 }
 
-__global__ void k_f32_to_bf16(const float *x, long count, bf16_t *y)
+// true-size parameters (or gradients) to one packed array and back: W1 (in x
+// h1), b1, W2, b2, W3, b3, row-major
+__global__ void k_pack(Params P, int grads, float *flat)
 {
-    long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < count) y[e] = to_bf16(x[e]);
+    const int l = (int)blockIdx.y;
+    long off = 0;
+    for (int k = 0; k < l; k++) off += (long)P.in[k] * P.on[k] + P.on[k];
+    const long wc = (long)P.in[l] * P.on[l], e = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= wc + P.on[l]) return;
+    const float *W = grads ? P.gW[l] : P.W[l], *b = grads ? P.gb[l] : P.b[l];
+    flat[off + e] = e < wc ? W[e / P.on[l] * P.np[l] + e % P.on[l]] : b[e - wc];
+}
+// packed parameters into the padded arrays, Adam state reset
+__global__ void k_unpack(Params P, const float *flat)
+{
+    const int l = (int)blockIdx.y;
+    long off = 0;
+    for (int k = 0; k < l; k++) off += (long)P.in[k] * P.on[k] + P.on[k];
+    const long wc = (long)P.kp[l] * P.np[l], e = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= wc + P.np[l]) return;
+    if (e < wc) {
+        const int r = (int)(e / P.np[l]), c = (int)(e - (long)r * P.np[l]);
+        const float v = r < P.in[l] && c < P.on[l] ? flat[off + (long)r * P.on[l] + c] : 0.f;
+        P.W[l][e] = v;
+        P.mW[l][e] = P.vW[l][e] = 0.f;
+        P.Wb[l][e] = to_bf16(v);
+        P.WbT[l][(long)c * P.kp[l] + r] = to_bf16(v);
+    } else {
+        const int c = (int)(e - wc);
+        P.b[l][c] = c < P.on[l] ? flat[off + (long)P.in[l] * P.on[l] + c] : 0.f;
+        P.mb[l][c] = P.vb[l][c] = 0.f;
+    }
 }
 
-static unsigned nb(long count) { return (unsigned)((count + 255) / 256); }
+// sum of the squared residuals in FP64, one block, fixed order (16 loads
+// ahead of the sums: 62 -> 9 us for 65536 values)
+__global__ void __launch_bounds__(1024) k_loss(const float *sq, long count, double *loss)
+{
+    __shared__ double s[1024];
+    double a = 0.0;
+    for (long e0 = threadIdx.x; e0 < count; e0 += 16 * 1024) {
+        float v[16];
+#pragma unroll
+        for (int q = 0; q < 16; q++) v[q] = e0 + q * 1024 < count ? sq[e0 + q * 1024] : 0.f;
+#pragma unroll
+        for (int q = 0; q < 16; q++) a += (double)v[q];
+    }
+    s[threadIdx.x] = a;
+    __syncthreads();
+    for (int w = 512; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *loss = s[0];
+}
 
 }  // namespace fv3
 
@@ -237,23 +384,19 @@ static unsigned nb(long count) { return (unsigned)((count + 255) / 256); }
 // ====================================================================
 struct fv3_mlp {
     int in, h1, h2, out;        // true sizes
-    int inp, outp;              // padded to multiples of 16
-    int maxrows;
-    long step;
-    // FP32 master parameters (padded layouts), Adam moments, BF16 copies
-    float *W[3], *b[3], *mW[3], *vW[3], *mb[3], *vb[3], *gW[3], *gb[3];
-    fv3::bf16_t *Wb[3];
-    // activations and gradients for up to maxrows rows
-    fv3::bf16_t *Xb, *H1b, *H2b, *dYb, *dZ2b, *dZ1b;
-    float *H1, *H2, *Y, *dY, *dH2, *dZ2, *dH1, *dZ1, *sq, *part;
+    int limit, maxrows;         // most rows of a call; rows the arrays hold
+    long step, ldt;             // Adam steps taken; row stride of the transposed arrays
+    fv3::Params P;              // parameters, Adam moments, gradients, BF16 copies
+    // activations and errors for up to maxrows rows: FP32, BF16, BF16 transposed
+    fv3::bf16_t *Xb, *XbT, *H1b, *H1bT, *H2b, *H2bT, *dYb, *dYbT, *dZ2b, *dZ2bT, *dZ1bT;
+    float *H1, *H2, *dY, *dZ2, *dZ1, *sq, *part, *flat;
+    double *loss;
     int device;
+    mutable std::mutex mu;      // `flat` holds one download at a time
 };
 
 namespace fv3 {
 namespace {
-
-long wrows(const fv3_mlp *n, int l) { return l == 0 ? n->inp : (l == 1 ? n->h1 : n->h2); }
-long wcols(const fv3_mlp *n, int l) { return l == 0 ? n->h1 : (l == 1 ? n->h2 : n->outp); }
 
 template <class T>
 bool dalloc(T **p, long count)
@@ -262,50 +405,72 @@ bool dalloc(T **p, long count)
     return hipMemset(*p, 0, count * sizeof(T)) == hipSuccess;
 }
 
-void colsum(fv3_mlp *n, const float *x, int rows, int cols, float *out, hipStream_t st)
+template <int KIND>
+void layer(int rows, int N, int K, const bf16_t *A, const bf16_t *B, const float *bias, const float *h,
+           const LayerOut &O, float *Y, const float *T, int out, float scale, float *sq, hipStream_t st)
 {
-    int chunks = (rows + 255) / 256;
-    hipLaunchKernelGGL(k_colsum_partial, dim3((unsigned)((cols + 63) / 64), (unsigned)chunks), dim3(64), 0, st, x,
-                       rows, cols, (long)cols, n->part);
-    hipLaunchKernelGGL(k_colsum_final, dim3((unsigned)((cols + 63) / 64)), dim3(64), 0, st, (const float *)n->part,
-                       chunks, cols, out);
+    dim3 grd((unsigned)((N + 63) / 64), (unsigned)((rows + 63) / 64));
+    hipLaunchKernelGGL(k_layer<KIND>, grd, dim3(256), 0, st, rows, N, K, A, (long)K, B, (long)K, bias, h, O, Y, T, out,
+                       scale, sq);
 }
 
-// forward pass on `rows` rows of X (FP32, in columns, row stride in)
-void forward(fv3_mlp *n, const float *X, int rows, hipStream_t st)
+// forward pass on `rows` rows of X (FP32, in columns): with Y the outputs,
+// else the activations the backward pass needs and the output errors
+void forward(fv3_mlp *n, const float *X, int rows, float *Y, const float *T, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_to_bf16, dim3(nb((long)rows * n->inp)), dim3(256), 0, st, X, (long)n->in, rows, n->in,
-                       n->inp, n->Xb, (long)n->inp);
-    gemm(rows, n->h1, n->inp, n->Xb, n->inp, 1, n->Wb[0], n->h1, 1, n->b[0], GE_TANH, n->H1, n->h1, n->H1b, n->h1, st);
-    gemm(rows, n->h2, n->h1, n->H1b, n->h1, 1, n->Wb[1], n->h2, 1, n->b[1], GE_TANH, n->H2, n->h2, n->H2b, n->h2, st);
-    gemm(rows, n->outp, n->h2, n->H2b, n->h2, 1, n->Wb[2], n->outp, 1, n->b[2], GE_NONE, n->Y, n->outp, nullptr, 0,
-         st);
+    const bool train = Y == nullptr;
+    const Params &P = n->P;
+    hipLaunchKernelGGL(k_to_bf16, dim3((unsigned)((P.kp[0] + 63) / 64), (unsigned)((rows + 63) / 64)), dim3(256), 0, st,
+                       X, rows, n->in, n->Xb, P.kp[0], train ? n->XbT : nullptr, n->ldt);
+    layer<LY_TANH>(rows, P.np[0], P.kp[0], n->Xb, P.WbT[0], P.b[0], nullptr,
+                   LayerOut{train ? n->H1 : nullptr, n->H1b, train ? n->H1bT : nullptr, P.np[0], n->ldt}, nullptr, nullptr,
+                   0, 0.f, nullptr, st);
+    layer<LY_TANH>(rows, P.np[1], P.kp[1], n->H1b, P.WbT[1], P.b[1], nullptr,
+                   LayerOut{train ? n->H2 : nullptr, n->H2b, train ? n->H2bT : nullptr, P.np[1], n->ldt}, nullptr, nullptr,
+                   0, 0.f, nullptr, st);
+    if (!train)
+        layer<LY_OUT>(rows, P.np[2], P.kp[2], n->H2b, P.WbT[2], P.b[2], nullptr, LayerOut{}, Y, nullptr, n->out, 0.f,
+                      nullptr, st);
+    else
+        layer<LY_LOSS>(rows, P.np[2], P.kp[2], n->H2b, P.WbT[2], P.b[2], nullptr,
+                       LayerOut{n->dY, n->dYb, n->dYbT, P.np[2], n->ldt}, nullptr, T, n->out,
+                       2.0f / (float)((long)rows * n->out), n->sq, st);
 }
 
-// gradients of the mean squared error over rows x out into gW, gb
-void backward(fv3_mlp *n, const float *T, int rows, hipStream_t st)
+// gradients of the mean squared error over rows x out: gW, and the partials
+// of the bias gradients
+void backward(fv3_mlp *n, int rows, hipStream_t st)
 {
-    float scale = 2.0f / (float)((long)rows * n->out);
-    (void)hipMemsetAsync(n->sq, 0, 1024 * sizeof(float), st);
-    hipLaunchKernelGGL(k_loss_grad, dim3(nb((long)rows * n->outp)), dim3(256), 0, st, n->Y, T, rows, n->out,
-                       n->outp, scale, n->dY, n->dYb, n->sq);
-    // layer 3
-    gemm(n->h2, n->outp, rows, n->H2b, 1, n->h2, n->dYb, n->outp, 1, nullptr, GE_NONE, n->gW[2], n->outp, nullptr, 0,
-         st);
-    colsum(n, n->dY, rows, n->outp, n->gb[2], st);
-    gemm(rows, n->h2, n->outp, n->dYb, n->outp, 1, n->Wb[2], 1, n->outp, nullptr, GE_NONE, n->dH2, n->h2, nullptr,
-         0, st);
-    hipLaunchKernelGGL(k_tanh_back, dim3(nb((long)rows * n->h2)), dim3(256), 0, st, n->dH2, n->H2,
-                       (long)rows * n->h2, n->dZ2, n->dZ2b);
-    // layer 2
-    gemm(n->h1, n->h2, rows, n->H1b, 1, n->h1, n->dZ2b, n->h2, 1, nullptr, GE_NONE, n->gW[1], n->h2, nullptr, 0, st);
-    colsum(n, n->dZ2, rows, n->h2, n->gb[1], st);
-    gemm(rows, n->h1, n->h2, n->dZ2b, n->h2, 1, n->Wb[1], 1, n->h2, nullptr, GE_NONE, n->dH1, n->h1, nullptr, 0, st);
-    hipLaunchKernelGGL(k_tanh_back, dim3(nb((long)rows * n->h1)), dim3(256), 0, st, n->dH1, n->H1,
-                       (long)rows * n->h1, n->dZ1, n->dZ1b);
-    // layer 1
-    gemm(n->inp, n->h1, rows, n->Xb, 1, n->inp, n->dZ1b, n->h1, 1, nullptr, GE_NONE, n->gW[0], n->h1, nullptr, 0, st);
-    colsum(n, n->dZ1, rows, n->h1, n->gb[0], st);
+    Params &P = n->P;
+    layer<LY_BACK>(rows, P.np[1], P.np[2], n->dYb, P.Wb[2], nullptr, n->H2,
+                   LayerOut{n->dZ2, n->dZ2b, n->dZ2bT, P.np[1], n->ldt}, nullptr, nullptr, 0, 0.f, nullptr, st);
+    layer<LY_BACK>(rows, P.np[0], P.np[1], n->dZ2b, P.Wb[1], nullptr, n->H1,
+                   LayerOut{n->dZ1, nullptr, n->dZ1bT, P.np[0], n->ldt}, nullptr, nullptr, 0, 0.f, nullptr, st);
+    GradW G{{n->XbT, n->H1bT, n->H2bT}, {n->dZ1bT, n->dZ2bT, n->dYbT}, {P.gW[0], P.gW[1], P.gW[2]}, {}, {}};
+    ColSum S{{n->dZ1, n->dZ2, n->dY}, {}, {}, n->part, P.stride};
+    int tiles = 0, cbs = 0;
+    for (int l = 0; l < 3; l++) {
+        G.mt[l] = P.kp[l] / 16;
+        G.nt[l] = P.np[l] / 16;
+        tiles += G.mt[l] * G.nt[l];
+        S.ld[l] = P.np[l];
+        S.cb[l] = (P.np[l] + 63) / 64;
+        cbs += S.cb[l];
+    }
+    P.chunks = (rows + 255) / 256;
+    hipLaunchKernelGGL(k_wgrad, dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, st, pad32(rows), n->ldt, G);
+    hipLaunchKernelGGL(k_colsum_partial, dim3((unsigned)cbs, (unsigned)P.chunks), dim3(64), 0, st, S, rows);
+}
+
+// launch over the elements of every layer's weights and bias
+dim3 param_grid(const Params &P, bool padded)
+{
+    long most = 0;
+    for (int l = 0; l < 3; l++) {
+        const long c = padded ? (long)P.kp[l] * P.np[l] + P.np[l] : (long)P.in[l] * P.on[l] + P.on[l];
+        most = c > most ? c : most;
+    }
+    return dim3((unsigned)((most + 255) / 256), 3);
 }
 
 }  // namespace
@@ -331,28 +496,41 @@ fv3_status fv3_mlp_create(int in, int h1, int h2, int out, int maxrows, const fl
         return mfail(FV3_EINVAL, "bad network sizes (hidden widths must be multiples of 16)");
     fv3_mlp *n = new fv3_mlp();
     n->in = in; n->h1 = h1; n->h2 = h2; n->out = out;
-    n->inp = (in + 15) / 16 * 16;
-    n->outp = (out + 15) / 16 * 16;
-    n->maxrows = (maxrows + 15) / 16 * 16;
+    n->limit = (maxrows + 15) / 16 * 16;
+    n->maxrows = (maxrows + 63) / 64 * 64;   // whole product tiles
+    n->ldt = n->maxrows;
     n->step = 0;
     if (hipGetDevice(&n->device) != hipSuccess) {
         delete n;
         return mfail(FV3_EDEVICE, "no current HIP device");
     }
+    Params &P = n->P;
+    const int wi[3] = {in, h1, h2}, wo[3] = {h1, h2, out};
     bool ok = true;
+    int wmax = 0;
+    long flat = 0;
     for (int l = 0; l < 3; l++) {
-        long wc = wrows(n, l) * wcols(n, l), bc = wcols(n, l);
-        ok = ok && dalloc(&n->W[l], wc) && dalloc(&n->mW[l], wc) && dalloc(&n->vW[l], wc) && dalloc(&n->gW[l], wc) &&
-             dalloc(&n->b[l], bc) && dalloc(&n->mb[l], bc) && dalloc(&n->vb[l], bc) && dalloc(&n->gb[l], bc) &&
-             dalloc(&n->Wb[l], wc);
+        P.in[l] = wi[l];
+        P.on[l] = wo[l];
+        P.kp[l] = pad32(wi[l]);
+        P.np[l] = pad32(wo[l]);
+        wmax = std::max(wmax, std::max(P.kp[l], P.np[l]));
+        flat += (long)wi[l] * wo[l] + wo[l];
+        // operand rows are read in whole tiles of up to 64
+        const long kr = (P.kp[l] + 63) / 64 * 64, nr = (P.np[l] + 63) / 64 * 64, wc = (long)P.kp[l] * P.np[l];
+        ok = ok && dalloc(&P.W[l], wc) && dalloc(&P.mW[l], wc) && dalloc(&P.vW[l], wc) && dalloc(&P.gW[l], wc) &&
+             dalloc(&P.b[l], P.np[l]) && dalloc(&P.mb[l], P.np[l]) && dalloc(&P.vb[l], P.np[l]) &&
+             dalloc(&P.gb[l], P.np[l]) && dalloc(&P.Wb[l], kr * P.np[l]) && dalloc(&P.WbT[l], nr * P.kp[l]);
     }
-    long R = n->maxrows;
-    ok = ok && dalloc(&n->Xb, R * n->inp) && dalloc(&n->H1b, R * h1) && dalloc(&n->H2b, R * h2) &&
-         dalloc(&n->dYb, R * n->outp) && dalloc(&n->dZ2b, R * h2) && dalloc(&n->dZ1b, R * h1) &&
-         dalloc(&n->H1, R * h1) && dalloc(&n->H2, R * h2) && dalloc(&n->Y, R * n->outp) &&
-         dalloc(&n->dY, R * n->outp) && dalloc(&n->dH2, R * h2) && dalloc(&n->dZ2, R * h2) &&
-         dalloc(&n->dH1, R * h1) && dalloc(&n->dZ1, R * h1) && dalloc(&n->sq, 1024) &&
-         dalloc(&n->part, (R / 256 + 1) * (long)std::max(std::max(h1, h2), n->outp));
+    const long R = n->maxrows, X = P.kp[0], A = P.np[0], B = P.np[1], O = P.np[2];
+    P.stride = (R / 256 + 1) * (long)wmax;
+    ok = ok && dalloc(&n->Xb, R * X) && dalloc(&n->XbT, R * X) && dalloc(&n->H1b, R * A) && dalloc(&n->H1bT, R * A) &&
+         dalloc(&n->H2b, R * B) && dalloc(&n->H2bT, R * B) && dalloc(&n->dYb, R * O) && dalloc(&n->dYbT, R * O) &&
+         dalloc(&n->dZ2b, R * B) && dalloc(&n->dZ2bT, R * B) && dalloc(&n->dZ1bT, R * A) && dalloc(&n->H1, R * A) &&
+         dalloc(&n->H2, R * B) && dalloc(&n->dY, R * O) && dalloc(&n->dZ2, R * B) && dalloc(&n->dZ1, R * A) &&
+         dalloc(&n->sq, R * (O / 16)) && dalloc(&n->part, 3 * P.stride) && dalloc(&n->flat, flat) &&
+         dalloc(&n->loss, 1);
+    P.part = n->part;
     if (!ok) {
         fv3_mlp_free(n);
         return mfail(FV3_ENOMEM, "device allocation failed");
@@ -370,13 +548,14 @@ fv3_status fv3_mlp_free(fv3_mlp *n)
 {
     if (!n) return FV3_OK;
     (void)hipDeviceSynchronize();
+    const Params &P = n->P;
     for (int l = 0; l < 3; l++) {
-        void *ps[] = {n->W[l], n->b[l], n->mW[l], n->vW[l], n->mb[l], n->vb[l], n->gW[l], n->gb[l], n->Wb[l]};
+        void *ps[] = {P.W[l], P.b[l], P.mW[l], P.vW[l], P.mb[l], P.vb[l], P.gW[l], P.gb[l], P.Wb[l], P.WbT[l]};
         for (void *p : ps)
             if (p) (void)hipFree(p);
     }
-    void *ps[] = {n->Xb, n->H1b, n->H2b, n->dYb, n->dZ2b, n->dZ1b, n->H1, n->H2, n->Y, n->dY,
-                  n->dH2, n->dZ2, n->dH1, n->dZ1, n->sq, n->part};
+    void *ps[] = {n->Xb, n->XbT, n->H1b, n->H1bT, n->H2b, n->H2bT, n->dYb, n->dYbT, n->dZ2b, n->dZ2bT, n->dZ1bT,
+                  n->H1, n->H2, n->dY, n->dZ2, n->dZ1, n->sq, n->part, n->flat, n->loss};
     for (void *p : ps)
         if (p) (void)hipFree(p);
     delete n;
@@ -392,23 +571,11 @@ static long packed_count(const fv3_mlp *n)
 fv3_status fv3_mlp_set_params(fv3_mlp *n, const float *params)
 {
     if (!n || !params) return mfail(FV3_EINVAL, "NULL argument");
-    const float *p = params;
-    int tin[3] = {n->in, n->h1, n->h2}, tout[3] = {n->h1, n->h2, n->out};
-    for (int l = 0; l < 3; l++) {
-        long R = wrows(n, l), Cc = wcols(n, l);
-        std::vector<float> w(R * Cc, 0.f), b(Cc, 0.f);
-        for (int r = 0; r < tin[l]; r++)
-            for (int c = 0; c < tout[l]; c++) w[r * Cc + c] = *p++;
-        for (int c = 0; c < tout[l]; c++) b[c] = *p++;
-        if (hipMemcpy(n->W[l], w.data(), w.size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
-            hipMemcpy(n->b[l], b.data(), b.size() * 4, hipMemcpyHostToDevice) != hipSuccess)
-            return mfail(FV3_EDEVICE, "parameter upload failed");
-        hipLaunchKernelGGL(k_f32_to_bf16, dim3(nb(R * Cc)), dim3(256), 0, 0, (const float *)n->W[l], R * Cc, n->Wb[l]);
-        (void)hipMemset(n->mW[l], 0, R * Cc * 4);
-        (void)hipMemset(n->vW[l], 0, R * Cc * 4);
-        (void)hipMemset(n->mb[l], 0, Cc * 4);
-        (void)hipMemset(n->vb[l], 0, Cc * 4);
-    }
+    std::lock_guard<std::mutex> lock(n->mu);
+    if (hipDeviceSynchronize() != hipSuccess ||
+        hipMemcpy(n->flat, params, (size_t)packed_count(n) * 4, hipMemcpyHostToDevice) != hipSuccess)
+        return mfail(FV3_EDEVICE, "parameter upload failed");
+    hipLaunchKernelGGL(k_unpack, param_grid(n->P, true), dim3(256), 0, 0, n->P, (const float *)n->flat);
     n->step = 0;
     return hipDeviceSynchronize() == hipSuccess ? FV3_OK : mfail(FV3_EDEVICE, "sync failed");
 }
@@ -416,19 +583,11 @@ fv3_status fv3_mlp_set_params(fv3_mlp *n, const float *params)
 fv3_status fv3_mlp_get_params(const fv3_mlp *n, float *params)
 {
     if (!n || !params) return mfail(FV3_EINVAL, "NULL argument");
+    std::lock_guard<std::mutex> lock(n->mu);
     if (hipDeviceSynchronize() != hipSuccess) return mfail(FV3_EDEVICE, "sync failed");
-    float *p = params;
-    int tin[3] = {n->in, n->h1, n->h2}, tout[3] = {n->h1, n->h2, n->out};
-    for (int l = 0; l < 3; l++) {
-        long R = wrows(n, l), Cc = wcols(n, l);
-        std::vector<float> w(R * Cc), b(Cc);
-        if (hipMemcpy(w.data(), n->W[l], w.size() * 4, hipMemcpyDeviceToHost) != hipSuccess ||
-            hipMemcpy(b.data(), n->b[l], b.size() * 4, hipMemcpyDeviceToHost) != hipSuccess)
-            return mfail(FV3_EDEVICE, "parameter download failed");
-        for (int r = 0; r < tin[l]; r++)
-            for (int c = 0; c < tout[l]; c++) *p++ = w[r * Cc + c];
-        for (int c = 0; c < tout[l]; c++) *p++ = b[c];
-    }
+    hipLaunchKernelGGL(k_pack, param_grid(n->P, false), dim3(256), 0, 0, n->P, 0, n->flat);
+    if (hipMemcpy(params, n->flat, (size_t)packed_count(n) * 4, hipMemcpyDeviceToHost) != hipSuccess)
+        return mfail(FV3_EDEVICE, "parameter download failed");
     return FV3_OK;
 }
 
@@ -436,65 +595,48 @@ long fv3_mlp_param_count(const fv3_mlp *n) { return n ? packed_count(n) : 0; }
 
 fv3_status fv3_mlp_forward(fv3_mlp *n, const float *X, int rows, float *Y, void *stream)
 {
-    if (!n || !X || !Y || rows < 1 || rows > n->maxrows) return mfail(FV3_EINVAL, "bad arguments");
+    if (!n || !X || !Y || rows < 1 || rows > n->limit) return mfail(FV3_EINVAL, "bad arguments");
     if (!on_device(n)) return mfail(FV3_EDEVICE, "current HIP device differs from the network's device");
     hipStream_t st = (hipStream_t)stream;
-    forward(n, X, rows, st);
-    // copy the true output columns out
-    if (hipMemcpy2DAsync(Y, (size_t)n->out * 4, n->Y, (size_t)n->outp * 4, (size_t)n->out * 4, rows,
-                         hipMemcpyDeviceToDevice, st) != hipSuccess)
-        return mfail(FV3_EDEVICE, "output copy failed");
-    return FV3_OK;
+    forward(n, X, rows, Y, nullptr, st);
+    return hipGetLastError() == hipSuccess ? FV3_OK : mfail(FV3_EDEVICE, "launch failed");
 }
 
 fv3_status fv3_mlp_gradients(fv3_mlp *n, const float *X, const float *T, int rows, float *grads, void *stream)
 {
-    if (!n || !X || !T || !grads || rows < 1 || rows > n->maxrows) return mfail(FV3_EINVAL, "bad arguments");
+    if (!n || !X || !T || !grads || rows < 1 || rows > n->limit) return mfail(FV3_EINVAL, "bad arguments");
     if (!on_device(n)) return mfail(FV3_EDEVICE, "current HIP device differs from the network's device");
     hipStream_t st = (hipStream_t)stream;
-    forward(n, X, rows, st);
-    backward(n, T, rows, st);
-    if (hipStreamSynchronize(st) != hipSuccess) return mfail(FV3_EDEVICE, "sync failed");
-    float *p = grads;
-    int tin[3] = {n->in, n->h1, n->h2}, tout[3] = {n->h1, n->h2, n->out};
-    for (int l = 0; l < 3; l++) {
-        long R = wrows(n, l), Cc = wcols(n, l);
-        std::vector<float> w(R * Cc), b(Cc);
-        if (hipMemcpy(w.data(), n->gW[l], w.size() * 4, hipMemcpyDeviceToHost) != hipSuccess ||
-            hipMemcpy(b.data(), n->gb[l], b.size() * 4, hipMemcpyDeviceToHost) != hipSuccess)
-            return mfail(FV3_EDEVICE, "gradient download failed");
-        for (int r = 0; r < tin[l]; r++)
-            for (int c = 0; c < tout[l]; c++) *p++ = w[r * Cc + c];
-        for (int c = 0; c < tout[l]; c++) *p++ = b[c];
-    }
+    forward(n, X, rows, nullptr, T, st);
+    backward(n, rows, st);
+    int wmax = std::max(n->P.np[0], std::max(n->P.np[1], n->P.np[2]));
+    hipLaunchKernelGGL(k_bias_final, dim3((unsigned)((wmax + 63) / 64), 3), dim3(64), 0, st, n->P);
+    std::lock_guard<std::mutex> lock(n->mu);
+    hipLaunchKernelGGL(k_pack, param_grid(n->P, false), dim3(256), 0, st, n->P, 1, n->flat);
+    if (hipMemcpyAsync(grads, n->flat, (size_t)packed_count(n) * 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess)
+        return mfail(FV3_EDEVICE, "gradient download failed");
     return FV3_OK;
 }
 
 fv3_status fv3_mlp_train_step(fv3_mlp *n, const float *X, const float *T, int rows, float lr, double *loss,
                               void *stream)
 {
-    if (!n || !X || !T || rows < 1 || rows > n->maxrows) return mfail(FV3_EINVAL, "bad arguments");
+    if (!n || !X || !T || rows < 1 || rows > n->limit) return mfail(FV3_EINVAL, "bad arguments");
     if (!on_device(n)) return mfail(FV3_EDEVICE, "current HIP device differs from the network's device");
     hipStream_t st = (hipStream_t)stream;
-    forward(n, X, rows, st);
-    backward(n, T, rows, st);
+    forward(n, X, rows, nullptr, T, st);
+    backward(n, rows, st);
     n->step++;
     const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     float c1 = 1.f - powf(b1, (float)n->step), c2 = 1.f - powf(b2, (float)n->step);
-    for (int l = 0; l < 3; l++) {
-        long wc = wrows(n, l) * wcols(n, l), bc = wcols(n, l);
-        hipLaunchKernelGGL(k_adam, dim3(nb(wc)), dim3(256), 0, st, n->W[l], (const float *)n->gW[l], n->mW[l],
-                           n->vW[l], wc, lr, b1, b2, eps, c1, c2, n->Wb[l]);
-        hipLaunchKernelGGL(k_adam, dim3(nb(bc)), dim3(256), 0, st, n->b[l], (const float *)n->gb[l], n->mb[l],
-                           n->vb[l], bc, lr, b1, b2, eps, c1, c2, (bf16_t *)nullptr);
-    }
+    hipLaunchKernelGGL(k_adam, param_grid(n->P, true), dim3(256), 0, st, n->P, lr, b1, b2, eps, c1, c2);
     if (loss) {
-        std::vector<float> sq(1024);
-        if (hipMemcpyAsync(sq.data(), n->sq, 1024 * 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
+        hipLaunchKernelGGL(k_loss, dim3(1), dim3(1024), 0, st, (const float *)n->sq, (long)rows * (n->P.np[2] / 16), n->loss);
+        double s = 0.0;
+        if (hipMemcpyAsync(&s, n->loss, sizeof(s), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess)
             return mfail(FV3_EDEVICE, "loss read failed");
-        double s = 0.0;
-        for (float x : sq) s += x;
         *loss = s / ((double)rows * n->out);
     }
     return hipGetLastError() == hipSuccess ? FV3_OK : mfail(FV3_EDEVICE, "launch failed");
