@@ -2158,51 +2158,120 @@ __global__ void k_absmax(int ilo, int ihi, int jlo, int jhi, Geo G, const B *cx,
 
 // Neumaier-compensated sums: each thread sums its column over levels in a
 // fixed order, then the block combines pairs (s, c) with Neumaier additions,
-// one partial per block; the host adds the partials in order.
+// one partial per block and field; one thread per field adds the partials in
+// block order.
 DEVI void neu_add(double &s, double &c, double x)
 {
-    double t = s + x;
-    if (fabs(s) >= fabs(x)) c += (s - t) + x;
-    else c += (x - t) + s;
+    const double t = s + x;
+    const bool big = fabs(s) >= fabs(x);
+    c += ((big ? s : x) - t) + (big ? x : s);
     s = t;
 }
 
+// Up to MNF sums share one pass (delp and the cell mass are read and formed
+// once for all): field f is delp alone (null pointer) or p[f] times it.  The
+// values of four levels are loaded ahead of their additions.  Bound by the
+// reads: C192 x 79 mixed, six sums: six passes of 75 us -> one of 103.
+constexpr int MNF = 6;
 template <class B>
-__global__ void k_mass_partial(int ilo, int ihi, int jlo, int jhi, Geo G, MetD M, const B *delp, const B *pt, const B *q,
-                               int which, double *part)
+struct MassFields {
+    const B *p[MNF];
+    int nf;
+};
+template <class B>
+__global__ void __launch_bounds__(256) k_mass_partial(int ilo, int ihi, int jlo, int jhi, Geo G, MetD M,
+                                                      const B *delp, MassFields<B> F, double *part)
 {
-    __shared__ double ss[256], sc[256];
+    // a product fused into a compensated addition would leave its error term wrong
+#pragma clang fp contract(off)
+    __shared__ double ss[MNF][256], sc[MNF][256];
     int tid = threadIdx.y * blockDim.x + threadIdx.x;
     int i = ilo + (int)(blockIdx.x * blockDim.x + threadIdx.x);
     int j = jlo + (int)(blockIdx.y * blockDim.y + threadIdx.y);
     int t = blockIdx.z;
-    double s = 0.0, c = 0.0;
+    double s[MNF], c[MNF];
+#pragma unroll
+    for (int f = 0; f < MNF; f++) s[f] = c[f] = 0.0;
     if (i <= ihi && j <= jhi) {
-        double ar = AT(MP(M, M_AREA), i, j);
-        for (int k = 0; k < G.nz; k++) {
-            long o = pidx(G, G.nz, t, k);
-            double m = (double)AT(delp + o, i, j) * ar;
-            double x = which == 0 ? m : (which == 1 ? (double)AT(pt + o, i, j) * m : (double)AT(q + o, i, j) * m);
-            neu_add(s, c, x);
+        const double ar = AT(MP(M, M_AREA), i, j);
+        constexpr int U = 4;
+        for (int k0 = 0; k0 < G.nz; k0 += U) {
+            B d[U], v[MNF][U];
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const long o = pidx(G, G.nz, t, min(k0 + u, G.nz - 1));
+                d[u] = AT(delp + o, i, j);
+#pragma unroll
+                for (int f = 0; f < MNF; f++)
+                    if (f < F.nf && F.p[f]) v[f][u] = AT(F.p[f] + o, i, j);
+            }
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                if (k0 + u >= G.nz) break;
+                const double m = (double)d[u] * ar;
+#pragma unroll
+                for (int f = 0; f < MNF; f++)
+                    if (f < F.nf) neu_add(s[f], c[f], F.p[f] ? (double)v[f][u] * m : m);
+            }
         }
     }
-    ss[tid] = s;
-    sc[tid] = c;
+#pragma unroll
+    for (int f = 0; f < MNF; f++) {
+        ss[f][tid] = s[f];
+        sc[f][tid] = c[f];
+    }
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if (tid < w) {
-            double a = ss[tid], ac = sc[tid] + sc[tid + w];
-            neu_add(a, ac, ss[tid + w]);
-            ss[tid] = a;
-            sc[tid] = ac;
+            for (int f = 0; f < F.nf; f++) {
+                double a = ss[f][tid], ac = sc[f][tid] + sc[f][tid + w];
+                neu_add(a, ac, ss[f][tid + w]);
+                ss[f][tid] = a;
+                sc[f][tid] = ac;
+            }
         }
         __syncthreads();
     }
-    if (tid == 0) {
-        long b = ((long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-        part[2 * b] = ss[0];
-        part[2 * b + 1] = sc[0];
+    if (tid < F.nf) {
+        const long nb = (long)gridDim.x * gridDim.y * gridDim.z;
+        const long b = ((long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+        part[2 * (nb * tid + b)] = ss[tid][0];
+        part[2 * (nb * tid + b) + 1] = sc[tid][0];
     }
+}
+
+// The block partials of one field per block, added in block order by one
+// thread; the others stage the next partials in LDS.
+__global__ void __launch_bounds__(256) k_mass_final(const double *part, long np, double *out)
+{
+    __shared__ double st[2][512];
+    const double *p = part + 2 * np * blockIdx.x;
+    double s = 0.0, c = 0.0;
+    auto stage = [&](long b0, double *d) {
+        for (int q = 0; q < 2; q++) {
+            const long e = 2 * b0 + (int)threadIdx.x + 256 * q;
+            if (e < 2 * np) d[threadIdx.x + 256 * q] = p[e];
+        }
+    };
+    stage(0, st[0]);
+    __syncthreads();
+    for (long b0 = 0; b0 < np; b0 += 256) {
+        const int cur = (int)(b0 / 256) & 1;
+        if (b0 + 256 < np && threadIdx.x >= 64) {
+            // the wavefront of the adding thread leaves the staging to the others
+            for (int e = (int)threadIdx.x - 64; e < 512; e += 192)
+                if (2 * (b0 + 256) + e < 2 * np) st[1 - cur][e] = p[2 * (b0 + 256) + e];
+        }
+        if (threadIdx.x == 0) {
+            const int m = (int)(np - b0 < 256 ? np - b0 : 256);
+            for (int b = 0; b < m; b++) {
+                c += st[cur][2 * b + 1];
+                neu_add(s, c, st[cur][2 * b]);
+            }
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[blockIdx.x] = s + c;
 }
 
 // ====================================================================
@@ -2249,7 +2318,8 @@ static size_t carve(const fv3_grid *g, char *base, Work<B> *w)
     return off + 256;
 }
 
-long reduction_elems(const fv3_grid *g) { return 2 * part_count(g); }
+// block partials of MNF fields, and their sums
+long reduction_elems(const fv3_grid *g) { return 2 * part_count(g) * MNF + MNF; }
 
 void timing_start(const char *filter)
 {
@@ -2719,32 +2789,30 @@ fv3_status run_tracer(void *const *q, int nq, fv3_state *s, const fv3_grid *g, i
     return tracer_t<double>(q, nq, s, g, nsplt, st);
 }
 
+// the sums of fields w0 .. w0 + nf - 1 (0: mass, 1: pt, 2 + m: q[m]) into out
+template <class B>
+static void mass_group(const fv3_grid *g, const void *delp, const void *pt, void *const *q, int w0, int nf, double *part,
+                       double *out, hipStream_t st)
+{
+    MassFields<B> F{};
+    F.nf = nf;
+    for (int f = 0; f < nf; f++) F.p[f] = (const B *)(w0 + f == 0 ? nullptr : w0 + f == 1 ? pt : q[w0 + f - 2]);
+    launch2d_native("k_mass_partial", k_mass_partial<B>, 0, g->n - 1, 0, g->n - 1, g->T, st, g->geo, metrics_d(g),
+                    (const B *)delp, F, part);
+    hipLaunchKernelGGL(k_mass_final, dim3((unsigned)nf), dim3(256), 0, st, (const double *)part, part_count(g), out);
+}
+
 template <class B>
 static fv3_status mass_sums_t(const fv3_grid *g, const void *delp, const void *pt, void *const *q,
                               int nq, double *out, hipStream_t st)
 {
-    MetD M = metrics_d(g);
-    const Geo &G = g->geo;
-    int n = g->n;
-    long np = part_count(g);
-    double *part = g->red;
-    std::vector<double> h(2 * np);
-    for (int which = 0; which < 2 + nq; which++) {
-        const B *qq = which >= 2 ? (const B *)q[which - 2] : nullptr;
-        launch2d_native("k_mass_partial", k_mass_partial<B>, 0, n - 1, 0, n - 1, g->T, st, G, M, (const B *)delp, (const B *)pt, qq,
-                 which < 2 ? which : 2, part);
-        if (hipMemcpyAsync(h.data(), part, 2 * np * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess)
+    double *dout = g->red + 2 * part_count(g) * MNF;
+    for (int w0 = 0; w0 < 2 + nq; w0 += MNF) {
+        const int nf = 2 + nq - w0 < MNF ? 2 + nq - w0 : MNF;
+        mass_group<B>(g, delp, pt, q, w0, nf, g->red, dout, st);
+        if (hipMemcpyAsync(out + w0, dout, nf * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess)
             return FV3_EDEVICE;
         if (hipStreamSynchronize(st) != hipSuccess) return FV3_EDEVICE;
-        double s = 0.0, c = 0.0;
-        for (long b = 0; b < np; b++) {
-            c += h[2 * b + 1];
-            double x = h[2 * b], t = s + x;
-            if (std::fabs(s) >= std::fabs(x)) c += (s - t) + x;
-            else c += (x - t) + s;
-            s = t;
-        }
-        out[which] = s + c;
     }
     return FV3_OK;
 }
@@ -2820,38 +2888,17 @@ fv3_status noalloc_setup(int device)
 
 long noalloc_mass_doubles(const fv3_grid *g) { return 2 * part_count(g); }
 
-// The block partials added in block order with the same Neumaier steps as
-// the host-side combine of run_mass_sums, so both give the same bits.
-__global__ void k_mass_final(const double *part, long np, double *out)
-{
-    if (threadIdx.x != 0) return;
-    double s = 0.0, c = 0.0;
-    for (long b = 0; b < np; b++) {
-        c += part[2 * b + 1];
-        double x = part[2 * b], t = s + x;
-        if (fabs(s) >= fabs(x)) c += (s - t) + x;
-        else c += (x - t) + s;
-        s = t;
-    }
-    *out = s + c;
-}
-
 template <class B>
 static fv3_status mass_sums_noalloc_t(const fv3_grid *g, const void *delp, const void *pt, void *const *q,
                                       int nq, double *dev_out, double *part, hipStream_t st)
 {
-    MetD M = metrics_d(g);
-    const Geo &G = g->geo;
-    int n = g->n;
-    long np = part_count(g);
-    // every block of k_mass_partial writes its own two slots (zero outside
-    // the interior), so nothing in the scratch has to be cleared first
-    for (int which = 0; which < 2 + nq; which++) {
-        const B *qq = which >= 2 ? (const B *)q[which - 2] : nullptr;
-        launch2d_native("k_mass_partial", k_mass_partial<B>, 0, n - 1, 0, n - 1, g->T, st, G, M, (const B *)delp,
-                        (const B *)pt, qq, which < 2 ? which : 2, part);
-        hipLaunchKernelGGL(k_mass_final, dim3(1), dim3(64), 0, st, (const double *)part, np, dev_out + which);
-    }
+    // as many fields a pass as the scratch holds; every block of
+    // k_mass_partial writes its own slots (zero outside the interior), so
+    // nothing in the scratch has to be cleared first
+    const long cap = (long)(FV3_NOALLOC_SCRATCH_BYTES / sizeof(double)) / noalloc_mass_doubles(g);
+    const int most = cap < MNF ? (int)cap : MNF;
+    for (int w0 = 0; w0 < 2 + nq; w0 += most)
+        mass_group<B>(g, delp, pt, q, w0, 2 + nq - w0 < most ? 2 + nq - w0 : most, part, dev_out + w0, st);
     return hipGetLastError() == hipSuccess ? FV3_OK : FV3_EDEVICE;
 }
 
