@@ -33,6 +33,7 @@
 
 #include "flog.hpp"
 #include "launch.hpp"
+#include "march.hpp"
 #include "transport.hpp"
 
 #pragma clang fp contract(off)
@@ -41,29 +42,6 @@ namespace fv3 {
 
 enum { MARCH_MASS = 0, MARCH_WIND = 1, MARCH_HEIGHT = 2, MARCH_TRACER = 3 };
 
-// value of the lane to the west (l - 1) or east (l + 1); lanes without one get 0
-template <int CTRL>
-DEVI float lane_shift(float x)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-DEVI double lane_shift(double x)
-{
-    typedef int i2 __attribute__((ext_vector_type(2)));
-    const i2 v = __builtin_bit_cast(i2, x);
-    i2 r;
-    r.x = __builtin_amdgcn_update_dpp(0, v.x, CTRL, 0xf, 0xf, true);
-    r.y = __builtin_amdgcn_update_dpp(0, v.y, CTRL, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, r);
-}
-template <class T>
-DEVI T west(T x) { return lane_shift<0x138>(x); }   // wave shift right by one
-template <class T>
-DEVI T east(T x) { return lane_shift<0x130>(x); }   // wave shift left by one
-
-DEVI float ffma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-DEVI double ffma(double a, double b, double c) { return __builtin_fma(a, b, c); }
 // quotients with a shared reciprocal: FP32 by the hardware reciprocal (about
 // one ulp), FP64 with Newton steps and a residual correction per quotient
 DEVI float inv(float d) { return __builtin_amdgcn_rcpf(d); }
@@ -186,10 +164,6 @@ struct YSweep {
         return f;
     }
 };
-
-// element of a plane (block-uniform pointer to its halo corner) at byte offset o
-template <class T>
-DEVI T &el(T *plane, unsigned o) { return *(T *)((char *)plane + o); }
 
 template <class T, int KIND, int NF, int ORD>
 DEVI void k_march(Bk bk, Geo G, MarchArgs<T> A)
@@ -478,39 +452,18 @@ constexpr int march_occ()
     return KIND == MARCH_TRACER ? (NF == 1 ? 5 : NF == 2 ? 4 : 3) : KIND == MARCH_MASS ? 4 : 6;
 }
 
-// Strips of at most 58 columns, equally wide.  A segment marches 6 rows more
-// than it owns, so few long segments do the least work and many short ones
-// spread over more of the 1024 SIMDs: the number of segments with the least
-// (wavefronts on the fullest SIMD) x (rows marched), where a round of fewer
-// than two wavefronts on a SIMD takes as long as one of two (they wait on
-// each other's latency instead of sharing it).  FP64 wind update at C192 x 79
-// (three wavefronts fit): 365 us in 3 segments, 444 in 2 (a round of three
-// wavefronts and one of a single one).
 template <class T>
-static unsigned march_shape(const fv3_grid *g, MarchArgs<T> &a, int occ)
+static unsigned transport_shape(const fv3_grid *g, MarchArgs<T> &a, int occ)
 {
-    a.strips = (g->n + 57) / 58;
-    a.width = (g->n + a.strips - 1) / a.strips;
     const long planes = (long)g->T * g->nz;
-    long best = -1;
-    for (int segs = 1; segs <= g->n; segs++) {
-        const int rows = (g->n + segs - 1) / segs;
-        const long waves = (planes * a.strips * segs + 1023) / 1024, last = waves % occ;
-        const long cost = (10 * (waves - last) + (last == 0 ? 0 : last > 2 ? 10 * last : 22)) * (rows + 6);
-        if (best < 0 || cost < best) {
-            best = cost;
-            a.rows = rows;
-        }
-        if (waves > 4 * occ) break;
-    }
-    a.segs = (g->n + a.rows - 1) / a.rows;
+    march_shape(g->n, planes, 6, occ, a.strips, a.width, a.segs, a.rows);
     return (unsigned)((planes * a.strips * a.segs + 3) / 4);
 }
 
 template <int KIND, int NF, class T>
 static void march(const char *name, const fv3_grid *g, int ord, MarchArgs<T> a, hipStream_t st)
 {
-    const dim3 grd(march_shape(g, a, march_occ<KIND, NF, T>())), blk(256);
+    const dim3 grd(transport_shape(g, a, march_occ<KIND, NF, T>())), blk(256);
     if (ord == 5) launch_fn<k_march<T, KIND, NF, 5>>(name, grd, blk, st, g->geo, a);
     else if (ord == 6) launch_fn<k_march<T, KIND, NF, 6>>(name, grd, blk, st, g->geo, a);
     else launch_fn<k_march<T, KIND, NF, 8>>(name, grd, blk, st, g->geo, a);
@@ -537,7 +490,7 @@ static void march_tracer_n(const fv3_grid *g, const MarchArgs<T> &a, hipStream_t
 {
     const int ord = g->p.hord_tr ? g->p.hord_tr : g->p.hord;
     MarchArgs<T> b = a;
-    const dim3 grd(march_shape(g, b, march_occ<MARCH_TRACER, NF, T>())), blk(256);
+    const dim3 grd(transport_shape(g, b, march_occ<MARCH_TRACER, NF, T>())), blk(256);
     if (ord == 7) launch_fn<k_march<T, MARCH_TRACER, NF, 7>>("k_march_tracer", grd, blk, st, g->geo, b);
     else march<MARCH_TRACER, NF>("k_march_tracer", g, ord, a, st);
 }
