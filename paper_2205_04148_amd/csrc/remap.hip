@@ -13,17 +13,31 @@
 // mean interfaces of the two cells that share the face; delp becomes the
 // reference thickness.
 //
-// GPU mapping: one thread per (column, field), 64 consecutive columns per
-// wavefront so that every level load is one coalesced row segment.  A thread
-// walks its column once, top to bottom, over the merged sequence of source
-// and target interfaces, keeping a five-layer window of means and
-// thicknesses in registers and the interface value below the current layer
-// (which becomes the one above the next).  The walk finishes target layers
-// before it has read every source layer they could overwrite, so results go
-// to workspace slots and are copied back.  All arithmetic is FP64.
+// GPU mapping: a block takes RCOL = 16 columns, its 256 threads 16 chunks of
+// target layers each.  The block sums the columns' interface pressures into
+// LDS (in layer order) and stages the source columns of up to RNF fields
+// there; then every thread finds the source layer that its first target layer
+// starts in by bisection, rebuilds the interpolation state from the two layers
+// above and walks on: per source layer it finishes the target layers that end
+// in it, so that the threads of a wavefront advance together.  A window of
+// means and thicknesses and the interface value below the current layer (which
+// becomes the one above the next) stay in registers.  As every read of the
+// walk is from LDS, results go straight into the fields.  All arithmetic is
+// FP64.
+//
+// What bounds it is the instructions of the walk: some 240 a source layer and
+// 50 more a field, with about ten divisions in a serial chain, and two or
+// three layers per chunk to rebuild the state.  Measured, cells (seven fields)
+// / both winds / whole remap: C48 x 79 mixed 496 / 534 / 1030 us as one thread
+// per column with results in a workspace and copied back, 87 / 52 / 148 now;
+// C192 x 79, eight fields, 3.78 -> 1.98 ms (FP64 4.14 -> 2.00).  On the way:
+// chunks without the staging, 8 chunks of 32 columns, 120 us for the cells
+// (their loads wait for the stores before them); staged, 8 chunks of 32
+// columns, 108 us with four fields a thread, 124 with three, 134 with two.
 #include <cmath>
 #include <string>
 
+#include "flog.hpp"
 #include "fv3_internal.hpp"
 
 namespace fv3 {
@@ -32,7 +46,8 @@ namespace {
 constexpr int RMAX = FV3_REMAP_MAX_LEVELS;
 constexpr int RSLOTS = 8;   // fields per launch, at most
 constexpr int RNF = 4;      // cell fields per thread (one walk of the column serves them all)
-enum { RM_CELL = 0, RM_U = 1, RM_V = 2 };
+constexpr int RCOL = 16, RCHUNK = 16;   // columns and chunks of layers per block
+enum { RM_CELL = 0, RM_WIND = 1 };
 
 // reference coordinate, passed by value in the kernel arguments
 struct RCoef {
@@ -41,22 +56,24 @@ struct RCoef {
 
 struct RBatch {
     const void *src[RSLOTS];
-    void *dst[RSLOTS];
+    void *dst[RSLOTS];   // the field itself, or a workspace slot
     int fp64[RSLOTS];    // 1: the field is FP64, else bulk precision
     int ratio[RSLOTS];   // 1: remap field / delp, store its integral (delz)
     int nf;
 };
 
-__device__ __forceinline__ double ld(const void *p, long e, bool fp64, bool bulk64)
+// element of a field of bulk type B, or of an FP64 one
+template <class B>
+__device__ __forceinline__ void st(void *p, long e, bool fp64, double v)
 {
-    if (fp64 || bulk64) return ((const double *)p)[e];
-    return (double)((const float *)p)[e];
-}
-
-__device__ __forceinline__ void st(void *p, long e, bool fp64, bool bulk64, double v)
-{
-    if (fp64 || bulk64) ((double *)p)[e] = v;
+    if (fp64 || sizeof(B) == 8) ((double *)p)[e] = v;
     else ((float *)p)[e] = (float)v;
+}
+template <class B>
+__device__ __forceinline__ void copy(void *to, const void *from, long e, bool fp64)
+{
+    if (fp64 || sizeof(B) == 8) ((double *)to)[e] = ((const double *)from)[e];
+    else ((float *)to)[e] = ((const float *)from)[e];
 }
 
 // monotonised slope from the raw slope and the two one-sided differences
@@ -66,169 +83,243 @@ __device__ __forceinline__ double mono(double raw, double lo, double hi)
     return copysign(fmin(fabs(raw), 2.0 * fmin(fabs(lo), fabs(hi))), raw);
 }
 
-// Remap up to NF fields of one column (cell or face, by MODE) in one walk.
-// The layer geometry (reciprocals of the thickness sums of the interface
-// interpolation, the layer's own reciprocal thickness) is computed once per
-// source layer for all fields; the limited slope of layer s + 1, needed by the
-// interface below layer s, is kept for the interface below layer s + 1.
-template <int MODE, int NF>
-__global__ __launch_bounds__(256) void k_remap(Geo G, int bulk64, double ptop, RCoef C, RBatch F,
-                                               const void *delp, int *flags)
+// interface pressures of the block's columns (thread (c, ch): layers of chunk
+// ch of column c), summed in layer order: pe[k * RCOL + c], k = 0 .. nz
+template <class H>
+__device__ __forceinline__ void interfaces(double *pe, int nz, double ptop, int c, int ch, bool in, H thick)
 {
-    const int n = G.n, nz = G.nz;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x, j = blockIdx.y * blockDim.y + threadIdx.y;
-    const int ni = MODE == RM_V ? n + 1 : n, nj = MODE == RM_U ? n + 1 : n;
-    if (i >= ni || j >= nj) return;
-    const int groups = (F.nf + NF - 1) / NF;
-    const int t = (int)blockIdx.z / groups, f0 = ((int)blockIdx.z % groups) * NF;
-    const int nfg = min(NF, F.nf - f0);
-    const bool b64 = bulk64 != 0;
+    const int cs = (nz + RCHUNK - 1) / RCHUNK, k1 = min(nz, (ch + 1) * cs);
+    constexpr int CMAX = (RMAX + RCHUNK - 1) / RCHUNK;
+    double h[CMAX];
+#pragma unroll
+    for (int q = 0; q < CMAX; q++) h[q] = in && ch * cs + q < k1 ? thick(ch * cs + q) : 1.0;   // all loads in flight
+#pragma unroll
+    for (int q = 0; q < CMAX; q++)
+        if (ch * cs + q < k1) pe[(ch * cs + q + 1) * RCOL + c] = h[q];
+    __syncthreads();
+    if (ch == 0) {
+        double p = ptop;
+        pe[c] = p;
+        for (int k = 1; k <= nz; k += 8) {
+            double h[8];
+#pragma unroll
+            for (int q = 0; q < 8; q++) h[q] = pe[min(k + q, nz) * RCOL + c];
+#pragma unroll
+            for (int q = 0; q < 8; q++) {
+                p += h[q];
+                if (k + q <= nz) pe[(k + q) * RCOL + c] = p;
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// layers m0 .. m1 - 1 of a column to LDS (divided by delp, if given)
+template <class T, class B>
+__device__ __forceinline__ void stage(T *to, const void *from, const B *delp, long c0, long lev, int m0, int m1, int c)
+{
+    constexpr int CMAX = (RMAX + RCHUNK - 1) / RCHUNK;
+    T v[CMAX];
+    B h[CMAX];
+#pragma unroll
+    for (int q = 0; q < CMAX; q++) {
+        const long e = c0 + (long)(m0 + q) * lev;
+        v[q] = m0 + q < m1 ? ((const T *)from)[e] : (T)0;
+        h[q] = delp && m0 + q < m1 ? delp[e] : (B)1;
+    }
+#pragma unroll
+    for (int q = 0; q < CMAX; q++)
+        if (m0 + q < m1) to[(m0 + q) * RCOL + c] = delp ? (T)(v[q] * fdiv(1.0, (double)h[q])) : v[q];
+}
+
+// Remap up to NF fields of a chunk of target layers of one column, cells
+// (fields f0 .. of the batch) or faces (field 0: west-east faces of u, field
+// 1: v).  The layer geometry (reciprocals of the thickness sums of the
+// interface interpolation) is computed once per source layer for all fields;
+// the limited slope of layer s + 1, needed by the interface below layer s, is
+// kept for the interface below layer s + 1.
+template <class B, int MODE, int NF>
+__global__ __launch_bounds__(256) void k_remap(Geo G, double ptop, RCoef C, RBatch F, const B *delp, int *flags)
+{
+    extern __shared__ double lds[];
+    const int n = G.n, nz = G.nz, c = (int)threadIdx.x % RCOL, ch = (int)threadIdx.x / RCOL;
+    // interface pressures, coefficients, source fields
+    double *pe = lds, *ab = pe + (nz + 1) * RCOL, *fld = ab + 2 * (nz + 1);
+    if ((int)threadIdx.x <= nz) {
+        // the coefficients by lane from LDS: the kernel arguments lie in host
+        // memory, and the walk would wait for one at every target layer
+        ab[threadIdx.x] = C.ak[threadIdx.x];
+        ab[nz + 1 + threadIdx.x] = C.bk[threadIdx.x];
+    }
+    const int groups = MODE == RM_WIND ? 2 : (F.nf + NF - 1) / NF;
+    const int t = (int)blockIdx.y / groups, f0 = (int)blockIdx.y % groups * NF;
+    const int nfg = MODE == RM_WIND ? 1 : min(NF, F.nf - f0);
+    const bool vface = MODE == RM_WIND && f0 == 1;
+    const int ni = vface ? n + 1 : n, nj = MODE == RM_WIND && !vface ? n + 1 : n;
+    const int col = (int)blockIdx.x * RCOL + c, j = col / ni, i = col - j * ni;
+    const bool in = j < nj;
     const long lev = G.lev;
     const long c0 = G.off0 + (long)t * nz * lev + (long)j * G.pitch + i;
-    const long c1 = MODE == RM_U ? c0 - G.pitch : MODE == RM_V ? c0 - 1 : c0;   // other cell of a face
-
+    const long c1 = vface ? c0 - 1 : c0 - G.pitch;   // other cell of a face
     auto thick = [&](int k) -> double {
-        long o = (long)k * lev;
-        if (MODE == RM_CELL) return ld(delp, c0 + o, false, b64);
-        return 0.5 * (ld(delp, c0 + o, false, b64) + ld(delp, c1 + o, false, b64));
+        const long o = (long)k * lev;
+        if (MODE == RM_CELL) return (double)delp[c0 + o];
+        return 0.5 * ((double)delp[c0 + o] + (double)delp[c1 + o]);
     };
-    // surface pressure, summed in the same order as the walk's interfaces
-    double ps = ptop;
-    for (int k = 0; k < nz; k++) ps += thick(k);
-
-    // window over layers s-1 .. s+2 (positions 1..4): thicknesses d1..d4,
-    // means a2..a4 per field (layer s-1 enters only through its slope and
-    // thickness); b3, b4 = bottom interfaces of layers s+1, s+2 as summed
-    double d1 = 1, d2 = 1, d3 = 1, d4 = 1, pa = ptop, b2 = ptop, b3 = ptop, b4 = ptop;
-    double a2[NF], a3[NF], a4[NF];
-    auto next = [&](int k, double *a, double &d, double &bot) {
-        if (k >= nz) return;
-        double h = thick(k), bb = pa + h;
-        d = bb - pa;
-        pa = bb;
-        bot = bb;
-        double rh = 1.0 / h;
-#pragma unroll
-        for (int q = 0; q < NF; q++) {
-            if (q < nfg) {
-                double v = ld(F.src[f0 + q], c0 + (long)k * lev, F.fp64[f0 + q] != 0, b64);
-                a[q] = F.ratio[f0 + q] ? v * rh : v;
-            }
-        }
-    };
-#pragma unroll
-    for (int q = 0; q < NF; q++) a2[q] = a3[q] = a4[q] = 0.0;
-    next(0, a2, d2, b2);
-    next(1, a3, d3, b3);
-    next(2, a4, d4, b4);
-
-    // limited slope of the layer at position 3 (layers s, s+1, s+2 at
-    // positions 2, 3, 4) for every field
-    double sl3[NF];
-    auto slope3 = [&](bool have) {
-        double r = 1.0 / (d2 + d3 + d4), kh = d3 * r * (2.0 * d2 + d3) / (d4 + d3),
-               kl = d3 * r * (d3 + 2.0 * d4) / (d2 + d3);
-#pragma unroll
-        for (int q = 0; q < NF; q++) {
-            double lo = a3[q] - a2[q], hi = a4[q] - a3[q];
-            sl3[q] = have ? mono(kh * hi + kl * lo, lo, hi) : 0.0;
-        }
-    };
-    slope3(nz >= 3);
-    // interface values below layer s (K = s + 1) before limiting; sl2 = the
-    // limited slope of layer s
-    double eR[NF], l[NF], r[NF], c6[NF], acc[NF];
-    auto below = [&](int s, const double *sl2) {
-        const int K = s + 1;
-        if (K >= 2 && K <= nz - 2) {
-            double s23 = d2 + d3, rs = 1.0 / s23, rsum = 1.0 / (d1 + d2 + d3 + d4);
-            double cj = d2 * rs;
-            double w = 2.0 * d3 * d2 * rs * ((d1 + d2) / (2.0 * d2 + d3) - (d4 + d3) / (2.0 * d3 + d2));
-            double g1 = d3 * (d3 + d4) / (d2 + 2.0 * d3), g2 = d2 * (d1 + d2) / (2.0 * d2 + d3);
-#pragma unroll
-            for (int q = 0; q < NF; q++) {
-                double jump = a3[q] - a2[q];
-                eR[q] = a2[q] + cj * jump + (w * jump - g2 * sl3[q] + g1 * sl2[q]) * rsum;
-            }
-        } else {
-            double rs = 1.0 / (d2 + d3);
-#pragma unroll
-            for (int q = 0; q < NF; q++) eR[q] = (a2[q] * d3 + a3[q] * d2) * rs;
-        }
-    };
+    const int cs = (nz + RCHUNK - 1) / RCHUNK, m0 = ch * cs, m1 = min(nz, m0 + cs);
+    // the source columns: every read of the walk is then from LDS, and its
+    // stores, straight into the fields, are never waited for
+    double *src[NF];
+    bool ratio[NF], f64[NF];
     {
-        double zero[NF];
+        double *at = fld;
 #pragma unroll
         for (int q = 0; q < NF; q++) {
-            zero[q] = 0.0;
-            eR[q] = a2[q];
+            src[q] = at;
+            ratio[q] = f64[q] = false;
+            if (q >= nfg) continue;
+            ratio[q] = F.ratio[f0 + q] != 0;
+            f64[q] = sizeof(B) == 8 || F.fp64[f0 + q] != 0;
+            at += (f64[q] ? nz : (nz + 1) / 2) * RCOL;
+            if (!in) continue;
+            if (ratio[q]) stage<double>(src[q], F.src[f0 + q], delp, c0, lev, m0, m1, c);
+            else if (f64[q]) stage<double>(src[q], F.src[f0 + q], (const B *)nullptr, c0, lev, m0, m1, c);
+            else stage<float>((float *)src[q], F.src[f0 + q], (const B *)nullptr, c0, lev, m0, m1, c);
         }
-        if (nz > 1) below(0, zero);
     }
-#pragma unroll
-    for (int q = 0; q < NF; q++) {
-        l[q] = r[q] = a2[q];   // layer 0 is constant
-        c6[q] = 0.0;
-        acc[q] = 0.0;
-    }
-    int s = 0;
-    // both walks end on ps exactly
-    double top1 = ptop, bot1 = nz > 1 ? b2 : ps, rds = 1.0 / (bot1 - top1);
-    double top2 = ptop, bot2 = nz > 1 ? C.ak[1] + C.bk[1] * ps : ps;
-    double cur = ptop;
-    int m = 0;
+    interfaces(pe, nz, ptop, c, ch, in, thick);
+    const double ps = pe[nz * RCOL + c];
+    const bool mine = in && m0 < m1;
+    auto target = [&](int K) -> double {   // both coordinates end on ps exactly
+        return K == 0 ? ptop : K < nz ? ab[K] + ab[nz + 1 + K] * ps : ps;
+    };
     bool bad = false;
-    for (int it = 0; it <= 2 * nz; it++) {
-        double nxt = fmin(bot1, bot2);
-        double x1 = (cur - top1) * rds, x2 = (nxt - top1) * rds;
-        // integral over [x1, x2] of l + x (r - l + c6 (1 - x)), times the thickness
-        double h = (nxt - cur), sx = 0.5 * (x1 + x2), qx = (x1 * x1 + x1 * x2 + x2 * x2) * (1.0 / 3.0);
-#pragma unroll
-        for (int q = 0; q < NF; q++) acc[q] += h * (l[q] + (r[q] - l[q] + c6[q]) * sx - c6[q] * qx);
-        cur = nxt;
-        if (nxt >= bot2) {   // target layer m complete
-            double dm = bot2 - top2, rdm = 1.0 / dm;
-            bad |= !(dm > 0.0);
+    if (mine) {
+        double top2 = target(m0), bot2 = target(m0 + 1), cur = top2;
+        // first source layer that ends below the chunk's top
+        int lo = 0, hi = nz - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (pe[(mid + 1) * RCOL + c] > top2) hi = mid;
+            else lo = mid + 1;
+        }
+        // The state of the walk at layer s: means of layers s, s + 1, s + 2
+        // (a2..a4), thicknesses of s - 1 .. s + 2 (d1..d4), the limited slope
+        // of s + 1 (sl3), the interface value below s (eR).  It starts two
+        // layers above the first one that is integrated (or at the top).
+        int s = max(lo - 2, 0);
+        double d1 = 1, d2 = 1, d3 = 1, d4 = 1;
+        double a2[NF], a3[NF], a4[NF], sl3[NF], eR[NF], l[NF], r[NF], c6[NF], acc[NF];
+        auto layer = [&](int k, double *a, double &d) {
+            if (k >= nz) return;
+            d = pe[(k + 1) * RCOL + c] - pe[k * RCOL + c];
 #pragma unroll
             for (int q = 0; q < NF; q++) {
-                if (q < nfg)
-                    st(F.dst[f0 + q], c0 + (long)m * lev, F.fp64[f0 + q] != 0, b64,
-                       F.ratio[f0 + q] ? acc[q] : acc[q] * rdm);
-                acc[q] = 0.0;
+                a[q] = f64[q] ? src[q][k * RCOL + c] : (double)((const float *)src[q])[k * RCOL + c];
             }
-            top2 = bot2;
-            if (++m == nz) break;
-            bot2 = m + 1 < nz ? C.ak[m + 1] + C.bk[m + 1] * ps : ps;
+        };
+        // limited slope of layer s + 1
+        auto slope3 = [&](bool have) {
+            const double rr = fdiv(1.0, d2 + d3 + d4), kh = fdiv(d3 * rr * (2.0 * d2 + d3), d4 + d3),
+                         kl = fdiv(d3 * rr * (d3 + 2.0 * d4), d2 + d3);
+#pragma unroll
+            for (int q = 0; q < NF; q++) {
+                const double dl = a3[q] - a2[q], dh = a4[q] - a3[q];
+                sl3[q] = have ? mono(kh * dh + kl * dl, dl, dh) : 0.0;
+            }
+        };
+        // interface value below layer s (K = s + 1); sl2 = the limited slope of layer s
+        auto below = [&](const double *sl2) {
+            const int K = s + 1;
+            const double s23 = d2 + d3, rs = fdiv(1.0, s23);
+            if (K >= 2 && K <= nz - 2) {
+                const double rsum = fdiv(1.0, d1 + d2 + d3 + d4), cj = d2 * rs;
+                const double e1 = 2.0 * d2 + d3, e2 = 2.0 * d3 + d2;
+                const double q1 = fdiv(d1 + d2, e1), q2 = fdiv(d4 + d3, e2);
+                const double w = 2.0 * d3 * d2 * rs * (q1 - q2), g1 = d3 * q2, g2 = d2 * q1;
+#pragma unroll
+                for (int q = 0; q < NF; q++) {
+                    const double jump = a3[q] - a2[q];
+                    eR[q] = a2[q] + cj * jump + (w * jump - g2 * sl3[q] + g1 * sl2[q]) * rsum;
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < NF; q++) eR[q] = (a2[q] * d3 + a3[q] * d2) * rs;
+            }
+        };
+#pragma unroll
+        for (int q = 0; q < NF; q++) a2[q] = a3[q] = a4[q] = acc[q] = 0.0;
+        if (s > 0) d1 = pe[(s) * RCOL + c] - pe[(s - 1) * RCOL + c];
+        layer(s, a2, d2);
+        layer(s + 1, a3, d3);
+        layer(s + 2, a4, d4);
+        slope3(s + 2 <= nz - 1);
+        {
+            // used at the top layer only, which is constant
+            const double rs = fdiv(1.0, d2 + d3);
+#pragma unroll
+            for (int q = 0; q < NF; q++) {
+                eR[q] = nz > 1 ? (a2[q] * d3 + a3[q] * d2) * rs : a2[q];
+                l[q] = r[q] = a2[q];
+                c6[q] = 0.0;
+            }
         }
-        if (nxt >= bot1 && s < nz - 1) {   // into source layer s + 1
+        int m = m0;
+        for (;;) {
+            const double top1 = pe[(s) * RCOL + c], bot1 = pe[(s + 1) * RCOL + c];
+            if (s >= lo) {
+                const double rds = fdiv(1.0, bot1 - top1);
+                // integral over [x1, x2] of l + x (r - l + c6 (1 - x)), times the thickness
+                auto part = [&](double nxt) {
+                    const double x1 = (cur - top1) * rds, x2 = (nxt - top1) * rds;
+                    const double h = nxt - cur, sx = 0.5 * (x1 + x2), qx = (x1 * x1 + x1 * x2 + x2 * x2) * (1.0 / 3.0);
+#pragma unroll
+                    for (int q = 0; q < NF; q++) acc[q] += h * (l[q] + (r[q] - l[q] + c6[q]) * sx - c6[q] * qx);
+                    cur = nxt;
+                };
+                while (bot2 <= bot1) {   // target layers that end in layer s
+                    part(bot2);
+                    const double dm = bot2 - top2, rdm = fdiv(1.0, dm);
+                    bad |= !(dm > 0.0);
+#pragma unroll
+                    for (int q = 0; q < NF; q++) {
+                        if (q < nfg)
+                            st<B>(F.dst[f0 + q], c0 + (long)m * lev, f64[q], ratio[q] ? acc[q] : acc[q] * rdm);
+                        acc[q] = 0.0;
+                    }
+                    top2 = bot2;
+                    if (++m == m1) break;
+                    bot2 = target(m + 1);
+                }
+                if (m == m1) break;
+                if (s == nz - 1) {   // a target interface below the surface
+                    bad = true;
+                    break;
+                }
+                part(bot1);
+            }
+            // into source layer s + 1
             s++;
-            double sl2[NF];
+            double sl2[NF], eL[NF];
 #pragma unroll
             for (int q = 0; q < NF; q++) {
                 a2[q] = a3[q];
                 a3[q] = a4[q];
                 sl2[q] = sl3[q];
+                eL[q] = eR[q];
             }
             d1 = d2; d2 = d3; d3 = d4;
-            top1 = bot1;
-            bot1 = s < nz - 1 ? b3 : ps;
-            rds = 1.0 / (bot1 - top1);
-            b3 = b4;
-            next(s + 2, a4, d4, b4);
+            layer(s + 2, a4, d4);
             slope3(s + 2 <= nz - 1);
-            double eL[NF];
-#pragma unroll
-            for (int q = 0; q < NF; q++) eL[q] = eR[q];
-            if (s < nz - 1) below(s, sl2);
+            if (s < nz - 1) below(sl2);
 #pragma unroll
             for (int q = 0; q < NF; q++) {
-                double lq = eL[q], rq = eR[q], aq = a2[q];
-                if (s == nz - 1) {
-                    lq = rq = aq;
-                } else if ((rq - aq) * (aq - lq) <= 0.0) {
+                double lq = eL[q], rq = eR[q];
+                const double aq = a2[q];
+                if (s == nz - 1 || (rq - aq) * (aq - lq) <= 0.0) {
                     lq = rq = aq;
                 } else {
-                    double dq = rq - lq, cc = 6.0 * (aq - 0.5 * (lq + rq));
+                    const double dq = rq - lq, cc = 6.0 * (aq - 0.5 * (lq + rq));
                     if (dq * cc > dq * dq) lq = 3.0 * aq - 2.0 * rq;
                     else if (-dq * dq > dq * cc) rq = 3.0 * aq - 2.0 * lq;
                 }
@@ -238,58 +329,64 @@ __global__ __launch_bounds__(256) void k_remap(Geo G, int bulk64, double ptop, R
             }
         }
     }
-    if (bad || m != nz) atomicOr(flags + 2, 1);
+    if (bad) atomicOr(flags + 2, 1);
 }
 
-// copy the remapped interior points of the batch back into the fields
-template <int MODE>
-__global__ __launch_bounds__(256) void k_remap_back(Geo G, int bulk64, RBatch F)
+// copy the remapped interior points of a batch back into the cell fields
+template <class B>
+__global__ __launch_bounds__(256) void k_remap_back(Geo G, RBatch F)
 {
-    const int n = G.n;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x, j = blockIdx.y * blockDim.y + threadIdx.y;
-    const int ni = MODE == RM_V ? n + 1 : n, nj = MODE == RM_U ? n + 1 : n;
-    if (i >= ni || j >= nj) return;
-    const int z = (int)blockIdx.z, f = z % F.nf, tk = z / F.nf;   // tk = t * nz + k
-    const long e = G.off0 + (long)tk * G.lev + (long)j * G.pitch + i;
-    const bool b64 = bulk64 != 0, f64 = F.fp64[f] != 0;
-    st((void *)F.src[f], e, f64, b64, ld(F.dst[f], e, f64, b64));
+    const int n = G.n, col = (int)blockIdx.x * 256 + (int)threadIdx.x, j = col / n, i = col - j * n;
+    if (j >= n) return;
+    const int f = (int)blockIdx.y % F.nf, t = (int)blockIdx.y / F.nf;
+    for (int k = 0; k < G.nz; k++) {
+        const long e = G.off0 + ((long)t * G.nz + k) * G.lev + (long)j * G.pitch + i;
+        copy<B>((void *)F.src[f], F.dst[f], e, F.fp64[f] != 0);
+    }
 }
 
 // delp of every column becomes the reference thickness
-__global__ __launch_bounds__(256) void k_remap_delp(Geo G, int bulk64, double ptop, RCoef C, void *delp)
+template <class B>
+__global__ __launch_bounds__(256) void k_remap_delp(Geo G, double ptop, RCoef C, B *delp)
 {
-    const int n = G.n, nz = G.nz;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x, j = blockIdx.y * blockDim.y + threadIdx.y;
-    if (i >= n || j >= n) return;
-    const bool b64 = bulk64 != 0;
-    const long c0 = G.off0 + (long)blockIdx.z * nz * G.lev + (long)j * G.pitch + i;
-    double ps = ptop;
-    for (int k = 0; k < nz; k++) ps += ld(delp, c0 + (long)k * G.lev, false, b64);
-    double top = ptop;
-    for (int k = 0; k < nz; k++) {
-        double bot = C.ak[k + 1] + C.bk[k + 1] * ps;
-        st(delp, c0 + (long)k * G.lev, false, b64, bot - top);
+    __shared__ double pe[(RMAX + 1) * RCOL], ab[2][RMAX + 1];
+    const int n = G.n, nz = G.nz, c = (int)threadIdx.x % RCOL, ch = (int)threadIdx.x / RCOL;
+    if ((int)threadIdx.x <= nz) {
+        ab[0][threadIdx.x] = C.ak[threadIdx.x];
+        ab[1][threadIdx.x] = C.bk[threadIdx.x];
+    }
+    const int col = (int)blockIdx.x * RCOL + c, j = col / n, i = col - j * n;
+    const bool in = j < n;
+    const long c0 = G.off0 + (long)blockIdx.y * nz * G.lev + (long)j * G.pitch + i;
+    interfaces(pe, nz, ptop, c, ch, in, [&](int k) -> double { return (double)delp[c0 + (long)k * G.lev]; });
+    if (!in) return;
+    const double ps = pe[nz * RCOL + c];
+    const int cs = (nz + RCHUNK - 1) / RCHUNK, k1 = min(nz, (ch + 1) * cs);
+    double top = ch == 0 ? ptop : ab[0][min(ch * cs, nz)] + ab[1][min(ch * cs, nz)] * ps;
+    for (int k = ch * cs; k < k1; k++) {
+        const double bot = ab[0][k + 1] + ab[1][k + 1] * ps;
+        delp[c0 + (long)k * G.lev] = (B)(bot - top);
         top = bot;
     }
 }
 
 template <class K, class... A>
-void timed(const char *name, K kern, dim3 grd, dim3 blk, hipStream_t s, A... args)
+void timed(const char *name, K kern, size_t lds, dim3 grd, dim3 blk, hipStream_t s, A... args)
 {
     TimingRec r;
     bool tm = timing_wanted(name);
     if (tm) timing_begin(name, s, r);
-    hipLaunchKernelGGL(kern, grd, blk, 0, s, args...);
+    hipLaunchKernelGGL(kern, grd, blk, lds, s, args...);
     if (tm) timing_end(s, r);
 }
 
-}  // namespace
-
-fv3_status run_remap(fv3_state *s, const fv3_grid *g, const double *ak, const double *bk, void *const *q,
+template <class T>
+fv3_status remap(fv3_state *s, const fv3_grid *g, const double *ak, const double *bk, void *const *q,
                      int nq, hipStream_t st)
 {
     const Geo &G = g->geo;
-    const int n = g->n, nz = g->nz, b64 = g->bulk_bytes == 8;
+    const int n = g->n, nz = g->nz;
+    constexpr int NF = RNF;
     const double ptop = g->p.ptop;
     RCoef C{};
     for (int K = 0; K <= nz; K++) {
@@ -304,47 +401,65 @@ fv3_status run_remap(fv3_state *s, const fv3_grid *g, const double *ak, const do
 
     fv3_status hs = run_halo_cells(g, &s->delp, 1, nz, 0, st);   // face winds read the neighbour cells
     if (hs != FV3_OK) return hs;
-    const dim3 blk(64, 4);
+    const dim3 blk(256);
+    // interface pressures, coefficients; staged fields of a group
+    const size_t base = ((size_t)(nz + 1) * (RCOL + 2)) * 8;
+    auto lds = [&](const RBatch &B, int NF) {
+        size_t most = 0;
+        for (int f0 = 0; f0 < B.nf; f0 += NF) {
+            size_t e = 0;
+            for (int f = f0; f < std::min(f0 + NF, B.nf); f++)
+                e += (size_t)(sizeof(T) == 8 || B.fp64[f] ? nz : (nz + 1) / 2) * RCOL * 8;
+            most = std::max(most, e);
+        }
+        return base + most;
+    };
+    auto grid = [&](long cols, int planes) { return dim3((unsigned)((cols + RCOL - 1) / RCOL), (unsigned)planes); };
     // winds at faces
     {
-        RBatch U{}, V{};
-        U.src[0] = s->u;
-        U.dst[0] = ws;
-        U.nf = 1;
-        V.src[0] = s->v;
-        V.dst[0] = ws + slot;
-        V.nf = 1;
-        dim3 gu((unsigned)((n + 63) / 64), (unsigned)((n + 1 + 3) / 4), (unsigned)g->T);
-        dim3 gv((unsigned)((n + 1 + 63) / 64), (unsigned)((n + 3) / 4), (unsigned)g->T);
-        timed("k_remap_u", k_remap<RM_U, 1>, gu, blk, st, G, b64, ptop, C, U, (const void *)s->delp, g->flags);
-        timed("k_remap_v", k_remap<RM_V, 1>, gv, blk, st, G, b64, ptop, C, V, (const void *)s->delp, g->flags);
-        gu.z = (unsigned)(g->T * nz);
-        gv.z = (unsigned)(g->T * nz);
-        timed("k_remap_back", k_remap_back<RM_U>, gu, blk, st, G, b64, U);
-        timed("k_remap_back", k_remap_back<RM_V>, gv, blk, st, G, b64, V);
+        RBatch B{};
+        B.src[0] = s->u;
+        B.src[1] = s->v;
+        B.dst[0] = s->u;
+        B.dst[1] = s->v;
+        B.nf = 2;
+        timed("k_remap_winds", k_remap<T, RM_WIND, 1>, lds(B, 1), grid((long)n * (n + 1), g->T * 2), blk, st, G, ptop, C, B,
+              (const T *)s->delp, g->flags);
     }
     // cell fields: pt, w, delz (as delz/delp), tracers, in batches of nslots
-    std::vector<const void *> fs = {s->pt, s->w, s->delz};
+    std::vector<void *> fs = {s->pt, s->w, s->delz};
     for (int m = 0; m < nq; m++) fs.push_back(q[m]);
     for (size_t b = 0; b < fs.size(); b += (size_t)nslots) {
         RBatch B{};
         B.nf = (int)std::min<size_t>((size_t)nslots, fs.size() - b);
         for (int f = 0; f < B.nf; f++) {
             B.src[f] = fs[b + f];
-            B.dst[f] = ws + (size_t)f * slot;
             B.fp64[f] = fs[b + f] == (const void *)s->delz;
             B.ratio[f] = B.fp64[f];
         }
-        const int groups = (B.nf + RNF - 1) / RNF;
-        dim3 gc((unsigned)((n + 63) / 64), (unsigned)((n + 3) / 4), (unsigned)(g->T * groups));
-        timed("k_remap_cells", k_remap<RM_CELL, RNF>, gc, blk, st, G, b64, ptop, C, B, (const void *)s->delp,
-              g->flags);
-        gc.z = (unsigned)(g->T * nz * B.nf);
-        timed("k_remap_back", k_remap_back<RM_CELL>, gc, blk, st, G, b64, B);
+        // a field listed twice in a batch is remapped once: its blocks read it
+        // in both groups, so none of them may write it
+        bool twice = false;
+        for (int f = 0; f < B.nf; f++)
+            for (int h = 0; h < f; h++) twice |= B.src[f] == B.src[h];
+        for (int f = 0; f < B.nf; f++) B.dst[f] = twice ? ws + (size_t)f * slot : fs[b + f];
+        const int groups = (B.nf + NF - 1) / NF;
+        timed("k_remap_cells", k_remap<T, RM_CELL, NF>, lds(B, NF), grid((long)n * n, g->T * groups), blk, st, G, ptop, C, B,
+              (const T *)s->delp, g->flags);
+        if (twice)
+            timed("k_remap_back", k_remap_back<T>, 0, dim3((unsigned)(((long)n * n + 255) / 256), (unsigned)(g->T * B.nf)), blk,
+                  st, G, B);
     }
-    dim3 gd((unsigned)((n + 63) / 64), (unsigned)((n + 3) / 4), (unsigned)g->T);
-    timed("k_remap_delp", k_remap_delp, gd, blk, st, G, b64, ptop, C, s->delp);
+    timed("k_remap_delp", k_remap_delp<T>, 0, grid((long)n * n, g->T), blk, st, G, ptop, C, (T *)s->delp);
     return hipGetLastError() == hipSuccess ? FV3_OK : FV3_EDEVICE;
+}
+
+}  // namespace
+
+fv3_status run_remap(fv3_state *s, const fv3_grid *g, const double *ak, const double *bk, void *const *q, int nq,
+                     hipStream_t st)
+{
+    return g->bulk_bytes == 8 ? remap<double>(s, g, ak, bk, q, nq, st) : remap<float>(s, g, ak, bk, q, nq, st);
 }
 
 }  // namespace fv3
