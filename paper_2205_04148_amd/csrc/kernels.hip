@@ -901,64 +901,94 @@ static void fvtp(const fv3_grid *g, int planes, const FvArgs<T, C, M> &a, hipStr
 // d_sw (full step bdt on one level), around the fused transport
 // ====================================================================
 // Courant numbers and area fluxes from the contravariant half-step C-grid
-// winds (partner component: four-point mean of the other C-grid wind).
+// winds (partner component: four-point mean of the other C-grid wind).  Two
+// fields in, six out: bound by the stores and by latency, so a thread takes
+// CRK (four, or one) consecutive layers of its point, all their loads in flight, and loads
+// the metric terms once.  C192 x 79, FP32 / FP64: one layer a thread in blocks
+// of 16 x 16 259 / 442 us, two 230 / 388, four 235 / 350 (32 x 8: 190 / 392,
+// 64 x 4: 187 / 390), eight 243 / 330; C48 x 79 FP32: 19 us with four, 23 with
+// eight (too few blocks); periodic 48 x 8 FP64, the whole call of ten
+// substeps: 1117 us with one, 1147 with four.
 // CORNER = false for blocks whose reads cannot reach a cube corner block
 // (no view checks).
-template <class B, bool CORNER>
-DEVI void dsw_courant_body(const Geo &G, const Mets<B> &M, B bdt, const B *UC, const B *VC, long o, int t, int i, int j,
-                           B *ut, B *vt, B *crx, B *cry, B *xfx, B *yfx, bool &bad)
+template <class B, int CRK, bool CORNER>
+DEVI bool dsw_courant_body(const Geo &G, const Mets<B> &M, B bdt, const B *uc, const B *vc, int t, int k0, int i, int j,
+                           B *ut, B *vt, B *crx, B *cry, B *xfx, B *yfx)
 {
-    const int n = G.n;
+    const int n = G.n, k1 = min(k0 + CRK, G.nz);
+    const bool fx = i >= 0 && i <= n && j >= -3 && j <= n + 2, fy = i >= -3 && i <= n + 2 && j >= 0 && j <= n;
     const B *dxa = MP(M, M_DXA), *dya = MP(M, M_DYA);
-    if (i >= 0 && i <= n && j >= -3 && j <= n + 2) {
-        B vb;
-        if constexpr (CORNER)
-            vb = (B)0.25 * (pvy(G, UC, VC, SY, i - 1, j, 0, true) + pvy(G, UC, VC, SY, i, j, 0, true) +
-                            pvy(G, UC, VC, SY, i - 1, j + 1, 0, true) + pvy(G, UC, VC, SY, i, j + 1, 0, true));
-        else
-            vb = (B)0.25 * (AT(VC, i - 1, j) + AT(VC, i, j) + AT(VC, i - 1, j + 1) + AT(VC, i, j + 1));
-        B su = AT(MP(M, M_SIN_U), i, j);
-        B uu = rdiv(AT(UC, i, j) - vb * AT(MP(M, M_COS_U), i, j), su * su);
-        int up = uu > 0 ? i - 1 : i;
-        B da = CORNER ? pvx(G, dxa, dya, SC, up, j, 0, false) : AT(dxa, up, j);
-        B cr = rdiv(bdt * uu, da);
-        AT(ut + o, i, j) = uu;
-        AT(crx + o, i, j) = cr;
-        AT(xfx + o, i, j) = bdt * uu * su * AT(MP(M, M_DY), i, j);
-        bad |= fabs((double)cr) > 1.0;
+    bool bad = false;
+    if (fx) {
+        const B su = AT(MP(M, M_SIN_U), i, j), cu = AT(MP(M, M_COS_U), i, j), dy = AT(MP(M, M_DY), i, j);
+        const B dw = CORNER ? pvx(G, dxa, dya, SC, i - 1, j, 0, false) : AT(dxa, i - 1, j);
+        const B de = CORNER ? pvx(G, dxa, dya, SC, i, j, 0, false) : AT(dxa, i, j);
+#pragma unroll
+        for (int q = 0; q < CRK; q++) {
+            const long o = pidx(G, G.nz, t, min(k0 + q, k1 - 1));
+            const B *UC = uc + o, *VC = vc + o;
+            B vb;
+            if constexpr (CORNER)
+                vb = (B)0.25 * (pvy(G, UC, VC, SY, i - 1, j, 0, true) + pvy(G, UC, VC, SY, i, j, 0, true) +
+                                pvy(G, UC, VC, SY, i - 1, j + 1, 0, true) + pvy(G, UC, VC, SY, i, j + 1, 0, true));
+            else
+                vb = (B)0.25 * (AT(VC, i - 1, j) + AT(VC, i, j) + AT(VC, i - 1, j + 1) + AT(VC, i, j + 1));
+            B uu = rdiv(AT(UC, i, j) - vb * cu, su * su);
+            B da = uu > 0 ? dw : de;
+            B cr = rdiv(bdt * uu, da);
+            if (k0 + q < k1) {
+                AT(ut + o, i, j) = uu;
+                AT(crx + o, i, j) = cr;
+                AT(xfx + o, i, j) = bdt * uu * su * dy;
+                bad |= fabs((double)cr) > 1.0;
+            }
+        }
     }
-    if (i >= -3 && i <= n + 2 && j >= 0 && j <= n) {
-        B ub;
-        if constexpr (CORNER)
-            ub = (B)0.25 * (pvx(G, UC, VC, SX, i, j - 1, 1, true) + pvx(G, UC, VC, SX, i + 1, j - 1, 1, true) +
-                            pvx(G, UC, VC, SX, i, j, 1, true) + pvx(G, UC, VC, SX, i + 1, j, 1, true));
-        else
-            ub = (B)0.25 * (AT(UC, i, j - 1) + AT(UC, i + 1, j - 1) + AT(UC, i, j) + AT(UC, i + 1, j));
-        B sv_ = AT(MP(M, M_SIN_V), i, j);
-        B vv = rdiv(AT(VC, i, j) - ub * AT(MP(M, M_COS_V), i, j), sv_ * sv_);
-        int up = vv > 0 ? j - 1 : j;
-        B da = CORNER ? pvy(G, dxa, dya, SC, i, up, 1, false) : AT(dya, i, up);
-        B cr = rdiv(bdt * vv, da);
-        AT(vt + o, i, j) = vv;
-        AT(cry + o, i, j) = cr;
-        AT(yfx + o, i, j) = bdt * vv * sv_ * AT(MP(M, M_DX), i, j);
-        bad |= fabs((double)cr) > 1.0;
+    if (fy) {
+        const B sv_ = AT(MP(M, M_SIN_V), i, j), cv = AT(MP(M, M_COS_V), i, j), dx = AT(MP(M, M_DX), i, j);
+        const B ds = CORNER ? pvy(G, dxa, dya, SC, i, j - 1, 1, false) : AT(dya, i, j - 1);
+        const B dn = CORNER ? pvy(G, dxa, dya, SC, i, j, 1, false) : AT(dya, i, j);
+#pragma unroll
+        for (int q = 0; q < CRK; q++) {
+            const long o = pidx(G, G.nz, t, min(k0 + q, k1 - 1));
+            const B *UC = uc + o, *VC = vc + o;
+            B ub;
+            if constexpr (CORNER)
+                ub = (B)0.25 * (pvx(G, UC, VC, SX, i, j - 1, 1, true) + pvx(G, UC, VC, SX, i + 1, j - 1, 1, true) +
+                                pvx(G, UC, VC, SX, i, j, 1, true) + pvx(G, UC, VC, SX, i + 1, j, 1, true));
+            else
+                ub = (B)0.25 * (AT(UC, i, j - 1) + AT(UC, i + 1, j - 1) + AT(UC, i, j) + AT(UC, i + 1, j));
+            B vv = rdiv(AT(VC, i, j) - ub * cv, sv_ * sv_);
+            B da = vv > 0 ? ds : dn;
+            B cr = rdiv(bdt * vv, da);
+            if (k0 + q < k1) {
+                AT(vt + o, i, j) = vv;
+                AT(cry + o, i, j) = cr;
+                AT(yfx + o, i, j) = bdt * vv * sv_ * dx;
+                bad |= fabs((double)cr) > 1.0;
+            }
+        }
     }
+    return bad;
 }
 template <class B>
-DEVI void k_dsw_courant(KARGS, Geo G, Mets<B> M, B bdt, const B *uc, const B *vc, B *ut, B *vt,
+DEVI void k_dsw_courant(KARGS, Geo G, Mets<B> M, int layers, B bdt, const B *uc, const B *vc, B *ut, B *vt,
                               B *crx, B *cry, B *xfx, B *yfx, int *flags)
 {
-    KBEGIN(G.nz);
-    long o = pidx(G, G.nz, t, k);
+    KBEGIN((G.nz + layers - 1) / layers);
     // the block's reads span its points +-1 in both directions; corner views
     // exist only outside [0, n - 1] in both
     const int i0 = ib + (int)(bk.x * blockDim.x) - 1, i1 = i0 + (int)blockDim.x + 1;
     const int j0 = jlo + (int)(bk.y * blockDim.y) - 1, j1 = j0 + (int)blockDim.y + 1;
     const bool corner = G.cube && (i0 < 0 || i1 >= G.n) && (j0 < 0 || j1 >= G.n);
-    bool bad = false;
-    if (corner) dsw_courant_body<B, true>(G, M, bdt, uc + o, vc + o, o, t, i, j, ut, vt, crx, cry, xfx, yfx, bad);
-    else dsw_courant_body<B, false>(G, M, bdt, uc + o, vc + o, o, t, i, j, ut, vt, crx, cry, xfx, yfx, bad);
+    bool bad;
+    if (layers == 1) {
+        if (corner) bad = dsw_courant_body<B, 1, true>(G, M, bdt, uc, vc, t, k, i, j, ut, vt, crx, cry, xfx, yfx);
+        else bad = dsw_courant_body<B, 1, false>(G, M, bdt, uc, vc, t, k, i, j, ut, vt, crx, cry, xfx, yfx);
+    } else {
+        if (corner) bad = dsw_courant_body<B, 4, true>(G, M, bdt, uc, vc, t, k * 4, i, j, ut, vt, crx, cry, xfx, yfx);
+        else bad = dsw_courant_body<B, 4, false>(G, M, bdt, uc, vc, t, k * 4, i, j, ut, vt, crx, cry, xfx, yfx);
+    }
     if (bad) atomicOr(flags, 1);
 }
 
@@ -1983,8 +2013,13 @@ static fv3_status substeps_t(fv3_state *s, const fv3_grid *g, double dt, int n_s
         halo_pair(g, g->planCv, uc, vc, nz, st);
         STOP(5);
         // d_sw
-        launch2d_s(k_dsw_courant<B>, (Shape{16, 16}), -3, n + 2, -3, n + 2, P, st, G, M, (B)bdt, (const B *)uc, (const B *)vc, W.ut,
-                 W.vt, W.crx, W.cry, W.xfx, W.yfx, g->flags);
+        {
+            // four layers a thread where that leaves four wavefronts on every SIMD
+            const int layers = (long)(n + 6) * (n + 6) * P / 64 >= 4 * 4096 ? 4 : 1;
+            launch2d_s(k_dsw_courant<B>, (sizeof(B) == 4 ? Shape{32, 8} : Shape{16, 16}), -3, n + 2, -3, n + 2,
+                       T * ((nz + layers - 1) / layers), st, G, M, layers, (B)bdt, (const B *)uc, (const B *)vc, W.ut,
+                       W.vt, W.crx, W.cry, W.xfx, W.yfx, g->flags);
+        }
         const bool eppm = g->p.edge_ppm && g->p.kind == FV3_GRID_CUBED_SPHERE;
         // the marching transports' common arguments
         MarchArgs<B> ma{};
