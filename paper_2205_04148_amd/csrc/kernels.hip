@@ -32,6 +32,7 @@
 #include "fv3_internal.hpp"
 #include "column.hpp"
 #include "csw.hpp"
+#include "nhgrad.hpp"
 #include "launch.hpp"
 #include "transport.hpp"
 
@@ -1317,279 +1318,6 @@ DEVI void k_delz_from_zh(KARGS, Geo G, const double *zn, const double *phis, dou
 }
 
 // ====================================================================
-// nh_p_grad: corner values by the fourth-order (-1,7,7,-1)/12 tensor
-// interpolation (inner pass along x with the x-sweep corner view; mean of
-// the three cells at a cube vertex) of pfull and phi at the layer's two
-// interfaces and of delp, staged through LDS, then the finite-volume
-// pressure gradient along each D-grid edge.  Block: NPX x NPY corners; 33
-// wide so that the n + 1 corner columns of C192 take 6 tiles (32 wide took 7,
-// the last with one column), 7 rows so that its faces fit 256 threads.
-// ====================================================================
-#ifndef FV3_NHP_TX
-#define FV3_NHP_TX 33
-#endif
-#ifndef FV3_NHP_TY
-#define FV3_NHP_TY 7
-#endif
-constexpr int NPX = FV3_NHP_TX, NPY = FV3_NHP_TY;   // nh_p_grad corner tile
-constexpr int NCW = NPX + 5, NCH = NPY + 5;   // cells i0-2..i0+NPX+2, j0-2..j0+NPY+2
-
-// cell means x0..x3 of the cells m-2 .. m+1 to interface m: (-1,7,7,-1)/12,
-// or with `edge` next to a tile edge (interfaces 0, n) the interface value
-// of the quadratic with the three nearest cell means on the own side
-// (1/3, 5/6, -1/6), on the edge the mean of the two sides' linear
-// extrapolations (option edge_interp)
-DEVI double face_mean(double x0, double x1, double x2, double x3, int m, int n, bool edge, const double *w4)
-{
-    if (edge) {
-        if (m == 0 || m == n) return 0.75 * (x1 + x2) - 0.25 * (x0 + x3);
-        if (m == 1 || m == n + 1) return (2.0 * x1 + 5.0 * x2 - x3) / 6.0;
-        if (m == -1 || m == n - 1) return (2.0 * x2 + 5.0 * x1 - x0) / 6.0;
-    }
-    double r = 0.0;
-    r += w4[0] * x0;
-    r += w4[1] * x1;
-    r += w4[2] * x2;
-    r += w4[3] * x3;
-    return r;
-}
-
-// Each block walks NHK consecutive layers of its corner tile: the corner
-// values of p and phi at the interface below one layer are those above the
-// next, so they are kept (two alternating LDS slots) instead of being
-// interpolated again, and per layer only p, phi at the lower interface and
-// delp are staged.  The next layer's cells and winds are loaded while the
-// current layer computes.
-#ifndef FV3_NHK
-#define FV3_NHK 8
-#endif
-constexpr int NHK = FV3_NHK;
-constexpr int NCS = (NCH * NCW + 255) / 256;    // staged cells per thread
-constexpr int NBC = (NPY + 1) * (NPX + 1);      // corners of a block
-constexpr int NPP = (NPX * NPY + 255) / 256;    // faces per thread
-struct NhLds {
-    double sc[3][NCH * NCW];   // staged cells (x-sweep view), then the x pass in place
-    double sb[5][NBC];         // corner values: p, p (alternating interfaces), phi, phi, delp
-};
-
-// cells of the block's staging window into registers: p and phi of one
-// interface and (WD) delp of one layer
-template <class B, bool CORNER, bool WD>
-DEVI void nh_load(const Geo &G, int i0, int j0, const double *Fp, const double *Fz, const B *D, double (&r)[NCS][3])
-{
-    const int n = G.n;
-#pragma unroll
-    for (int m = 0; m < NCS; m++) {
-        const int e = (int)threadIdx.x + m * 256, rr = e / NCW, c = e - rr * NCW;
-        const int i = i0 - 2 + c, j = j0 - 2 + rr;
-        double a = 0.0, b = 0.0, d = 0.0;
-        if (e < NCH * NCW && i <= n + 2 && j <= n + 2) {
-            if constexpr (CORNER) {
-                a = sv(G, Fp, SC, i, j, 0);
-                b = sv(G, Fz, SC, i, j, 0);
-                if constexpr (WD) d = (double)sv(G, D, SC, i, j, 0);
-            } else {
-                a = AT(Fp, i, j);
-                b = AT(Fz, i, j);
-                if constexpr (WD) d = (double)AT(D, i, j);
-            }
-        }
-        r[m][0] = a;
-        r[m][1] = b;
-        r[m][2] = d;
-    }
-}
-
-template <int NF>
-DEVI void nh_store(NhLds &L, const double (&r)[NCS][3])
-{
-#pragma unroll
-    for (int m = 0; m < NCS; m++) {
-        const int e = (int)threadIdx.x + m * 256;
-        if (e < NCH * NCW) {
-#pragma unroll
-            for (int f = 0; f < NF; f++) L.sc[f][e] = r[m][f];
-        }
-    }
-}
-
-// The tensor interpolation of the NF staged fields to the block's corners
-// (into corner slots s0, s1, s2) in two passes: along x for every staged row
-// at every corner column (into registers), then along y at each corner.
-// Expects the staged cells to be visible (after a barrier); ends with one.
-template <bool EI, bool CORNER, int NF>
-DEVI void nh_corners(const Geo &G, int i0, int j0, NhLds &L, int s0, int s1, int s2, bool ebx, bool eby)
-{
-    const int n = G.n, tid = threadIdx.x;
-    const int slot[3] = {s0, s1, s2};
-    const double w4[4] = {-1.0 / 12.0, 7.0 / 12.0, 7.0 / 12.0, -1.0 / 12.0};
-    constexpr int NRX = (NPY + 4) * (NPX + 1), NRP = (NRX + 255) / 256;
-    double xr[NRP][NF];
-#pragma unroll
-    for (int m = 0; m < NRP; m++) {
-        const int e = tid + m * 256, rr = e / (NPX + 1), c = e - rr * (NPX + 1);
-        // the edge rule on rows inside the tile (row j = j0 - 2 + rr)
-        const int jr = j0 - 2 + rr;
-        const bool ex = EI && jr >= 0 && jr < n;
-#pragma unroll
-        for (int f = 0; f < NF; f++) {
-            double rw = 0.0;
-            if (e < NRX) {
-                const double *row = &L.sc[f][rr * NCW + c];
-                if (EI && ebx)
-                    rw = face_mean(row[0], row[1], row[2], row[3], i0 + c, n, ex, w4);
-                else
-                    for (int a = 0; a < 4; a++) rw += w4[a] * row[a];
-            }
-            xr[m][f] = rw;
-        }
-    }
-    // corners at cube vertices (corner blocks only): mean of the three
-    // cells, from the staged cells
-    if constexpr (CORNER) {
-        for (int e = tid; e < NBC; e += 256) {
-            const int r = e / (NPX + 1), c = e - r * (NPX + 1);
-            const int i = i0 + c, j = j0 + r;
-            if (i > n || j > n || !is_vertex(G, i, j)) continue;
-            const int ci[4] = {i - 1, i, i, i - 1}, cj[4] = {j - 1, j - 1, j, j};
-            for (int f = 0; f < NF; f++) {
-                double sum = 0.0;
-                for (int q = 0; q < 4; q++)
-                    if (!in_corner(G, SC, ci[q], cj[q])) sum += L.sc[f][(cj[q] - j0 + 2) * NCW + (ci[q] - i0 + 2)];
-                L.sb[slot[f]][e] = sum / 3.0;
-            }
-        }
-    }
-    __syncthreads();
-    // the x pass in place of the staged cells (row rr, corner column c)
-#pragma unroll
-    for (int m = 0; m < NRP; m++) {
-        const int e = tid + m * 256, rr = e / (NPX + 1), c = e - rr * (NPX + 1);
-        if (e < NRX) {
-#pragma unroll
-            for (int f = 0; f < NF; f++) L.sc[f][rr * NCW + c] = xr[m][f];
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < (NBC + 255) / 256; m++) {
-        const int e = tid + m * 256;
-        if (e >= NBC) break;
-        const int r = e / (NPX + 1), c = e - r * (NPX + 1);
-        const int i = i0 + c, j = j0 + r;
-        if (i > n || j > n || (CORNER && is_vertex(G, i, j))) continue;
-#pragma unroll
-        for (int f = 0; f < NF; f++) {
-            double acc = 0.0;
-            if (EI && eby) {
-                const double *col = &L.sc[f][r * NCW + c];
-                acc = face_mean(col[0], col[NCW], col[2 * NCW], col[3 * NCW], j, n, true, w4);
-            } else {
-                for (int b = 0; b < 4; b++) acc += w4[b] * L.sc[f][(r + b) * NCW + c];
-            }
-            L.sb[slot[f]][e] = acc;
-        }
-    }
-    __syncthreads();
-}
-
-// CORNER: the block's staging window reaches a cube corner block, so its
-// cell reads go through the corner views and its vertex corners take the
-// three-cell mean; every other block reads the planes directly.
-template <class B, bool EI, bool CORNER>
-DEVI void nhpgrad_body(Bk bk, const Geo &G, const MetD &M, double bdt, const double *pfull, const double *phi,
-                       const B *delp, B *u, B *v, NhLds &L)
-{
-    const int n = G.n, nz = G.nz, tid = threadIdx.x;
-    const int i0 = bk.x * NPX, j0 = bk.y * NPY;
-    const int nzb = (nz + NHK - 1) / NHK;
-    const int t = (int)bk.z / nzb, k0 = ((int)bk.z % nzb) * NHK, k1 = k0 + NHK < nz ? k0 + NHK : nz;
-    // with the edge rule, only blocks with corner columns (rows) within one
-    // cell of a tile edge (0, 1, n - 1, n) take the one-sided branches of
-    // the x (y) pass
-    const bool ebx = EI && (i0 <= 1 || i0 + NPX >= n - 1), eby = EI && (j0 <= 1 || j0 + NPY >= n - 1);
-    // edge lengths of the faces this thread updates (the same on every layer)
-    double pdx[NPP], pdy[NPP];
-#pragma unroll
-    for (int m = 0; m < NPP; m++) {
-        const int e = tid + m * 256, r = e / NPX, c = e - r * NPX;
-        const int i = i0 + c, j = j0 + r;
-        const bool in = e < NPX * NPY;
-        pdx[m] = (in && i < n && j <= n) ? AT(MP(M, M_DX), i, j) : 1.0;
-        pdy[m] = (in && i <= n && j < n) ? AT(MP(M, M_DY), i, j) : 1.0;
-    }
-    // the interface above the first layer
-    double rg[NCS][3];
-    nh_load<B, CORNER, false>(G, i0, j0, pfull + pidx(G, nz + 1, t, k0), phi + pidx(G, nz + 1, t, k0),
-                              (const B *)nullptr, rg);
-    nh_store<2>(L, rg);
-    __syncthreads();
-    nh_corners<EI, CORNER, 2>(G, i0, j0, L, 0, 2, 4, ebx, eby);
-    nh_load<B, CORNER, true>(G, i0, j0, pfull + pidx(G, nz + 1, t, k0 + 1), phi + pidx(G, nz + 1, t, k0 + 1),
-                             delp + pidx(G, nz, t, k0), rg);
-    for (int k = k0; k < k1; k++) {
-        const int b = 1 - ((k - k0) & 1), a = 1 - b;   // corner slots of the lower / upper interface
-        const long o = pidx(G, nz, t, k);
-        double pu[NPP], pv[NPP];
-#pragma unroll
-        for (int m = 0; m < NPP; m++) {
-            const int e = tid + m * 256, r = e / NPX, c = e - r * NPX;
-            const int i = i0 + c, j = j0 + r;
-            const bool in = e < NPX * NPY;
-            pu[m] = (in && i < n && j <= n) ? (double)AT(u + o, i, j) : 0.0;
-            pv[m] = (in && i <= n && j < n) ? (double)AT(v + o, i, j) : 0.0;
-        }
-        nh_store<3>(L, rg);
-        __syncthreads();
-        if (k + 1 < k1)
-            nh_load<B, CORNER, true>(G, i0, j0, pfull + pidx(G, nz + 1, t, k + 2), phi + pidx(G, nz + 1, t, k + 2),
-                                     delp + pidx(G, nz, t, k + 1), rg);
-        nh_corners<EI, CORNER, 3>(G, i0, j0, L, b, 2 + b, 4, ebx, eby);
-        const double *P0 = L.sb[a], *P1 = L.sb[b], *Z0 = L.sb[2 + a], *Z1 = L.sb[2 + b], *DD = L.sb[4];
-        // Each block owns the faces of its NPX x NPY corner rows/columns: the
-        // grid spans corners 0..n, so a face row or column on a block boundary
-        // is updated by exactly one block.  u on y-faces (i, j) uses corners
-        // (i, j) and (i + 1, j); v on x-faces (i, j) corners (i, j) and (i, j + 1).
-#pragma unroll
-        for (int m = 0; m < NPP; m++) {
-            const int e = tid + m * 256;
-            if (e >= NPX * NPY) break;
-            const int r = e / NPX, c = e - r * NPX;
-            const int i = i0 + c, j = j0 + r;
-            const int W = r * (NPX + 1) + c;
-            if (i < n && j <= n) {
-                const int E = W + 1;
-                AT(u + o, i, j) = (B)pu[m] + (B)pgf(bdt, pdx[m], DD[W], DD[E], Z0[W], Z1[W], Z0[E], Z1[E], P0[W],
-                                                    P1[W], P0[E], P1[E]);
-            }
-            if (i <= n && j < n) {
-                const int E = W + (NPX + 1);
-                AT(v + o, i, j) = (B)pv[m] + (B)pgf(bdt, pdy[m], DD[W], DD[E], Z0[W], Z1[W], Z0[E], Z1[E], P0[W],
-                                                    P1[W], P0[E], P1[E]);
-            }
-        }
-    }
-}
-
-template <class B, bool EI = false>
-DEVI void k_nhpgrad(Bk bk, Geo G, MetD M, double bdt, const double *pfull, const double *phi, const B *delp, B *u,
-                    B *v)
-{
-    __shared__ NhLds L;
-    const int i0 = bk.x * NPX, j0 = bk.y * NPY;
-    const bool corner = G.cube && (i0 - 2 < 0 || i0 + NPX + 2 >= G.n) && (j0 - 2 < 0 || j0 + NPY + 2 >= G.n);
-    if (corner) nhpgrad_body<B, EI, true>(bk, G, M, bdt, pfull, phi, delp, u, v, L);
-    else nhpgrad_body<B, EI, false>(bk, G, M, bdt, pfull, phi, delp, u, v, L);
-}
-
-// FP32 nh_p_grad compiled for six wavefronts per SIMD (its LDS allows six,
-// its natural 95 VGPRs five; 75 VGPRs without spills)
-#ifndef FV3_NHP_OCC
-#define FV3_NHP_OCC 6
-#endif
-template <> constexpr int kocc<k_nhpgrad<float, false>> = FV3_NHP_OCC;
-
-// ====================================================================
 // utilities: fills, copies, finiteness check, tracer helpers, reductions
 // ====================================================================
 template <class T>
@@ -2162,13 +1890,9 @@ static fv3_status substeps_t(fv3_state *s, const fv3_grid *g, double dt, int n_s
         STOP(9);
         // nh_p_grad
         {
-            const dim3 ngrd((n + NPX) / NPX, (n + NPY) / NPY, T * ((nz + NHK - 1) / NHK));
-            if (g->p.edge_interp && g->p.kind == FV3_GRID_CUBED_SPHERE)
-                launch_fn<k_nhpgrad<B, true>>("k_nhpgrad", ngrd, dim3(256), st, G, Md, bdt, (const double *)s->pfull,
-                                              (const double *)s->phi, (const B *)delp, u, v);
-            else
-                launch_fn<k_nhpgrad<B>>("k_nhpgrad", ngrd, dim3(256), st, G, Md, bdt, (const double *)s->pfull,
-                                        (const double *)s->phi, (const B *)delp, u, v);
+            NhArgs<B> a{};
+            a.bdt = bdt; a.pfull = s->pfull; a.phi = s->phi; a.delp = delp; a.u = u; a.v = v;
+            nh_grad(g, a, st);
         }
 #undef STOP
     }
