@@ -24,7 +24,8 @@
 // face fluxes of their rims: FP32 575 -> 389 us, FP64 963 -> 713.
 //
 // The FP32 result is bit for bit that of the expressions as first written and
-// contracted; the fma forms are therefore explicit.
+// contracted; the fma forms are therefore explicit.  FP32 with edge_interp has
+// its own kernel (csw_edge.hip).
 //
 // Cube corner blocks are never stored.  The rows and columns that reach them
 // are read through the corner views: D-grid winds and cell fields as they are
@@ -279,7 +280,6 @@ DEVI void k_csw(Bk bk, Geo G, Mets<B> M, CswArgs<B> A)
 // FP32: 128 registers, four wavefronts per SIMD (130 and three without the
 // hint: 475 against 389 us at C192 x 79)
 template <> constexpr int kocc<k_csw<float, false>> = 4;
-template <> constexpr int kocc<k_csw<float, true>> = 4;
 
 template <class B>
 void csw(const fv3_grid *g, const CswArgs<B> &args, hipStream_t st)
@@ -290,9 +290,10 @@ void csw(const fv3_grid *g, const CswArgs<B> &args, hipStream_t st)
     const int pts = g->n + 3;
     march_shape(pts, (long)g->T * ((g->nz + 3) / 4) * 4, 5, sizeof(B) == 8 ? 2 : 4, a.strips, a.width, a.segs, a.rows);
     const dim3 grd((unsigned)((long)a.strips * a.segs * g->T * ((g->nz + 3) / 4))), blk(256);
-    if (g->p.edge_interp && g->p.kind == FV3_GRID_CUBED_SPHERE)
-        launch_fn<k_csw<B, true>>("k_csw", grd, blk, st, g->geo, M, a);
-    else
+    if (g->p.edge_interp && g->p.kind == FV3_GRID_CUBED_SPHERE) {
+        if constexpr (sizeof(B) == 4) csw_edge(g, a, st);
+        else launch_fn<k_csw<B, true>>("k_csw", grd, blk, st, g->geo, M, a);
+    } else
         launch_fn<k_csw<B, false>>("k_csw", grd, blk, st, g->geo, M, a);
 }
 template void csw<float>(const fv3_grid *, const CswArgs<float> &, hipStream_t);

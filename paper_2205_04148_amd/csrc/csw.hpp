@@ -1,4 +1,4 @@
-// c_sw (csw.hip).
+// c_sw (csw.hip, csw_edge.hip).
 #pragma once
 
 #include "march.hpp"
@@ -16,5 +16,8 @@ struct CswArgs {
 };
 template <class B>
 void csw(const fv3_grid *g, const CswArgs<B> &a, hipStream_t st);
+
+// FP32 with one-sided stencils at tile edges (csw_edge.hip)
+void csw_edge(const fv3_grid *g, const CswArgs<float> &a, hipStream_t st);
 
 }  // namespace fv3

@@ -7,15 +7,16 @@
 // build); the column solves, vertical scans, pressure gradients and mass-flux
 // accumulators are always FP64.
 //
-// Stencil kernels work on one (tile, level) plane per grid z index.  The
-// flux-form transport fv_tp_2d (paper Sec. IX-C) is one fused kernel: a
-// 64 x 16 cell tile with its 3-point halo is staged in LDS, and the outer
-// fluxes, inner advective updates, final fluxes and the flux-divergence update
-// of the transported field all run out of LDS.  Corner blocks of cube tiles
+// Stencil kernels of this file work on one (tile, level) plane per grid z index.
+// c_sw, the flux-form transports, nh_p_grad and the column solves have files of
+// their own (csw, transport, nhgrad, column); with one-sided faces at tile edges
+// (edge_ppm) the transport fv_tp_2d (paper Sec. IX-C) is the kernel here: a cell
+// tile with its 3-point halo is staged in LDS, and the outer fluxes, inner
+// advective updates, final fluxes and the flux-divergence update of the
+// transported field all run out of LDS.  Corner blocks of cube tiles
 // are never stored: reads of them are remapped to the adjacent edge halo
 // rotated about the cube vertex, in the x-sweep or y-sweep sense of the
-// reading stencil (generalising the corner statement of Sec. VII-C).  Column
-// kernels march k in one thread per column with software-pipelined loads.
+// reading stencil (generalising the corner statement of Sec. VII-C).
 //
 // The order of the stages inside a substep follows the FV3 acoustic loop
 // (Sec. II): halo A, c_sw, dz_c + riem_solver_c, p_grad_c, halo B, d_sw,
@@ -395,8 +396,8 @@ DEVI void k_pgradc(KARGS, Geo G, MetD M, double dt2, const B *delpc, const doubl
 }
 
 // ====================================================================
-// fv_tp_2d (Sec. IX-C): Lin-Rood flux-form transport on one level, fused.
-// A cell tile (32 x 16 in FP32, 32 x 8 in FP64) plus 3-point halo is staged
+// fv_tp_2d (Sec. IX-C) with one-sided faces at cube tile edges (edge_ppm):
+// Lin-Rood flux-form transport on one level, fused.  A cell tile (32 x 16 in FP32, 32 x 8 in FP64) plus 3-point halo is staged
 // in LDS in both sweep views; outer PPM fluxes, inner advective half updates, final averaged and
 // weighted fluxes, then an epilogue that applies the flux divergence:
 //   EPI_FLUX   write the fluxes only
@@ -479,7 +480,7 @@ struct FvLds {
 // CORNER: the block's staging window reaches a cube corner block (only
 // blocks at the four corners of a tile), so its field reads go through the
 // corner views; every other block reads the plane directly.
-template <class T, class C, class M, int EPI, int ORD, int EDGE, bool CORNER>
+template <class T, class C, class M, int EPI, int ORD, bool CORNER>
 DEVI void fvtp_body(Bk bk, const Geo &G, const FvArgs<T, C, M> &A, FvLds<T> &L)
 {
     constexpr int FTX = FvTile<T>::X, FTY = FvTile<T>::Y;
@@ -502,8 +503,8 @@ DEVI void fvtp_body(Bk bk, const Geo &G, const FvArgs<T, C, M> &A, FvLds<T> &L)
     const int avg = EPI == EPI_ADV && A.iface && k > 0;   // set only for the interface heights
     const long ob = avg ? pidx(G, A.Lc, t, k - 1) : oc;
     const T *AR = A.area + G.off0 + (long)t * G.lev;
-    const T *DXA = EDGE ? A.dxa + G.off0 + (long)t * G.lev : nullptr;
-    const T *DYA = EDGE ? A.dya + G.off0 + (long)t * G.lev : nullptr;
+    const T *DXA = A.dxa + G.off0 + (long)t * G.lev;
+    const T *DYA = A.dya + G.off0 + (long)t * G.lev;
     const T *Qh = Q - hb, *ARh = AR - hb;
     const C *cryh = A.cry + oc - hb, *yfxh = A.yfx + oc - hb, *crxh = A.crx + oc - hb, *xfxh = A.xfx + oc - hb;
     const C *cry0h = A.cry + ob - hb, *yfx0h = A.yfx + ob - hb, *crx0h = A.crx + ob - hb, *xfx0h = A.xfx + ob - hb;
@@ -527,7 +528,7 @@ DEVI void fvtp_body(Bk bk, const Geo &G, const FvArgs<T, C, M> &A, FvLds<T> &L)
         wx[m] = (MX && in) ? ldo(MX, (unsigned)(j * P + i)) : (M)0;
         if constexpr (EPI == EPI_DELP) {
             // the faces phase 4 writes: c < FTX, or the last face i == n
-            const bool own = in && (c < FTX || i == n) && !(EDGE && edge_face(i, n));
+            const bool own = in && (c < FTX || i == n) && !edge_face(i, n);
             amx[m] = own ? ldo(A.mfx + oc, (unsigned)(j * P + i)) : 0.0;
             acx[m] = own ? ldo(A.cxa + oc, (unsigned)(j * P + i)) : (C)0;
         }
@@ -539,7 +540,7 @@ DEVI void fvtp_body(Bk bk, const Geo &G, const FvArgs<T, C, M> &A, FvLds<T> &L)
         const bool in = e < YH * FTX && i < n && j <= n;
         wy[m] = (MY && in) ? ldo(MY, (unsigned)(j * P + i)) : (M)0;
         if constexpr (EPI == EPI_DELP) {
-            const bool own = in && (r < FTY || j == n) && !(EDGE && edge_face(j, n));
+            const bool own = in && (r < FTY || j == n) && !edge_face(j, n);
             amy[m] = own ? ldo(A.mfy + oc, (unsigned)(j * P + i)) : 0.0;
             acy[m] = own ? ldo(A.cya + oc, (unsigned)(j * P + i)) : (C)0;
         }
@@ -672,7 +673,7 @@ DEVI void fvtp_body(Bk bk, const Geo &G, const FvArgs<T, C, M> &A, FvLds<T> &L)
         }
         sFx[e] = f;
     }
-    if constexpr (EDGE) {
+    {
         // faces with an edge cell upwind, on sweeps whose cross index lies
         // inside the tile (at most six per row or column): the one-sided
         // values replace the centred ones
@@ -755,14 +756,14 @@ DEVI void fvtp_body(Bk bk, const Geo &G, const FvArgs<T, C, M> &A, FvLds<T> &L)
         if (e >= FTY * XW) break;
         int r = e / XW, c = e - r * XW;
         int i = i0 + c, j = j0 + r;
-        if (i <= n && j < n && !(EDGE && edge_face(i, n))) {
+        if (i <= n && j < n && !edge_face(i, n)) {
             const int s = (r + 3) * XW + c;
             T fx = ppm_lds<1, ORD>(sQi + r * QW + c, sCX[s]);
             put_x(i, c, j * P + i, s, fx, A.mx ? (T)wx[m] : sXF[s], amx[EPI == EPI_DELP ? m : 0],
                   acx[EPI == EPI_DELP ? m : 0]);
         }
     }
-    if constexpr (EDGE) {
+    {
         // the faces with an edge cell upwind, at most six per row
         for (int e = tid; e < FTY * 6; e += FNT) {
             const int r = e / 6, i = edge_face_at(e - r * 6, n), c = i - i0, j = j0 + r;
@@ -782,14 +783,14 @@ DEVI void fvtp_body(Bk bk, const Geo &G, const FvArgs<T, C, M> &A, FvLds<T> &L)
         if (e >= YH * FTX) break;
         int r = e / FTX, c = e - r * FTX;
         int i = i0 + c, j = j0 + r;
-        if (i < n && j <= n && !(EDGE && edge_face(j, n))) {
+        if (i < n && j <= n && !edge_face(j, n)) {
             const int s = r * YW + c + 3;
             T fy = ppm_lds<FTX, ORD>(sQj + r * FTX + c, sCY[s]);
             put_y(j, r, j * P + i, s, fy, A.my ? (T)wy[m] : sYF[s], amy[EPI == EPI_DELP ? m : 0],
                   acy[EPI == EPI_DELP ? m : 0]);
         }
     }
-    if constexpr (EDGE) {
+    {
         // the faces with an edge cell upwind, at most six per column
         for (int e = tid; e < FTX * 6; e += FNT) {
             const int c = e / 6, j = edge_face_at(e - c * 6, n), r = j - j0, i = i0 + c;
@@ -837,18 +838,18 @@ DEVI void fvtp_body(Bk bk, const Geo &G, const FvArgs<T, C, M> &A, FvLds<T> &L)
 }
 
 
-template <class T, class C, class M, int EPI, int ORD, int EDGE>
+template <class T, class C, class M, int EPI, int ORD>
 DEVI void k_fvtp(Bk bk, Geo G, FvArgs<T, C, M> A)
 {
     constexpr int FTX = FvTile<T>::X, FTY = FvTile<T>::Y;
     __shared__ FvLds<T> L;
     const int n = G.n, i0 = bk.x * FTX, j0 = bk.y * FTY;
     const bool corner = G.cube && (i0 - 3 < 0 || i0 + FTX + 2 >= n) && (j0 - 3 < 0 || j0 + FTY + 2 >= n);
-    if (corner) fvtp_body<T, C, M, EPI, ORD, EDGE, true>(bk, G, A, L);
-    else fvtp_body<T, C, M, EPI, ORD, EDGE, false>(bk, G, A, L);
+    if (corner) fvtp_body<T, C, M, EPI, ORD, true>(bk, G, A, L);
+    else fvtp_body<T, C, M, EPI, ORD, false>(bk, G, A, L);
 }
 
-template <class T, class C, class M, int ORD, int EDGE>
+template <class T, class C, class M, int ORD>
 static void fvtp_order(const fv3_grid *g, int planes, const FvArgs<T, C, M> &a, hipStream_t st)
 {
     static const char *names[] = {"k_fvtp_flux", "k_fvtp_delp", "k_fvtp_massw", "k_fvtp_adv", "k_fvtp_tracer"};
@@ -856,26 +857,26 @@ static void fvtp_order(const fv3_grid *g, int planes, const FvArgs<T, C, M> &a, 
     dim3 grd((unsigned)((g->n + FTX - 1) / FTX), (unsigned)((g->n + FTY - 1) / FTY), (unsigned)planes);
     if constexpr (ORD == 7) {
         // the positive-definite order exists for the tracer transport only
-        launch_fn<k_fvtp<T, C, M, EPI_TRACER, ORD, EDGE>>(names[EPI_TRACER], grd, dim3(FNT), st, g->geo, a);
+        launch_fn<k_fvtp<T, C, M, EPI_TRACER, ORD>>(names[EPI_TRACER], grd, dim3(FNT), st, g->geo, a);
     } else {
         switch (a.epi) {
-        case EPI_FLUX: launch_fn<k_fvtp<T, C, M, EPI_FLUX, ORD, EDGE>>(names[a.epi], grd, dim3(FNT), st, g->geo, a); break;
-        case EPI_DELP: launch_fn<k_fvtp<T, C, M, EPI_DELP, ORD, EDGE>>(names[a.epi], grd, dim3(FNT), st, g->geo, a); break;
-        case EPI_MASSW: launch_fn<k_fvtp<T, C, M, EPI_MASSW, ORD, EDGE>>(names[a.epi], grd, dim3(FNT), st, g->geo, a); break;
-        case EPI_ADV: launch_fn<k_fvtp<T, C, M, EPI_ADV, ORD, EDGE>>(names[a.epi], grd, dim3(FNT), st, g->geo, a); break;
-        default: launch_fn<k_fvtp<T, C, M, EPI_TRACER, ORD, EDGE>>(names[a.epi], grd, dim3(FNT), st, g->geo, a); break;
+        case EPI_FLUX: launch_fn<k_fvtp<T, C, M, EPI_FLUX, ORD>>(names[a.epi], grd, dim3(FNT), st, g->geo, a); break;
+        case EPI_DELP: launch_fn<k_fvtp<T, C, M, EPI_DELP, ORD>>(names[a.epi], grd, dim3(FNT), st, g->geo, a); break;
+        case EPI_MASSW: launch_fn<k_fvtp<T, C, M, EPI_MASSW, ORD>>(names[a.epi], grd, dim3(FNT), st, g->geo, a); break;
+        case EPI_ADV: launch_fn<k_fvtp<T, C, M, EPI_ADV, ORD>>(names[a.epi], grd, dim3(FNT), st, g->geo, a); break;
+        default: launch_fn<k_fvtp<T, C, M, EPI_TRACER, ORD>>(names[a.epi], grd, dim3(FNT), st, g->geo, a); break;
         }
     }
 }
 
-template <class T, class C, class M, int EDGE>
+template <class T, class C, class M>
 static void fvtp_ord(const fv3_grid *g, int ord, int planes, const FvArgs<T, C, M> &a, hipStream_t st)
 {
     switch (ord) {
-    case 5: fvtp_order<T, C, M, 5, EDGE>(g, planes, a, st); break;
-    case 6: fvtp_order<T, C, M, 6, EDGE>(g, planes, a, st); break;
-    case 7: fvtp_order<T, C, M, 7, EDGE>(g, planes, a, st); break;
-    default: fvtp_order<T, C, M, 8, EDGE>(g, planes, a, st); break;
+    case 5: fvtp_order<T, C, M, 5>(g, planes, a, st); break;
+    case 6: fvtp_order<T, C, M, 6>(g, planes, a, st); break;
+    case 7: fvtp_order<T, C, M, 7>(g, planes, a, st); break;
+    default: fvtp_order<T, C, M, 8>(g, planes, a, st); break;
     }
 }
 
@@ -895,7 +896,7 @@ static void fvtp(const fv3_grid *g, int planes, const FvArgs<T, C, M> &a, hipStr
         b.dxa = g->metf[M_DXA];
         b.dya = g->metf[M_DYA];
     }
-    fvtp_ord<T, C, M, 1>(g, ord, planes, b, st);
+    fvtp_ord<T, C, M>(g, ord, planes, b, st);
 }
 
 // ====================================================================
