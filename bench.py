@@ -67,21 +67,19 @@ HBM_PEAK_GBS = 8000.0
 BYTES_MODEL = {
     # name: (bulk fields, fp64 fields); a field both read and written counts twice
     "k_csw": (12, 0),          # fused c_sw: u, v, delp, pt, w in | uc, vc, delpc, ptc, wc, ax, ay out
-    "k_dzc": (2, 2),
-    # column solve in four passes; FP64 scratch columns (elimination coefficients,
-    # new w, new thickness) are fields of the passes that write and read them
-    "k_sim1_c.p1": (3, 3),     # delpc, ptc, wc | delz_c; c', d' out
-    "k_sim1_c.p2": (0, 3),     # c', d' | w new out
-    "k_sim1_c.p3": (3, 3),     # delpc, ptc, wc | w new; thickness, pkc out
-    "k_sim1_c.p4": (0, 2),     # thickness | gz out
-    "k_sim1_3.p1": (3, 3),     # delp, pt, w | delz; c', d' out
-    "k_sim1_3.p2": (0, 3),
-    "k_sim1_3.p3": (4, 3),     # delp, pt, w in, w out | w new; thickness, pfull out
-    "k_sim1_3.p4": (0, 3),     # thickness | phi, delz out
+    # column solves: the half step with the interface-height update (delpc, ptc,
+    # wc, ax, ay | heights; pkc, gz out), the full step with the commits (transported
+    # delp, pt, w, heights in; w, delp, pt out | delz, pfull, phi, heights out)
+    "k_column_c": (5, 3),
+    "k_column_3": (7, 4),
     "k_pgradc": (3, 4), "k_dsw_courant": (8, 0),
     "k_dsw_omke": (6, 0), "k_dsw_update": (13, 0), "k_heights": (0, 2), "k_delz_from_zh": (0, 2),
     "k_nhpgrad": (5, 2),       # delp, u, v in, u, v out | pfull, phi (each interface once)
-    # fused fv_tp_2d: the field, 4 Courant / area-flux arrays, weights, outputs, per epilogue
+    # marching fv_tp_2d: fields in and out, 4 Courant / area-flux arrays, accumulators
+    "k_march_mass": (14, 4),   # delp, pt, w in and out, 4 fluxes, cx, cy (rw) | mfx, mfy (rw)
+    "k_march_wind": (10, 0),   # vorticity, ke, 4 fluxes, u, v (rw)
+    "k_march_height": (5, 1),  # 4 fluxes, heights out | heights in
+    # with edge_ppm, fv_tp_2d on tiles: the field, 4 Courant / area-flux arrays, weights, outputs, per epilogue
     "k_fvtp_delp": (12, 4),    # delp, crx, cry, xfx, yfx, FX, FY, dn, cx, cy (rw) | mfx, mfy (rw)
     "k_fvtp_massw": (10, 0),   # q, 4 fluxes, mx, my, delp old, delp new, q new
     "k_fvtp_flux": (7, 0),     # q, 4 fluxes, FX, FY

@@ -10,7 +10,7 @@ counters are scaled by what they read for the plain copy kernel of the run
 (``k_copy``: each thread reads one element of its source type and writes one
 of its destination type, so its bytes are known exactly).  The output maps
 each launch name used by the library's timing hooks to its mean calibrated
-bytes read and written per launch, with the SHA-256 of the kernel source the
+bytes read and written per launch, with the SHA-256 of the kernel sources the
 counters were taken with (a reader treats the numbers as stale when the
 source has changed).
 """
@@ -26,14 +26,18 @@ import sqlite3
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCE = os.path.join(HERE, "csrc", "kernels.hip")
+CSRC = os.path.join(HERE, "csrc")
+MARCH_KIND = {0: "k_march_mass", 1: "k_march_wind", 2: "k_march_height", 3: "k_march_tracer"}
 FVTP_EPI = {0: "k_fvtp_flux", 1: "k_fvtp_delp", 2: "k_fvtp_massw", 3: "k_fvtp_adv", 4: "k_fvtp_tracer"}
 TSIZE = {"f": 4, "d": 8}
 
 
 def source_sha256() -> str:
-    with open(KERNEL_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    h = hashlib.sha256()
+    for path in sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.hpp"))):
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def launch_name(symbol: str):
@@ -56,6 +60,10 @@ def launch_name(symbol: str):
         # template integers: the epilogue first (then the PPM order and the
         # tile-edge switch)
         return FVTP_EPI.get(ints[0], name)
+    if name == "k_march" and ints:
+        return MARCH_KIND.get(ints[0], name)
+    if name in ("k_column", "k_column_any") and ints:
+        return "k_column_c" if ints[0] == 0 else "k_column_3"
     if name == "k_sim1" and len(ints) >= 2:
         return f"k_sim1_{'c' if ints[1] == 0 else '3'}.p{ints[0]}"
     if name in ("k_csw", "k_nhpgrad", "k_halo_scalar", "k_halo_pair", "k_fill"):
@@ -191,8 +199,9 @@ def trace_main(a):
     lines = [f"# {title}", "", "Command (GPU box, from the repository root; rocprofv3 run from /tmp with TMPDIR=/tmp):",
              "", "    " + command, "",
              "rocprofv3 top_kernels view (durations in microseconds; template arguments: bulk/Courant/weight "
-             "types, then the epilogue of fv_tp_2d (0 flux, 1 delp, 2 mass-weighted, 3 interface heights, "
-             "4 tracer) or the pass and site of k_sim1).", "",
+             "types, then k_march's transport (0 mass, 1 wind, 2 interface heights, 3 tracers), the epilogue of the "
+             "tiled fv_tp_2d (0 flux, 1 delp, 2 mass-weighted, 3 interface heights, 4 tracer) or the site of "
+             "k_column (0 half step, 1 full step)).", "",
              "| kernel | calls | total us | avg us | % |", "|---|---:|---:|---:|---:|"]
     for name, calls, tot, avg, pct in rows:
         if pct < 0.05:
