@@ -196,7 +196,7 @@ def trace_main(a):
         raise FileNotFoundError(f"no rocpd database under {dirname}")
     con = sqlite3.connect(db[0])
     rows = list(con.execute("select name, total_calls, total_duration, average, percentage from top_kernels"))
-    lines = [f"# {title}", "", "Command (GPU box, from the repository root; rocprofv3 run from /tmp with TMPDIR=/tmp):",
+    lines = [f"# {title}", "", "Command (from the repository root, one MI355X):",
              "", "    " + command, "",
              "rocprofv3 top_kernels view (durations in microseconds; template arguments: bulk/Courant/weight "
              "types, then k_march's transport (0 mass, 1 wind, 2 interface heights, 3 tracers), the epilogue of the "
