@@ -54,7 +54,7 @@ DEVI double face_mean(double x0, double x1, double x2, double x3, int m, int n, 
 DEVI double layer_pgf(double dt, double L, double dW, double dE, double zW0, double zW1, double zE0, double zE1,
                       double pW0, double pW1, double pE0, double pE1)
 {
-    return fdiv(dt, L * (dW + dE)) * ffma(zW1 - zE0, pE1 - pW0, (zW0 - zE1) * (pW1 - pE0));
+    return fdiv(dt, L * (dW + dE)) * ffma(zW0 - zE1, pW1 - pE0, (zW1 - zE0) * (pE1 - pW0));
 }
 
 template <class B, bool EI, int NL>
