@@ -32,6 +32,7 @@
 #include "column.hpp"
 #include "flog.hpp"
 #include "launch.hpp"
+#include "tridiag.hpp"
 
 namespace fv3 {
 
@@ -127,12 +128,12 @@ DEVI T &celem(T *base, typename ColOff<SMALL>::T e)
 // humidity; switched at run time), apart so that the plain one keeps its
 // registers.
 //
-// The elimination's recurrence c_k = A_k / (D_k - A_{k-1} c_{k-1}) costs a
-// division per level in a row; its chunk of layers is a fractional linear map
-// of the c above it, so each chunk forms its 2 x 2 matrix (no division), the
-// maps are applied chunk after chunk (one division per chunk), and the levels
-// of all chunks are eliminated at once from there.  The right-hand sides and
-// the back substitution are linear maps and go the same way.
+// The elimination's recurrence costs a division per level in a row; its chunk
+// of layers is a fractional linear map of the ratio above it, so each chunk
+// forms its 2 x 2 matrix (no division), the maps are applied chunk after chunk
+// (one division per chunk), and the levels of all chunks are eliminated at once
+// from there (in the form of tridiag.hpp, without cancellation).  The
+// right-hand sides and the back substitution are linear maps and go the same way.
 template <class B, int SITE, int CL, bool EXT, bool SMALL>
 DEVI void column_body(Bk bk, const Geo &G, const MetD &M, const ColArgs<B> &A, ColLds &L)
 {
@@ -259,6 +260,11 @@ DEVI void column_body(Bk bk, const Geo &G, const MetD &M, const ColArgs<B> &A, C
             l0 = l1;
         }
     }
+    // opaque, so that dpi / g and RDGAS theta are formed again where they are
+    // used and not kept in registers from here to the thicknesses (with that no
+    // plain instance spills; 8 to 18 registers of three of them otherwise)
+#pragma unroll
+    for (int u = 0; u < CL; u++) __asm__ volatile("" : "+v"(dpi[u]), "+v"(th[u]));
     // first and last layers of the chunk for its neighbours
     L.x[0][sl] = (double)dpi[0];
     L.x[1][sl] = h[0];
@@ -322,10 +328,9 @@ DEVI void column_body(Bk bk, const Geo &G, const MetD &M, const ColArgs<B> &A, C
     __syncthreads();
     const double At = ch > 0 ? L.x[0][sl - CW] : 0.0, pt_ = ch > 0 ? L.x[1][sl - CW] : 0.0;
 
-    // ---- diagonal (in cc) and right-hand side (in dd); the chunk's map of
-    // x / y = c: (x, y) -> (m00 x + m01 y, m10 x + m11 y)
+    // ---- right-hand side (in dd); the chunk's map
     double cc[CL], dd[CL];
-    double m00 = 1.0, m10 = 0.0, m01 = 0.0, m11 = 1.0;
+    ElimMap map;
 #pragma unroll
     for (int u = 0; u < CL; u++) {
         const int k = k0 + u;
@@ -341,34 +346,25 @@ DEVI void column_body(Bk bk, const Geo &G, const MetD &M, const ColArgs<B> &A, C
             rhs -= ex * (Ac[u] * (w0 - wb) - A0 * (wa - w0));
         }
         dd[u] = rhs;
-        cc[u] = m + A0 + Ac[u];
-        const double y0 = cc[u] * m10 - A0 * m00, y1 = cc[u] * m11 - A0 * m01;
-        m00 = Ac[u] * m10;
-        m01 = Ac[u] * m11;
-        m10 = y0;
-        m11 = y1;
+        map.layer(A0, Ac[u], m);
     }
-    // c above the chunk
-    double cin = 0.0;
+    // pivot ratio above the chunk (any value at the top, where A0 is 0)
+    double ein = 0.0;
     chain<false>(A.lw, sl, nch, [&]() {
-        if (ch > 0) cin = L.run[1][c];
-        L.run[1][c] = fdiv(m00 * cin + m01, m10 * cin + m11);
+        if (ch > 0) ein = L.run[1][c];
+        L.run[1][c] = map(ein);
     });
     // elimination of the chunk: w_k = dd + cc w_{k+1}, dd = (part of its own
     // rows) + qq (dd above the chunk)
     double qq[CL], din = 0.0;
     {
-        double cp = cin, dp_ = 0.0, qp = 1.0;
+        double dp_ = 0.0, qp = 1.0;
 #pragma unroll
         for (int u = 0; u < CL; u++) {
-            const double A0 = u > 0 ? Ac[u > 0 ? u - 1 : 0] : At;
-            const double rp = fdiv(1.0, cc[u] - A0 * cp);
-            dp_ = (dd[u] + A0 * dp_) * rp;
-            qp = A0 * rp * qp;
-            cp = Ac[u] * rp;
+            const double ck = elim_layer(u > 0 ? Ac[u > 0 ? u - 1 : 0] : At, Ac[u], div_grav((double)dpi[u]), dd[u], ein, dp_, qp);
             dd[u] = dp_;
             qq[u] = qp;
-            cc[u] = k0 + u < nz - 1 ? cp : 0.0;
+            cc[u] = k0 + u < nz - 1 ? ck : 0.0;
         }
     }
     chain<false>(A.lw, sl, nch, [&]() {
