@@ -486,6 +486,38 @@ bool on_device(const fv3_mlp *n)
     int cur = -1;
     return hipGetDevice(&cur) == hipSuccess && cur == n->device;
 }
+
+// The parameter transfers may be called with any device current: the
+// network's for the duration of one, then the caller's again.
+struct OnDevice {
+    int prev = -1;
+    bool ok;
+    explicit OnDevice(const fv3_mlp *n)
+    {
+        ok = hipGetDevice(&prev) == hipSuccess && (prev == n->device || hipSetDevice(n->device) == hipSuccess);
+    }
+    ~OnDevice()
+    {
+        if (prev >= 0) (void)hipSetDevice(prev);
+    }
+};
+
+// parameters (or gradients) of the padded arrays into `flat`
+bool pack(const fv3_mlp *n, int grads, hipStream_t st)
+{
+    Params P = n->P;
+    float *flat = n->flat;
+    void *a[] = {&P, &grads, &flat};
+    return hipLaunchKernel((const void *)k_pack, param_grid(P, false), dim3(256), a, 0, st) == hipSuccess;
+}
+// `flat` into the padded arrays
+bool unpack(fv3_mlp *n, hipStream_t st)
+{
+    Params P = n->P;
+    const float *flat = n->flat;
+    void *a[] = {&P, &flat};
+    return hipLaunchKernel((const void *)k_unpack, param_grid(P, true), dim3(256), a, 0, st) == hipSuccess;
+}
 }  // namespace
 
 extern "C" {
@@ -572,10 +604,11 @@ fv3_status fv3_mlp_set_params(fv3_mlp *n, const float *params)
 {
     if (!n || !params) return mfail(FV3_EINVAL, "NULL argument");
     std::lock_guard<std::mutex> lock(n->mu);
-    if (hipDeviceSynchronize() != hipSuccess ||
-        hipMemcpy(n->flat, params, (size_t)packed_count(n) * 4, hipMemcpyHostToDevice) != hipSuccess)
+    OnDevice dev(n);
+    if (!dev.ok || hipDeviceSynchronize() != hipSuccess ||
+        hipMemcpy(n->flat, params, (size_t)packed_count(n) * 4, hipMemcpyHostToDevice) != hipSuccess ||
+        !unpack(n, nullptr))
         return mfail(FV3_EDEVICE, "parameter upload failed");
-    hipLaunchKernelGGL(k_unpack, param_grid(n->P, true), dim3(256), 0, 0, n->P, (const float *)n->flat);
     n->step = 0;
     return hipDeviceSynchronize() == hipSuccess ? FV3_OK : mfail(FV3_EDEVICE, "sync failed");
 }
@@ -584,9 +617,9 @@ fv3_status fv3_mlp_get_params(const fv3_mlp *n, float *params)
 {
     if (!n || !params) return mfail(FV3_EINVAL, "NULL argument");
     std::lock_guard<std::mutex> lock(n->mu);
-    if (hipDeviceSynchronize() != hipSuccess) return mfail(FV3_EDEVICE, "sync failed");
-    hipLaunchKernelGGL(k_pack, param_grid(n->P, false), dim3(256), 0, 0, n->P, 0, n->flat);
-    if (hipMemcpy(params, n->flat, (size_t)packed_count(n) * 4, hipMemcpyDeviceToHost) != hipSuccess)
+    OnDevice dev(n);
+    if (!dev.ok || hipDeviceSynchronize() != hipSuccess) return mfail(FV3_EDEVICE, "sync failed");
+    if (!pack(n, 0, nullptr) || hipMemcpy(params, n->flat, (size_t)packed_count(n) * 4, hipMemcpyDeviceToHost) != hipSuccess)
         return mfail(FV3_EDEVICE, "parameter download failed");
     return FV3_OK;
 }
@@ -612,8 +645,7 @@ fv3_status fv3_mlp_gradients(fv3_mlp *n, const float *X, const float *T, int row
     int wmax = std::max(n->P.np[0], std::max(n->P.np[1], n->P.np[2]));
     hipLaunchKernelGGL(k_bias_final, dim3((unsigned)((wmax + 63) / 64), 3), dim3(64), 0, st, n->P);
     std::lock_guard<std::mutex> lock(n->mu);
-    hipLaunchKernelGGL(k_pack, param_grid(n->P, false), dim3(256), 0, st, n->P, 1, n->flat);
-    if (hipMemcpyAsync(grads, n->flat, (size_t)packed_count(n) * 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
+    if (!pack(n, 1, st) || hipMemcpyAsync(grads, n->flat, (size_t)packed_count(n) * 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
         return mfail(FV3_EDEVICE, "gradient download failed");
     return FV3_OK;
