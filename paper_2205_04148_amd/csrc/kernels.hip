@@ -1257,8 +1257,10 @@ DEVI void k_dsw_update(KARGS, Geo G, Mets<B> M, const B *ke, const B *VX, const 
 // ====================================================================
 // Halo of the interface heights.  A halo column stands on the surface height
 // the caller's phis holds at that halo point, which is the neighbour cell's
-// where phis is consistent.
-DEVI void k_halo_z(Bk bk, Geo G, const HaloEnt *__restrict__ plan, int count, const double *phis, double *z, int L)
+// where phis is consistent.  delz, where given, is exchanged with them: nothing
+// here reads its halo, the caller may.
+DEVI void k_halo_z(Bk bk, Geo G, const HaloEnt *__restrict__ plan, int count, const double *phis, double *z, int L,
+                   double *delz)
 {
     const int e = (int)(bk.x * blockDim.x + threadIdx.x);
     if (e >= count) return;
@@ -1270,6 +1272,7 @@ DEVI void k_halo_z(Bk bk, Geo G, const HaloEnt *__restrict__ plan, int count, co
         if (zs != zd) v = (v - zs) + zd;
     }
     z[pidx(G, L, h.dt, k) + h.di] = v;
+    if (delz && k < L - 1) delz[pidx(G, L - 1, h.dt, k) + h.di] = delz[pidx(G, L - 1, h.st, k) + h.si];
 }
 
 // Mixed precision: the heights travel as FP32 deviations from a reference
@@ -1716,7 +1719,7 @@ static fv3_status substeps_t(fv3_state *s, const fv3_grid *g, double dt, int n_s
         halo_set<B>(g, FieldSet<B>{{delp, pt, w, nullptr}}, 3, nz, st);
         if (g->planC.count > 0)
             launch_fn<k_halo_z>("k_halo_z", dim3((g->planC.count + 255) / 256, nz + 1), dim3(256), st, G,
-                                (const HaloEnt *)g->planC.d, g->planC.count, phis, zI, nz + 1);
+                                (const HaloEnt *)g->planC.d, g->planC.count, phis, zI, nz + 1, last ? delz : (double *)nullptr);
         STOP(1);
         // c_sw
         {
