@@ -264,13 +264,13 @@ fv3_status fv3_tracer_transport(void *const *q, int nq, fv3_state *s, const fv3_
  * with the interface pressures the mean of those of the two cells sharing
  * the face (the halo of delp is filled first); delp becomes the reference
  * thickness.  The column integral of every field times delp is conserved to
- * rounding.  Computes in FP64 in both precision modes.
+ * rounding.  Computes in FP64 in both precision modes.  A field listed more
+ * than once is remapped once.
  * ak, bk: host arrays of nz + 1 doubles, copied into the launch (the call
  * keeps no pointer); ak[0] must equal the grid's ptop, bk[0] = 0, ak[nz] = 0
- * and bk[nz] = 1 exactly.  Uses the state's workspace.  Asynchronous on
- * `stream`.  Errors: FV3_EINVAL (NULL pointers, non-finite or mismatched end
- * coefficients, nq < 0 or > 64), FV3_ESHAPE (nz > FV3_REMAP_MAX_LEVELS);
- * a column whose reference interfaces do not increase latches FV3_EREMAP,
+ * and bk[nz] = 1 exactly.  Asynchronous on `stream`.  Errors: FV3_EINVAL
+ * (NULL pointers, non-finite or mismatched end coefficients, nq < 0 or > 64),
+ * FV3_ESHAPE (nz > FV3_REMAP_MAX_LEVELS); a column whose reference interfaces do not increase latches FV3_EREMAP,
  * reported by fv3_check_status. */
 fv3_status fv3_remap(fv3_state *s, const fv3_grid *g, const double *ak, const double *bk,
                      void *const *q, int nq, void *stream);

@@ -34,6 +34,7 @@
 // chunks without the staging, 8 chunks of 32 columns, 120 us for the cells
 // (their loads wait for the stores before them); staged, 8 chunks of 32
 // columns, 108 us with four fields a thread, 124 with three, 134 with two.
+#include <algorithm>
 #include <cmath>
 #include <string>
 
@@ -44,7 +45,7 @@ namespace fv3 {
 namespace {
 
 constexpr int RMAX = FV3_REMAP_MAX_LEVELS;
-constexpr int RSLOTS = 8;   // fields per launch, at most
+constexpr int RFIELDS = 8;   // fields per launch, at most
 constexpr int RNF = 4;      // cell fields per thread (one walk of the column serves them all)
 constexpr int RCOL = 16, RCHUNK = 16;   // columns and chunks of layers per block
 enum { RM_CELL = 0, RM_WIND = 1 };
@@ -55,10 +56,9 @@ struct RCoef {
 };
 
 struct RBatch {
-    const void *src[RSLOTS];
-    void *dst[RSLOTS];   // the field itself, or a workspace slot
-    int fp64[RSLOTS];    // 1: the field is FP64, else bulk precision
-    int ratio[RSLOTS];   // 1: remap field / delp, store its integral (delz)
+    void *fld[RFIELDS];   // remapped in place
+    int fp64[RFIELDS];    // 1: the field is FP64, else bulk precision
+    int ratio[RFIELDS];   // 1: remap field / delp, store its integral (delz)
     int nf;
 };
 
@@ -69,13 +69,6 @@ __device__ __forceinline__ void st(void *p, long e, bool fp64, double v)
     if (fp64 || sizeof(B) == 8) ((double *)p)[e] = v;
     else ((float *)p)[e] = (float)v;
 }
-template <class B>
-__device__ __forceinline__ void copy(void *to, const void *from, long e, bool fp64)
-{
-    if (fp64 || sizeof(B) == 8) ((double *)to)[e] = ((const double *)from)[e];
-    else ((float *)to)[e] = ((const float *)from)[e];
-}
-
 // monotonised slope from the raw slope and the two one-sided differences
 __device__ __forceinline__ double mono(double raw, double lo, double hi)
 {
@@ -182,9 +175,9 @@ __global__ __launch_bounds__(256) void k_remap(Geo G, double ptop, RCoef C, RBat
             f64[q] = sizeof(B) == 8 || F.fp64[f0 + q] != 0;
             at += (f64[q] ? nz : (nz + 1) / 2) * RCOL;
             if (!in) continue;
-            if (ratio[q]) stage<double>(src[q], F.src[f0 + q], delp, c0, lev, m0, m1, c);
-            else if (f64[q]) stage<double>(src[q], F.src[f0 + q], (const B *)nullptr, c0, lev, m0, m1, c);
-            else stage<float>((float *)src[q], F.src[f0 + q], (const B *)nullptr, c0, lev, m0, m1, c);
+            if (ratio[q]) stage<double>(src[q], F.fld[f0 + q], delp, c0, lev, m0, m1, c);
+            else if (f64[q]) stage<double>(src[q], F.fld[f0 + q], (const B *)nullptr, c0, lev, m0, m1, c);
+            else stage<float>((float *)src[q], F.fld[f0 + q], (const B *)nullptr, c0, lev, m0, m1, c);
         }
     }
     interfaces(pe, nz, ptop, c, ch, in, thick);
@@ -284,7 +277,7 @@ __global__ __launch_bounds__(256) void k_remap(Geo G, double ptop, RCoef C, RBat
 #pragma unroll
                     for (int q = 0; q < NF; q++) {
                         if (q < nfg)
-                            st<B>(F.dst[f0 + q], c0 + (long)m * lev, f64[q], ratio[q] ? acc[q] : acc[q] * rdm);
+                            st<B>(F.fld[f0 + q], c0 + (long)m * lev, f64[q], ratio[q] ? acc[q] : acc[q] * rdm);
                         acc[q] = 0.0;
                     }
                     top2 = bot2;
@@ -330,19 +323,6 @@ __global__ __launch_bounds__(256) void k_remap(Geo G, double ptop, RCoef C, RBat
         }
     }
     if (bad) atomicOr(flags + 2, 1);
-}
-
-// copy the remapped interior points of a batch back into the cell fields
-template <class B>
-__global__ __launch_bounds__(256) void k_remap_back(Geo G, RBatch F)
-{
-    const int n = G.n, col = (int)blockIdx.x * 256 + (int)threadIdx.x, j = col / n, i = col - j * n;
-    if (j >= n) return;
-    const int f = (int)blockIdx.y % F.nf, t = (int)blockIdx.y / F.nf;
-    for (int k = 0; k < G.nz; k++) {
-        const long e = G.off0 + ((long)t * G.nz + k) * G.lev + (long)j * G.pitch + i;
-        copy<B>((void *)F.src[f], F.dst[f], e, F.fp64[f] != 0);
-    }
 }
 
 // delp of every column becomes the reference thickness
@@ -393,12 +373,6 @@ fv3_status remap(fv3_state *s, const fv3_grid *g, const double *ak, const double
         C.ak[K] = ak[K];
         C.bk[K] = bk[K];
     }
-    // workspace slots of one field each (FP64-sized, 256-byte aligned)
-    const size_t slot = ((size_t)alloc_elems(g, nz) * 8 + 255) / 256 * 256;
-    const int nslots = (int)std::min<size_t>(RSLOTS, s->workspace_bytes / slot);
-    if (nslots < 2) return FV3_ESHAPE;
-    char *ws = (char *)s->workspace;
-
     fv3_status hs = run_halo_cells(g, &s->delp, 1, nz, 0, st);   // face winds read the neighbour cells
     if (hs != FV3_OK) return hs;
     const dim3 blk(256);
@@ -418,38 +392,34 @@ fv3_status remap(fv3_state *s, const fv3_grid *g, const double *ak, const double
     // winds at faces
     {
         RBatch B{};
-        B.src[0] = s->u;
-        B.src[1] = s->v;
-        B.dst[0] = s->u;
-        B.dst[1] = s->v;
+        B.fld[0] = s->u;
+        B.fld[1] = s->v;
         B.nf = 2;
         timed("k_remap_winds", k_remap<T, RM_WIND, 1>, lds(B, 1), grid((long)n * (n + 1), g->T * 2), blk, st, G, ptop, C, B,
               (const T *)s->delp, g->flags);
     }
-    // cell fields: pt, w, delz (as delz/delp), tracers, in batches of nslots
+    // cell fields: pt, w, delz (as delz/delp), tracers.  A field listed again
+    // is remapped once.  delp, if it is listed as a tracer, comes last and
+    // alone: the blocks of every group of fields read it.
     std::vector<void *> fs = {s->pt, s->w, s->delz};
-    for (int m = 0; m < nq; m++) fs.push_back(q[m]);
-    for (size_t b = 0; b < fs.size(); b += (size_t)nslots) {
+    bool own = false;
+    for (int m = 0; m < nq; m++) {
+        if (q[m] == s->delp) own = true;
+        else if (std::find(fs.begin(), fs.end(), q[m]) == fs.end()) fs.push_back(q[m]);
+    }
+    auto cells = [&](void *const *f, int nf) {
         RBatch B{};
-        B.nf = (int)std::min<size_t>((size_t)nslots, fs.size() - b);
-        for (int f = 0; f < B.nf; f++) {
-            B.src[f] = fs[b + f];
-            B.fp64[f] = fs[b + f] == (const void *)s->delz;
-            B.ratio[f] = B.fp64[f];
+        B.nf = nf;
+        for (int k = 0; k < nf; k++) {
+            B.fld[k] = f[k];
+            B.fp64[k] = B.ratio[k] = f[k] == (const void *)s->delz;
         }
-        // a field listed twice in a batch is remapped once: its blocks read it
-        // in both groups, so none of them may write it
-        bool twice = false;
-        for (int f = 0; f < B.nf; f++)
-            for (int h = 0; h < f; h++) twice |= B.src[f] == B.src[h];
-        for (int f = 0; f < B.nf; f++) B.dst[f] = twice ? ws + (size_t)f * slot : fs[b + f];
-        const int groups = (B.nf + NF - 1) / NF;
+        const int groups = (nf + NF - 1) / NF;
         timed("k_remap_cells", k_remap<T, RM_CELL, NF>, lds(B, NF), grid((long)n * n, g->T * groups), blk, st, G, ptop, C, B,
               (const T *)s->delp, g->flags);
-        if (twice)
-            timed("k_remap_back", k_remap_back<T>, 0, dim3((unsigned)(((long)n * n + 255) / 256), (unsigned)(g->T * B.nf)), blk,
-                  st, G, B);
-    }
+    };
+    for (size_t b = 0; b < fs.size(); b += RFIELDS) cells(&fs[b], (int)std::min<size_t>(RFIELDS, fs.size() - b));
+    if (own) cells(&s->delp, 1);
     timed("k_remap_delp", k_remap_delp<T>, 0, grid((long)n * n, g->T), blk, st, G, ptop, C, (T *)s->delp);
     return hipGetLastError() == hipSuccess ? FV3_OK : FV3_EDEVICE;
 }
