@@ -270,8 +270,9 @@ fv3_status fv3_tracer_transport(void *const *q, int nq, fv3_state *s, const fv3_
  * keeps no pointer); ak[0] must equal the grid's ptop, bk[0] = 0, ak[nz] = 0
  * and bk[nz] = 1 exactly.  Asynchronous on `stream`.  Errors: FV3_EINVAL
  * (NULL pointers, non-finite or mismatched end coefficients, nq < 0 or > 64),
- * FV3_ESHAPE (nz > FV3_REMAP_MAX_LEVELS); a column whose reference interfaces do not increase latches FV3_EREMAP,
- * reported by fv3_check_status. */
+ * FV3_ESHAPE (nz > FV3_REMAP_MAX_LEVELS); a column whose reference
+ * interfaces do not increase latches FV3_EREMAP, reported by
+ * fv3_check_status. */
 fv3_status fv3_remap(fv3_state *s, const fv3_grid *g, const double *ak, const double *bk,
                      void *const *q, int nq, void *stream);
 

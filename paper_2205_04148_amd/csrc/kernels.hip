@@ -1986,50 +1986,68 @@ static fv3_status tracer_t(void *const *q, int nq, fv3_state *s, const fv3_grid 
              (const double *)s->mfx, (const double *)s->mfy, W.crx, W.cry, W.xfx, W.yfx, eppm ? W.mxs : (double *)nullptr,
              eppm ? W.mys : (double *)nullptr);
     if (!eppm) {
-        // up to MARCH_TRACERS fields at a time through all sub-cycles, each
-        // sub-cycle from the fields to scratch or back
+        // up to MARCH_TRACERS fields at a time, each sub-cycle from the fields to
+        // scratch or back
         B *scr[MARCH_TRACERS] = {W.qo, W.dn, W.pn, W.wn};
         B *efx[MARCH_TRACERS] = {W.delpc, W.wc, W.ut, W.VX}, *efy[MARCH_TRACERS] = {W.ptc, W.ke, W.vt, W.VY};
-        for (int m0 = 0, nf = 0; m0 < nq; m0 += nf) {
-            MarchArgs<B> a{};
-            a.crx = W.crx; a.cry = W.cry; a.xfx = W.xfx; a.yfx = W.yfx; a.area = M.m[M_AREA];
-            a.mx = s->mfx; a.my = s->mfy; a.area64 = Md.m[M_AREA]; a.rs = rs;
-            FieldSet<B> src{}, dst{};
-            for (nf = 0; nf < (sizeof(B) == 4 ? MARCH_TRACERS : 3) && m0 + nf < nq; nf++) {
-                // a field given twice is transported twice, one after the other
-                bool again = false;
-                for (int f = 0; f < nf; f++) again |= src.p[f] == (B *)q[m0 + nf];
-                if (again) break;
-                src.p[nf] = (B *)q[m0 + nf];
-                dst.p[nf] = scr[nf];
-                if (efix) {
-                    a.FX[nf] = efx[nf];
-                    a.FY[nf] = efy[nf];
+        MarchArgs<B> a{};
+        a.crx = W.crx; a.cry = W.cry; a.xfx = W.xfx; a.yfx = W.yfx; a.area = M.m[M_AREA];
+        a.mx = s->mfx; a.my = s->mfy; a.area64 = Md.m[M_AREA]; a.rs = rs;
+        struct Group {
+            FieldSet<B> src, dst;
+            int nf;
+        } gs[64];   // as many as there are tracers, at most
+        int ng = 0;
+        bool repeated = false;
+        for (int m = 0; m < nq; m++) {
+            for (int f = 0; f < m; f++) repeated |= q[f] == q[m];
+            // a field given twice is transported twice, one after the other
+            bool again = false;
+            if (ng > 0)
+                for (int f = 0; f < gs[ng - 1].nf; f++) again |= gs[ng - 1].src.p[f] == (B *)q[m];
+            if (ng == 0 || again || gs[ng - 1].nf == (sizeof(B) == 4 ? MARCH_TRACERS : 3)) gs[ng++] = Group{};
+            Group &t = gs[ng - 1];
+            t.src.p[t.nf] = (B *)q[m];
+            t.dst.p[t.nf] = scr[t.nf];
+            t.nf++;
+        }
+        auto subcycle = [&](Group &t, int itr) {
+            halo_set<B>(g, t.src, t.nf, nz, st);
+            for (int f = 0; f < t.nf; f++) {
+                a.q[f] = t.src.p[f];
+                a.out[f] = t.dst.p[f];
+                a.FX[f] = efix ? efx[f] : nullptr;
+                a.FY[f] = efix ? efy[f] : nullptr;
+            }
+            a.dp1 = itr == 0 ? s->dp0 : itr % 2 ? W.dp1 : W.dp2;
+            a.dp2 = itr + 1 < nsplt || efix ? (itr % 2 ? W.dp2 : W.dp1) : nullptr;
+            march_tracer(g, t.nf, a, st);
+            if (efix)
+                for (int f = 0; f < t.nf; f++)
+                    launch_fn<k_edgefix_q<B>>("k_edgefix_q", dim3((g->edge_count + 255) / 256, nz), dim3(256), st, G,
+                                              (const EdgeCell *)g->edge_cells, g->edge_count,
+                                              (const B *)M.m[M_AREA], (const B *)a.FX[f], (const B *)a.FY[f],
+                                              (const double *)a.dp2, t.dst.p[f]);
+            std::swap(t.src, t.dst);
+        };
+        auto back = [&](Group &t) {   // from scratch into the fields
+            launch2d_s(k_copy_back<B>, (Shape{128, 2}), 0, n - 1, 0, n - 1, P * t.nf, st, G, P, t.src, t.dst);
+            std::swap(t.src, t.dst);
+        };
+        if (!repeated) {
+            for (int k = 0; k < ng; k++) {
+                for (int itr = 0; itr < nsplt; itr++) subcycle(gs[k], itr);
+                if (nsplt % 2) back(gs[k]);
+                halo_set<B>(g, gs[k].src, gs[k].nf, nz, st);   // leave consistent halos
+            }
+        } else {
+            // every sub-cycle of a repeated field follows all of the one before
+            for (int itr = 0; itr < nsplt; itr++)
+                for (int k = 0; k < ng; k++) {
+                    subcycle(gs[k], itr);
+                    back(gs[k]);
                 }
-            }
-            a.dp1 = s->dp0;
-            for (int itr = 0; itr < nsplt; itr++) {
-                halo_set<B>(g, src, nf, nz, st);
-                for (int f = 0; f < nf; f++) {
-                    a.q[f] = src.p[f];
-                    a.out[f] = dst.p[f];
-                }
-                a.dp2 = itr + 1 < nsplt || efix ? (itr % 2 ? W.dp2 : W.dp1) : nullptr;
-                march_tracer(g, nf, a, st);
-                if (efix)
-                    for (int f = 0; f < nf; f++)
-                        launch_fn<k_edgefix_q<B>>("k_edgefix_q", dim3((g->edge_count + 255) / 256, nz), dim3(256), st, G,
-                                                  (const EdgeCell *)g->edge_cells, g->edge_count,
-                                                  (const B *)M.m[M_AREA], (const B *)a.FX[f], (const B *)a.FY[f],
-                                                  (const double *)a.dp2, dst.p[f]);
-                a.dp1 = a.dp2;
-                std::swap(src, dst);
-            }
-            if (nsplt % 2) {
-                launch2d_s(k_copy_back<B>, (Shape{128, 2}), 0, n - 1, 0, n - 1, P * nf, st, G, P, src, dst);
-                std::swap(src, dst);
-            }
-            halo_set<B>(g, src, nf, nz, st);   // leave consistent halos
+            for (int k = 0; k < ng; k++) halo_set<B>(g, gs[k].src, gs[k].nf, nz, st);
         }
         return hipGetLastError() == hipSuccess ? FV3_OK : FV3_EDEVICE;
     }
