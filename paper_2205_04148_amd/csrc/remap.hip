@@ -13,17 +13,18 @@
 // mean interfaces of the two cells that share the face; delp becomes the
 // reference thickness.
 //
-// GPU mapping: a block takes RCOL = 16 columns, its 256 threads 16 chunks of
-// target layers each.  The block sums the columns' interface pressures into
-// LDS (in layer order) and stages the source columns of up to RNF fields
-// there; then every thread finds the source layer that its first target layer
-// starts in by bisection, rebuilds the interpolation state from the two layers
-// above and walks on: per source layer it finishes the target layers that end
-// in it, so that the threads of a wavefront advance together.  A window of
-// means and thicknesses and the interface value below the current layer (which
-// becomes the one above the next) stay in registers.  As every read of the
-// walk is from LDS, results go straight into the fields.  All arithmetic is
-// FP64.
+// GPU mapping: a block's 256 threads take 16 to 256 columns and cut them into
+// 16 to 1 chunks of target layers, one thread per (column, chunk).  The block
+// sums the columns' interface pressures into LDS (in layer order) and stages
+// the source columns of up to RNF fields there; then every thread finds the
+// source layer that its first target layer starts in by bisection, rebuilds the
+// interpolation state from the two layers above and walks on: per source layer
+// it finishes the target layers that end in it, so that the threads of a
+// wavefront advance together.  A window of means and thicknesses and the
+// interface value below the current layer (which becomes the one above the
+// next) stay in registers.  As every read of the walk is from LDS, results go
+// straight into the fields.  All arithmetic is FP64; no value depends on the
+// split.
 //
 // What bounds it is the instructions of the walk: some 240 a source layer and
 // 50 more a field, with about ten divisions in a serial chain, and two or
@@ -31,7 +32,7 @@
 // / both winds / whole remap: C48 x 79 mixed 496 / 534 / 1030 us as one thread
 // per column with results in a workspace and copied back, 87 / 52 / 148 now;
 // C192 x 79, eight fields, 3.78 -> 1.98 ms (FP64 4.14 -> 2.00).  On the way:
-// chunks without the staging, 8 chunks of 32 columns, 120 us for the cells
+// 16 chunks without the staging, 8 chunks of 32 columns, 120 us for the cells
 // (their loads wait for the stores before them); staged, 8 chunks of 32
 // columns, 108 us with four fields a thread, 124 with three, 134 with two.
 #include <algorithm>
@@ -47,7 +48,8 @@ namespace {
 constexpr int RMAX = FV3_REMAP_MAX_LEVELS;
 constexpr int RFIELDS = 8;   // fields per launch, at most
 constexpr int RNF = 4;      // cell fields per thread (one walk of the column serves them all)
-constexpr int RCOL = 16, RCHUNK = 16;   // columns and chunks of layers per block
+constexpr int RNT = 256;    // threads per block: columns x chunks of layers
+constexpr int RB = 8;       // loads of a thread in flight while it fills LDS
 enum { RM_CELL = 0, RM_WIND = 1 };
 
 // reference coordinate, passed by value in the kernel arguments
@@ -76,53 +78,65 @@ __device__ __forceinline__ double mono(double raw, double lo, double hi)
     return copysign(fmin(fabs(raw), 2.0 * fmin(fabs(lo), fabs(hi))), raw);
 }
 
-// interface pressures of the block's columns (thread (c, ch): layers of chunk
-// ch of column c), summed in layer order: pe[k * RCOL + c], k = 0 .. nz
+// Split of a block: CW = 2^lw columns, thread (c, ch) works on chunk ch of
+// column c; chunks of cs layers.
+struct Split {
+    int cw, c, ch, cs;
+    __device__ __forceinline__ Split(int lw, int nz)
+        : cw(1 << lw), c((int)threadIdx.x & (cw - 1)), ch((int)threadIdx.x >> lw),
+          cs((nz + (RNT >> lw) - 1) / (RNT >> lw)) {}
+};
+
+// interface pressures of the block's columns, summed in layer order:
+// pe[k * cw + c], k = 0 .. nz
 template <class H>
-__device__ __forceinline__ void interfaces(double *pe, int nz, double ptop, int c, int ch, bool in, H thick)
+__device__ __forceinline__ void interfaces(double *pe, int nz, double ptop, const Split &S, bool in, H thick)
 {
-    const int cs = (nz + RCHUNK - 1) / RCHUNK, k1 = min(nz, (ch + 1) * cs);
-    constexpr int CMAX = (RMAX + RCHUNK - 1) / RCHUNK;
-    double h[CMAX];
+    const int k1 = min(nz, (S.ch + 1) * S.cs);
+    for (int k0 = S.ch * S.cs; k0 < k1; k0 += RB) {
+        double h[RB];
 #pragma unroll
-    for (int q = 0; q < CMAX; q++) h[q] = in && ch * cs + q < k1 ? thick(ch * cs + q) : 1.0;   // all loads in flight
+        for (int q = 0; q < RB; q++) h[q] = in && k0 + q < k1 ? thick(k0 + q) : 1.0;   // all loads in flight
 #pragma unroll
-    for (int q = 0; q < CMAX; q++)
-        if (ch * cs + q < k1) pe[(ch * cs + q + 1) * RCOL + c] = h[q];
+        for (int q = 0; q < RB; q++)
+            if (k0 + q < k1) pe[(k0 + q + 1) * S.cw + S.c] = h[q];
+    }
     __syncthreads();
-    if (ch == 0) {
+    if (S.ch == 0) {
         double p = ptop;
-        pe[c] = p;
+        pe[S.c] = p;
         for (int k = 1; k <= nz; k += 8) {
             double h[8];
 #pragma unroll
-            for (int q = 0; q < 8; q++) h[q] = pe[min(k + q, nz) * RCOL + c];
+            for (int q = 0; q < 8; q++) h[q] = pe[min(k + q, nz) * S.cw + S.c];
 #pragma unroll
             for (int q = 0; q < 8; q++) {
                 p += h[q];
-                if (k + q <= nz) pe[(k + q) * RCOL + c] = p;
+                if (k + q <= nz) pe[(k + q) * S.cw + S.c] = p;
             }
         }
     }
     __syncthreads();
 }
 
-// layers m0 .. m1 - 1 of a column to LDS (divided by delp, if given)
+// the thread's layers of a column to LDS (divided by delp, if given)
 template <class T, class B>
-__device__ __forceinline__ void stage(T *to, const void *from, const B *delp, long c0, long lev, int m0, int m1, int c)
+__device__ __forceinline__ void stage(T *to, const void *from, const B *delp, long c0, long lev, int nz, const Split &S)
 {
-    constexpr int CMAX = (RMAX + RCHUNK - 1) / RCHUNK;
-    T v[CMAX];
-    B h[CMAX];
+    const int k1 = min(nz, (S.ch + 1) * S.cs);
+    for (int k0 = S.ch * S.cs; k0 < k1; k0 += RB) {
+        T v[RB];
+        B h[RB];
 #pragma unroll
-    for (int q = 0; q < CMAX; q++) {
-        const long e = c0 + (long)(m0 + q) * lev;
-        v[q] = m0 + q < m1 ? ((const T *)from)[e] : (T)0;
-        h[q] = delp && m0 + q < m1 ? delp[e] : (B)1;
+        for (int q = 0; q < RB; q++) {
+            const long e = c0 + (long)(k0 + q) * lev;
+            v[q] = k0 + q < k1 ? ((const T *)from)[e] : (T)0;
+            h[q] = delp && k0 + q < k1 ? delp[e] : (B)1;
+        }
+#pragma unroll
+        for (int q = 0; q < RB; q++)
+            if (k0 + q < k1) to[(k0 + q) * S.cw + S.c] = delp ? (T)(v[q] * fdiv(1.0, (double)h[q])) : v[q];
     }
-#pragma unroll
-    for (int q = 0; q < CMAX; q++)
-        if (m0 + q < m1) to[(m0 + q) * RCOL + c] = delp ? (T)(v[q] * fdiv(1.0, (double)h[q])) : v[q];
 }
 
 // Remap up to NF fields of a chunk of target layers of one column, cells
@@ -132,12 +146,14 @@ __device__ __forceinline__ void stage(T *to, const void *from, const B *delp, lo
 // the limited slope of layer s + 1, needed by the interface below layer s, is
 // kept for the interface below layer s + 1.
 template <class B, int MODE, int NF>
-__global__ __launch_bounds__(256) void k_remap(Geo G, double ptop, RCoef C, RBatch F, const B *delp, int *flags)
+__global__ __launch_bounds__(256) void k_remap(Geo G, int lw, double ptop, RCoef C, RBatch F, const B *delp, int *flags)
 {
     extern __shared__ double lds[];
-    const int n = G.n, nz = G.nz, c = (int)threadIdx.x % RCOL, ch = (int)threadIdx.x / RCOL;
+    const int n = G.n, nz = G.nz;
+    const Split S(lw, nz);
+    const int c = S.c, CW = S.cw;
     // interface pressures, coefficients, source fields
-    double *pe = lds, *ab = pe + (nz + 1) * RCOL, *fld = ab + 2 * (nz + 1);
+    double *pe = lds, *ab = pe + (nz + 1) * CW, *fld = ab + 2 * (nz + 1);
     if ((int)threadIdx.x <= nz) {
         // the coefficients by lane from LDS: the kernel arguments lie in host
         // memory, and the walk would wait for one at every target layer
@@ -149,7 +165,7 @@ __global__ __launch_bounds__(256) void k_remap(Geo G, double ptop, RCoef C, RBat
     const int nfg = MODE == RM_WIND ? 1 : min(NF, F.nf - f0);
     const bool vface = MODE == RM_WIND && f0 == 1;
     const int ni = vface ? n + 1 : n, nj = MODE == RM_WIND && !vface ? n + 1 : n;
-    const int col = (int)blockIdx.x * RCOL + c, j = col / ni, i = col - j * ni;
+    const int col = (int)blockIdx.x * CW + c, j = col / ni, i = col - j * ni;
     const bool in = j < nj;
     const long lev = G.lev;
     const long c0 = G.off0 + (long)t * nz * lev + (long)j * G.pitch + i;
@@ -159,7 +175,7 @@ __global__ __launch_bounds__(256) void k_remap(Geo G, double ptop, RCoef C, RBat
         if (MODE == RM_CELL) return (double)delp[c0 + o];
         return 0.5 * ((double)delp[c0 + o] + (double)delp[c1 + o]);
     };
-    const int cs = (nz + RCHUNK - 1) / RCHUNK, m0 = ch * cs, m1 = min(nz, m0 + cs);
+    const int m0 = S.ch * S.cs, m1 = min(nz, m0 + S.cs);
     // the source columns: every read of the walk is then from LDS, and its
     // stores, straight into the fields, are never waited for
     double *src[NF];
@@ -173,15 +189,15 @@ __global__ __launch_bounds__(256) void k_remap(Geo G, double ptop, RCoef C, RBat
             if (q >= nfg) continue;
             ratio[q] = F.ratio[f0 + q] != 0;
             f64[q] = sizeof(B) == 8 || F.fp64[f0 + q] != 0;
-            at += (f64[q] ? nz : (nz + 1) / 2) * RCOL;
+            at += (f64[q] ? nz : (nz + 1) / 2) * CW;
             if (!in) continue;
-            if (ratio[q]) stage<double>(src[q], F.fld[f0 + q], delp, c0, lev, m0, m1, c);
-            else if (f64[q]) stage<double>(src[q], F.fld[f0 + q], (const B *)nullptr, c0, lev, m0, m1, c);
-            else stage<float>((float *)src[q], F.fld[f0 + q], (const B *)nullptr, c0, lev, m0, m1, c);
+            if (ratio[q]) stage<double>(src[q], F.fld[f0 + q], delp, c0, lev, nz, S);
+            else if (f64[q]) stage<double>(src[q], F.fld[f0 + q], (const B *)nullptr, c0, lev, nz, S);
+            else stage<float>((float *)src[q], F.fld[f0 + q], (const B *)nullptr, c0, lev, nz, S);
         }
     }
-    interfaces(pe, nz, ptop, c, ch, in, thick);
-    const double ps = pe[nz * RCOL + c];
+    interfaces(pe, nz, ptop, S, in, thick);
+    const double ps = pe[nz * CW + c];
     const bool mine = in && m0 < m1;
     auto target = [&](int K) -> double {   // both coordinates end on ps exactly
         return K == 0 ? ptop : K < nz ? ab[K] + ab[nz + 1 + K] * ps : ps;
@@ -193,7 +209,7 @@ __global__ __launch_bounds__(256) void k_remap(Geo G, double ptop, RCoef C, RBat
         int lo = 0, hi = nz - 1;
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
-            if (pe[(mid + 1) * RCOL + c] > top2) hi = mid;
+            if (pe[(mid + 1) * CW + c] > top2) hi = mid;
             else lo = mid + 1;
         }
         // The state of the walk at layer s: means of layers s, s + 1, s + 2
@@ -205,10 +221,10 @@ __global__ __launch_bounds__(256) void k_remap(Geo G, double ptop, RCoef C, RBat
         double a2[NF], a3[NF], a4[NF], sl3[NF], eR[NF], l[NF], r[NF], c6[NF], acc[NF];
         auto layer = [&](int k, double *a, double &d) {
             if (k >= nz) return;
-            d = pe[(k + 1) * RCOL + c] - pe[k * RCOL + c];
+            d = pe[(k + 1) * CW + c] - pe[k * CW + c];
 #pragma unroll
             for (int q = 0; q < NF; q++) {
-                a[q] = f64[q] ? src[q][k * RCOL + c] : (double)((const float *)src[q])[k * RCOL + c];
+                a[q] = f64[q] ? src[q][k * CW + c] : (double)((const float *)src[q])[k * CW + c];
             }
         };
         // limited slope of layer s + 1
@@ -242,7 +258,7 @@ __global__ __launch_bounds__(256) void k_remap(Geo G, double ptop, RCoef C, RBat
         };
 #pragma unroll
         for (int q = 0; q < NF; q++) a2[q] = a3[q] = a4[q] = acc[q] = 0.0;
-        if (s > 0) d1 = pe[(s) * RCOL + c] - pe[(s - 1) * RCOL + c];
+        if (s > 0) d1 = pe[(s) * CW + c] - pe[(s - 1) * CW + c];
         layer(s, a2, d2);
         layer(s + 1, a3, d3);
         layer(s + 2, a4, d4);
@@ -259,7 +275,7 @@ __global__ __launch_bounds__(256) void k_remap(Geo G, double ptop, RCoef C, RBat
         }
         int m = m0;
         for (;;) {
-            const double top1 = pe[(s) * RCOL + c], bot1 = pe[(s + 1) * RCOL + c];
+            const double top1 = pe[(s) * CW + c], bot1 = pe[(s + 1) * CW + c];
             if (s >= lo) {
                 const double rds = fdiv(1.0, bot1 - top1);
                 // integral over [x1, x2] of l + x (r - l + c6 (1 - x)), times the thickness
@@ -327,23 +343,26 @@ __global__ __launch_bounds__(256) void k_remap(Geo G, double ptop, RCoef C, RBat
 
 // delp of every column becomes the reference thickness
 template <class B>
-__global__ __launch_bounds__(256) void k_remap_delp(Geo G, double ptop, RCoef C, B *delp)
+__global__ __launch_bounds__(256) void k_remap_delp(Geo G, int lw, double ptop, RCoef C, B *delp)
 {
-    __shared__ double pe[(RMAX + 1) * RCOL], ab[2][RMAX + 1];
-    const int n = G.n, nz = G.nz, c = (int)threadIdx.x % RCOL, ch = (int)threadIdx.x / RCOL;
+    extern __shared__ double pe[];
+    __shared__ double ab[2][RMAX + 1];
+    const int n = G.n, nz = G.nz;
+    const Split S(lw, nz);
+    const int c = S.c, CW = S.cw;
     if ((int)threadIdx.x <= nz) {
         ab[0][threadIdx.x] = C.ak[threadIdx.x];
         ab[1][threadIdx.x] = C.bk[threadIdx.x];
     }
-    const int col = (int)blockIdx.x * RCOL + c, j = col / n, i = col - j * n;
+    const int col = (int)blockIdx.x * CW + c, j = col / n, i = col - j * n;
     const bool in = j < n;
     const long c0 = G.off0 + (long)blockIdx.y * nz * G.lev + (long)j * G.pitch + i;
-    interfaces(pe, nz, ptop, c, ch, in, [&](int k) -> double { return (double)delp[c0 + (long)k * G.lev]; });
+    interfaces(pe, nz, ptop, S, in, [&](int k) -> double { return (double)delp[c0 + (long)k * G.lev]; });
     if (!in) return;
-    const double ps = pe[nz * RCOL + c];
-    const int cs = (nz + RCHUNK - 1) / RCHUNK, k1 = min(nz, (ch + 1) * cs);
-    double top = ch == 0 ? ptop : ab[0][min(ch * cs, nz)] + ab[1][min(ch * cs, nz)] * ps;
-    for (int k = ch * cs; k < k1; k++) {
+    const double ps = pe[nz * CW + c];
+    const int k0 = S.ch * S.cs, k1 = min(nz, k0 + S.cs);
+    double top = k0 == 0 ? ptop : ab[0][min(k0, nz)] + ab[1][min(k0, nz)] * ps;
+    for (int k = k0; k < k1; k++) {
         const double bot = ab[0][k + 1] + ab[1][k + 1] * ps;
         delp[c0 + (long)k * G.lev] = (B)(bot - top);
         top = bot;
@@ -358,6 +377,22 @@ void timed(const char *name, K kern, size_t lds, dim3 grd, dim3 blk, hipStream_t
     if (tm) timing_begin(name, s, r);
     hipLaunchKernelGGL(kern, grd, blk, lds, s, args...);
     if (tm) timing_end(s, r);
+}
+
+// log2 of the columns per block: chunks of about five layers (each rebuilds the
+// state of the two layers above it, and the shorter they are the fewer columns
+// share the block's serial sums), 16 chunks at most, and no fewer than 128
+// blocks where 16 columns a block give as many.  Whole remap with four tracers,
+// mixed, us, 16 chunks / this rule (one thread per column, before the chunks):
+// 512 x 512 x 7 periodic 449 / 137 (198), C384 x 20 2439 / 1133 (1788), C96 x 5
+// 107 / 43 (92), C192 x 40 928 / 648 (1118); the same split at C192 x 79 (1395)
+// and C48 x 79 (131), where chunks of ten layers take 1579 and 151.
+int remap_shift(int nz, long columns)
+{
+    int lw = 8;
+    while (lw > 4 && (RNT >> lw) * 5 < nz) lw--;
+    while (lw > 4 && (columns >> lw) < 128) lw--;
+    return lw;
 }
 
 template <class T>
@@ -376,26 +411,26 @@ fv3_status remap(fv3_state *s, const fv3_grid *g, const double *ak, const double
     fv3_status hs = run_halo_cells(g, &s->delp, 1, nz, 0, st);   // face winds read the neighbour cells
     if (hs != FV3_OK) return hs;
     const dim3 blk(256);
-    // interface pressures, coefficients; staged fields of a group
-    const size_t base = ((size_t)(nz + 1) * (RCOL + 2)) * 8;
-    auto lds = [&](const RBatch &B, int NF) {
+    // bytes of LDS of a block: interface pressures, coefficients; staged fields of a group
+    auto lds = [&](const RBatch &B, int NF, int lw) {
         size_t most = 0;
         for (int f0 = 0; f0 < B.nf; f0 += NF) {
             size_t e = 0;
             for (int f = f0; f < std::min(f0 + NF, B.nf); f++)
-                e += (size_t)(sizeof(T) == 8 || B.fp64[f] ? nz : (nz + 1) / 2) * RCOL * 8;
+                e += (size_t)(sizeof(T) == 8 || B.fp64[f] ? nz : (nz + 1) / 2) * 8 << lw;
             most = std::max(most, e);
         }
-        return base + most;
+        return (((size_t)(nz + 1) * 8) << lw) + (size_t)(nz + 1) * 16 + most;
     };
-    auto grid = [&](long cols, int planes) { return dim3((unsigned)((cols + RCOL - 1) / RCOL), (unsigned)planes); };
+    auto grid = [&](long cols, int planes, int lw) { return dim3((unsigned)((cols + (1 << lw) - 1) >> lw), (unsigned)planes); };
+    const int lw = remap_shift(nz, (long)n * n * g->T);
     // winds at faces
     {
         RBatch B{};
         B.fld[0] = s->u;
         B.fld[1] = s->v;
         B.nf = 2;
-        timed("k_remap_winds", k_remap<T, RM_WIND, 1>, lds(B, 1), grid((long)n * (n + 1), g->T * 2), blk, st, G, ptop, C, B,
+        timed("k_remap_winds", k_remap<T, RM_WIND, 1>, lds(B, 1, lw), grid((long)n * (n + 1), g->T * 2, lw), blk, st, G, lw, ptop, C, B,
               (const T *)s->delp, g->flags);
     }
     // cell fields: pt, w, delz (as delz/delp), tracers.  A field listed again
@@ -415,12 +450,12 @@ fv3_status remap(fv3_state *s, const fv3_grid *g, const double *ak, const double
             B.fp64[k] = B.ratio[k] = f[k] == (const void *)s->delz;
         }
         const int groups = (nf + NF - 1) / NF;
-        timed("k_remap_cells", k_remap<T, RM_CELL, NF>, lds(B, NF), grid((long)n * n, g->T * groups), blk, st, G, ptop, C, B,
+        timed("k_remap_cells", k_remap<T, RM_CELL, NF>, lds(B, NF, lw), grid((long)n * n, g->T * groups, lw), blk, st, G, lw, ptop, C, B,
               (const T *)s->delp, g->flags);
     };
     for (size_t b = 0; b < fs.size(); b += RFIELDS) cells(&fs[b], (int)std::min<size_t>(RFIELDS, fs.size() - b));
     if (own) cells(&s->delp, 1);
-    timed("k_remap_delp", k_remap_delp<T>, 0, grid((long)n * n, g->T), blk, st, G, ptop, C, (T *)s->delp);
+    timed("k_remap_delp", k_remap_delp<T>, ((size_t)(nz + 1) * 8) << lw, grid((long)n * n, g->T, lw), blk, st, G, lw, ptop, C, (T *)s->delp);
     return hipGetLastError() == hipSuccess ? FV3_OK : FV3_EDEVICE;
 }
 
