@@ -27,6 +27,7 @@
 // per column; thickness and commit kernels for site 1): C192 x 79 site 0
 // 712 -> 388 us, site 1 712 -> 455 us; C48 x 79 (15 000 columns, fewer than
 // one wavefront per SIMD before) 250 -> 40 us and 210 -> 39 us.
+#include <algorithm>
 #include <cmath>
 
 #include "column.hpp"
@@ -73,7 +74,7 @@ DEVI double cubic_iface(double da, double db, double dc, double dd, double qa, d
 // LDS of a column block: values a chunk hands to its neighbours
 struct ColLds {
     double x[6][CNT];   // one slot per (chunk, column)
-    double run[3][CNT / 2];   // carried by the recurrence under way
+    double run[3][CNT];   // carried by the recurrence under way, one slot per column
 };
 
 // Runs f(s) for the chunks s = 0 .. nch-1 in order (UP: from the last to the
@@ -482,10 +483,12 @@ COLOCC(double, 1)
 // log2 of the columns per block: as many as leave a thread for every chunk,
 // fewer (down to 16: one 64-byte segment of FP32) while the tiles' columns
 // make fewer than two blocks per compute unit, where the idle threads cost
-// nothing and the shorter blocks spread over the chip.
+// nothing and the shorter blocks spread over the chip.  One chunk (up to five
+// layers): 256 columns; with 128 and half the threads idle 512 x 512 x 1
+// periodic takes 46 / 38 us a launch (site 0 / 1), with 256 columns 31 / 24.
 static int col_shift(int chunks, long columns)
 {
-    int lw = 7;
+    int lw = 8;
     while (lw > 3 && (CNT >> lw) < chunks) lw--;
     while (lw > 4 && (columns >> lw) < 512) lw--;
     return lw;
@@ -527,16 +530,17 @@ template void column_solve<double, 1>(const fv3_grid *, const ColArgs<double> &,
 
 // Interface heights of the cells of a tile from the state's thicknesses,
 // bottom up (once per call; each substep's second solve writes the next
-// ones): the sum passes from chunk to chunk as in the solves.
-constexpr int HW = 16, HC = CNT / HW;   // columns per block, chunks per column
-DEVI void k_heights(Bk bk, Geo G, const double *delz, const double *phis, double *zh)
+// ones): the sum passes from chunk to chunk as in the solves.  Chunks of about
+// five layers, 16 at most (1024 x 1024 x 2 periodic with 16 chunks whatever the
+// depth 202 us, with one 16; C192 x 20 55 us, with four 22).
+DEVI void k_heights(Bk bk, Geo G, int lw, int nch, const double *delz, const double *phis, double *zh)
 {
-    __shared__ double run[HW];
+    __shared__ double run[CNT];
     const int n = G.n, nz = G.nz, t = (int)bk.z;
-    const int c = (int)threadIdx.x % HW, ch = (int)threadIdx.x / HW, p = (int)bk.x * HW + c;
+    const int c = (int)threadIdx.x & ((1 << lw) - 1), ch = (int)threadIdx.x >> lw, p = ((int)bk.x << lw) + c;
     const bool col = p < n * n;
     const int pc = col ? p : 0, j = pc / n, i = pc % n;
-    const int cl = (nz + HC - 1) / HC, k0 = ch * cl, k1 = min(nz, k0 + cl);
+    const int cl = (nz + nch - 1) / nch, k0 = ch * cl, k1 = min(nz, k0 + cl);
     const long o = (long)j * G.pitch + i, lev = G.lev;
     const double *D = delz + pidx(G, nz, t, 0) + o;
     double *Z = zh + pidx(G, nz + 1, t, 0) + o;
@@ -544,9 +548,9 @@ DEVI void k_heights(Bk bk, Geo G, const double *delz, const double *phis, double
     double d[P];
 #pragma unroll
     for (int u = 0; u < P; u++) d[u] = k1 - 1 - u >= k0 ? D[(long)(k1 - 1 - u) * lev] : 0.0;
-    chain<true>(4, (int)threadIdx.x, HC, [&]() {
+    chain<true>(lw, (int)threadIdx.x, nch, [&]() {
         double z;
-        if (ch == HC - 1) {
+        if (ch == nch - 1) {
             z = phis ? phis[pidx(G, 1, t, 0) + o] / GRAV : 0.0;
             if (col) Z[(long)nz * lev] = z;
         } else {
@@ -571,8 +575,9 @@ DEVI void k_heights(Bk bk, Geo G, const double *delz, const double *phis, double
 
 void column_heights(const fv3_grid *g, const double *delz, const double *phis, double *z, hipStream_t st)
 {
-    launch_fn<k_heights>("k_heights", dim3((unsigned)((g->n * g->n + HW - 1) / HW), 1, (unsigned)g->T),
-                         dim3(CNT), st, g->geo, delz, phis, z);
+    const int nch = std::min(16, (g->nz + 4) / 5), lw = col_shift(nch, (long)g->n * g->n * g->T);
+    launch_fn<k_heights>("k_heights", dim3((unsigned)((g->n * g->n + (1 << lw) - 1) >> lw), 1, (unsigned)g->T),
+                         dim3(CNT), st, g->geo, lw, nch, delz, phis, z);
 }
 
 }  // namespace fv3
