@@ -1523,38 +1523,79 @@ __global__ void __launch_bounds__(256) k_mass_partial(int ilo, int ihi, int jlo,
     }
 }
 
-// The block partials of one field per block, added in block order by one
-// thread; the others stage the next partials in LDS.
+// The block partials of one field per block, combined in block order: the sums
+// s_i, one addition each after the other, the errors e_i of these additions,
+// independent of each other once the sums are known, and the compensation c,
+// two additions each.  One thread does the sums of a batch of partials, another
+// the compensation of the batch two before, two wavefronts the errors of the one
+// between.  Every value is that of the plain loop.  Bound by the latency of the
+// additions.  One thread doing all of it / this, the whole call: two sums of C768
+// x 3 (13824 partials) 423 / 223 us, of 1024 x 1024 x 2 136 / 86; six of C192 x 79
+// 121 / 113.
+constexpr int MFB = 256;   // partials per batch
 __global__ void __launch_bounds__(256) k_mass_final(const double *part, long np, double *out)
 {
-    __shared__ double st[2][512];
+#pragma clang fp contract(off)
+    __shared__ double px[4][MFB], pc[4][MFB], ps[2][MFB + 1], pe[2][MFB];
     const double *p = part + 2 * np * blockIdx.x;
-    double s = 0.0, c = 0.0;
-    auto stage = [&](long b0, double *d) {
-        for (int q = 0; q < 2; q++) {
-            const long e = 2 * b0 + (int)threadIdx.x + 256 * q;
-            if (e < 2 * np) d[threadIdx.x + 256 * q] = p[e];
-        }
+    const int tid = (int)threadIdx.x, nb = (int)((np + MFB - 1) / MFB);
+    double s = 0.0, c = 0.0;   // thread 0: s; thread 64: c
+    // partials past the last one are zeros, which change neither sum nor compensation
+    auto load = [&](int b, int i) {
+        const long e = (long)b * MFB + i;
+        px[b & 3][i] = e < np ? p[2 * e] : 0.0;
+        pc[b & 3][i] = e < np ? p[2 * e + 1] : 0.0;
     };
-    stage(0, st[0]);
+    load(0, tid);
     __syncthreads();
-    for (long b0 = 0; b0 < np; b0 += 256) {
-        const int cur = (int)(b0 / 256) & 1;
-        if (b0 + 256 < np && threadIdx.x >= 64) {
-            // the wavefront of the adding thread leaves the staging to the others
-            for (int e = (int)threadIdx.x - 64; e < 512; e += 192)
-                if (2 * (b0 + 256) + e < 2 * np) st[1 - cur][e] = p[2 * (b0 + 256) + e];
+    // partials of a batch, up to the next multiple of 16
+    auto count = [&](int b) { return (int)(np - (long)b * MFB < MFB ? (np - (long)b * MFB + 15) / 16 * 16 : MFB); };
+    for (int b = 0; b < nb + 2; b++) {
+        if (tid == 0 && b < nb) {
+            const double *x = px[b & 3];
+            double *o = ps[b & 1];
+            const int m = count(b);
+            for (int i = 0; i < m; i += 16) {
+                double v[16];
+#pragma unroll
+                for (int q = 0; q < 16; q++) v[q] = x[i + q];
+#pragma unroll
+                for (int q = 0; q < 16; q++) {
+                    o[i + q] = s;
+                    s = s + v[q];
+                }
+            }
+            o[m] = s;
         }
-        if (threadIdx.x == 0) {
-            const int m = (int)(np - b0 < 256 ? np - b0 : 256);
-            for (int b = 0; b < m; b++) {
-                c += st[cur][2 * b + 1];
-                neu_add(s, c, st[cur][2 * b]);
+        if (tid == 64 && b >= 2) {
+            const double *k = pc[(b - 2) & 3], *e = pe[b & 1];
+            const int m = count(b - 2);
+            for (int i = 0; i < m; i += 8) {
+                double v[8], w[8];
+#pragma unroll
+                for (int q = 0; q < 8; q++) {
+                    v[q] = k[i + q];
+                    w[q] = e[i + q];
+                }
+#pragma unroll
+                for (int q = 0; q < 8; q++) c = (c + v[q]) + w[q];
+            }
+        }
+        if (tid >= 128) {
+            for (int i = tid - 128; i < MFB; i += 128) {
+                if (b + 1 < nb) load(b + 1, i);
+                if (b >= 1 && b <= nb && i < count(b - 1)) {
+                    const double x = px[(b - 1) & 3][i], s0 = ps[(b - 1) & 1][i], t = ps[(b - 1) & 1][i + 1];
+                    const bool big = fabs(s0) >= fabs(x);
+                    pe[(b - 1) & 1][i] = ((big ? s0 : x) - t) + (big ? x : s0);
+                }
             }
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[blockIdx.x] = s + c;
+    if (tid == 64) px[0][0] = c;
+    __syncthreads();
+    if (tid == 0) out[blockIdx.x] = s + px[0][0];
 }
 
 // ====================================================================
@@ -2086,27 +2127,59 @@ fv3_status run_tracer(void *const *q, int nq, fv3_state *s, const fv3_grid *g, i
     return tracer_t<double>(q, nq, s, g, nsplt, st);
 }
 
-// the sums of fields w0 .. w0 + nf - 1 (0: mass, 1: pt, 2 + m: q[m]) into out
+// block partials of fields w0 .. w0 + nf - 1 (0: mass, 1: pt, 2 + m: q[m])
 template <class B>
-static void mass_group(const fv3_grid *g, const void *delp, const void *pt, void *const *q, int w0, int nf, double *part,
-                       double *out, hipStream_t st)
+static void mass_partials(const fv3_grid *g, const void *delp, const void *pt, void *const *q, int w0, int nf, double *part,
+                          hipStream_t st)
 {
     MassFields<B> F{};
     F.nf = nf;
     for (int f = 0; f < nf; f++) F.p[f] = (const B *)(w0 + f == 0 ? nullptr : w0 + f == 1 ? pt : q[w0 + f - 2]);
     launch2d_native("k_mass_partial", k_mass_partial<B>, 0, g->n - 1, 0, g->n - 1, g->T, st, g->geo, metrics_d(g),
                     (const B *)delp, F, part);
-    hipLaunchKernelGGL(k_mass_final, dim3((unsigned)nf), dim3(256), 0, st, (const double *)part, part_count(g), out);
+}
+static void mass_final(const fv3_grid *g, int nf, const double *part, double *out, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_mass_final, dim3((unsigned)nf), dim3(256), 0, st, part, part_count(g), out);
+}
+
+// k_mass_final's combination on the host
+static double mass_combine(const double *part, long np)
+{
+    double s = 0.0, c = 0.0;
+    for (long b = 0; b < np; b++) {
+        const double x = part[2 * b], t = s + x;
+        const bool big = std::fabs(s) >= std::fabs(x);
+        c = (c + part[2 * b + 1]) + (((big ? s : x) - t) + (big ? x : s));
+        s = t;
+    }
+    return s + c;
 }
 
 template <class B>
 static fv3_status mass_sums_t(const fv3_grid *g, const void *delp, const void *pt, void *const *q,
                               int nq, double *out, hipStream_t st)
 {
-    double *dout = g->red + 2 * part_count(g) * MNF;
+    const long np = part_count(g);
+    double *dout = g->red + 2 * np * MNF;
     for (int w0 = 0; w0 < 2 + nq; w0 += MNF) {
         const int nf = 2 + nq - w0 < MNF ? 2 + nq - w0 : MNF;
-        mass_group<B>(g, delp, pt, q, w0, nf, g->red, dout, st);
+        mass_partials<B>(g, delp, pt, q, w0, nf, g->red, st);
+        // A host thread makes the same additions in the same order in a quarter
+        // of the time of one of the device, but after a copy of all partials,
+        // whose first call costs about 100 us more.  It is taken for few fields of
+        // many blocks (two sums, device / host: 1024 x 1024 x 2 110 / 63 us, C384 x
+        // 20 121 / 80, C768 x 3 259 / 130); six sums are 115 / 104, 149 / 137 and
+        // 281 / 282, those of C192 x 79 126 / 120 (first call 212 / 320 to 430).
+        if (nf <= 3 && np >= 2048) {
+            std::vector<double> h((size_t)(2 * np * nf));
+            if (hipMemcpyAsync(h.data(), g->red, h.size() * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
+                hipStreamSynchronize(st) != hipSuccess)
+                return FV3_EDEVICE;
+            for (int f = 0; f < nf; f++) out[w0 + f] = mass_combine(&h[(size_t)(2 * np * f)], np);
+            continue;
+        }
+        mass_final(g, nf, g->red, dout, st);
         if (hipMemcpyAsync(out + w0, dout, nf * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess)
             return FV3_EDEVICE;
         if (hipStreamSynchronize(st) != hipSuccess) return FV3_EDEVICE;
@@ -2194,8 +2267,11 @@ static fv3_status mass_sums_noalloc_t(const fv3_grid *g, const void *delp, const
     // nothing in the scratch has to be cleared first
     const long cap = (long)(FV3_NOALLOC_SCRATCH_BYTES / sizeof(double)) / noalloc_mass_doubles(g);
     const int most = cap < MNF ? (int)cap : MNF;
-    for (int w0 = 0; w0 < 2 + nq; w0 += most)
-        mass_group<B>(g, delp, pt, q, w0, 2 + nq - w0 < most ? 2 + nq - w0 : most, part, dev_out + w0, st);
+    for (int w0 = 0; w0 < 2 + nq; w0 += most) {
+        const int nf = 2 + nq - w0 < most ? 2 + nq - w0 : most;
+        mass_partials<B>(g, delp, pt, q, w0, nf, part, st);
+        mass_final(g, nf, part, dev_out + w0, st);
+    }
     return hipGetLastError() == hipSuccess ? FV3_OK : FV3_EDEVICE;
 }
 
