@@ -29,6 +29,11 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 MARCH_KIND = {0: "k_march_mass", 1: "k_march_wind", 2: "k_march_height", 3: "k_march_tracer"}
 FVTP_EPI = {0: "k_fvtp_flux", 1: "k_fvtp_delp", 2: "k_fvtp_massw", 3: "k_fvtp_adv", 4: "k_fvtp_tracer"}
+REMAP_MODE = {0: "k_remap_cells", 1: "k_remap_winds"}
+# launched under their plain names (others under "name<B>"), or under another
+UNTYPED = ("k_csw", "k_nhpgrad", "k_halo_scalar", "k_halo_pair", "k_halo_z", "k_fill", "k_heights", "k_zdev",
+           "k_delz_from_zh", "k_delz_from_zdev", "k_tracer_dp", "k_edgefix_q", "k_ke_edge")
+RENAMED = {"k_halo_set": "k_halo_scalar", "k_edgefix_dsw": "k_edgefix"}
 TSIZE = {"f": 4, "d": 8}
 
 
@@ -46,9 +51,11 @@ def launch_name(symbol: str):
     if not m:
         # plain kernels of the library (reductions, copies, the learned
         # correction's products): their own name
-        p = re.search(r"_ZN3fv3(\d+)(k_\w+)", symbol) or re.search(r"^_Z(\d+)(k_\w+)", symbol)
+        p = re.search(r"_ZN3fv3(?:12_GLOBAL__N_1)?(\d+)(k_\w+)", symbol) or re.search(r"^_Z(\d+)(k_\w+)", symbol)
         if p:
-            return p.group(2)[:int(p.group(1))]
+            name, targs = p.group(2)[:int(p.group(1))], p.group(2)[int(p.group(1)):]
+            mode = re.match(r"I[fd]Li(\d)E", targs)
+            return REMAP_MODE[int(mode.group(1))] if name == "k_remap" and mode else name
         # names stored demangled ("fv3::k_name(args)")
         p = re.search(r"fv3::(k_\w+)\s*[(<]", symbol)
         return p.group(1) if p else None
@@ -65,14 +72,15 @@ def launch_name(symbol: str):
     if name in ("k_column", "k_column_any") and ints:
         return "k_column_c" if ints[0] == 0 else "k_column_3"
     if name == "k_sim1" and len(ints) >= 2:
+        # column solve passes, in databases of builds that had them
         return f"k_sim1_{'c' if ints[1] == 0 else '3'}.p{ints[0]}"
-    if name in ("k_csw", "k_nhpgrad", "k_halo_scalar", "k_halo_pair", "k_fill"):
+    if name in UNTYPED:
         return name
+    if name in RENAMED:
+        return RENAMED[name]
     if name == "k_copy":
         t = re.match(r"I([fd])([fd])E", targs)
         return f"k_copy<{t.group(1)}{t.group(2)}>" if t else name
-    if name in ("k_heights", "k_delz_from_zh"):
-        return name
     return name + "<B>"
 
 
