@@ -199,6 +199,10 @@ void nh_grad(const fv3_grid *g, const NhArgs<B> &args, hipStream_t st)
     // C96 x 79 FP64 82 / 78, C48 x 79 24.5 / 26.4, periodic 48 x 8 5.8 / 7.5)
     a.layers = (long)g->T * g->nz * ((pts + 57) / 58) >= 768 ? 2 : 1;
     const int nzb = (g->nz + 4 * a.layers - 1) / (4 * a.layers);
+    // wavefronts per round for the split, by measurement: the kernel, which holds
+    // both bodies, fits three, but told so it takes C192 x 79 mixed from 205 to
+    // 222 us and FP64 from 269 to 284 (C140 x 79 from 143 to 120 and from 202 to
+    // 177; within 2% elsewhere between 48 x 8 and C384 x 20)
     march_shape(pts, (long)g->T * nzb * 4, 4, a.layers == 2 ? 2 : 4, a.strips, a.width, a.segs, a.rows);
     const dim3 grd((unsigned)((long)a.strips * a.segs * g->T * nzb)), blk(256);
     if (g->p.edge_interp && g->p.kind == FV3_GRID_CUBED_SPHERE)

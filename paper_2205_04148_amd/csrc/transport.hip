@@ -434,8 +434,9 @@ DEVI void k_march(Bk bk, Geo G, MarchArgs<T> A)
     }
 }
 
-// FP32 MASS: 128 registers, four wavefronts per SIMD (132 and three without
-// the hint: 479 against 471 us at C192 x 79); FP64 MASS: 256, two
+// FP32 MASS: 128 registers (4 to 8 of them spilled), four wavefronts per SIMD
+// (132 and three without the hint: 479 against 471 us at C192 x 79); FP64 MASS:
+// 256, two
 #define MARCHOCC(T, ORD, W) template <> constexpr int kocc<k_march<T, MARCH_MASS, 3, ORD>> = W;
 MARCHOCC(float, 8, 4)
 MARCHOCC(float, 6, 4)
@@ -444,7 +445,8 @@ MARCHOCC(double, 8, 2)
 MARCHOCC(double, 6, 2)
 MARCHOCC(double, 5, 2)
 
-// wavefronts per SIMD of each kernel, from its registers
+// wavefronts per SIMD of each kernel, from its registers (orders 5, 7 and 8; of
+// order 6 FP32 HEIGHT fits seven, one FP32 tracer seven, one FP64 tracer four)
 template <int KIND, int NF, class T>
 constexpr int march_occ()
 {
