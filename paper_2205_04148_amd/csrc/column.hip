@@ -513,6 +513,13 @@ void column_solve(const fv3_grid *g, const ColArgs<B> &args, hipStream_t st)
     MetD M;
     for (int m = 0; m < M_ALL; m++) M.m[m] = g->met[m];
     const bool ext = a.beta != 1.0 || a.cubic || a.qv;
+    if (g_rec) {
+        // one kernel serves every combination of the options, but the members of
+        // an ensemble share them
+        const int opts = (a.beta != 1.0 ? 1 : 0) | (a.cubic ? 2 : 0) | (a.qv ? 4 : 0);
+        if (g_rec->column_options < 0) g_rec->column_options = opts;
+        if (g_rec->column_options != opts) g_rec->bad = true;
+    }
     if (g_rec && !g_rec->short_columns) {
         if (ext) launch_fn<k_column_any<B, SITE, true>>(name, grd, blk, st, g->geo, M, a);
         else launch_fn<k_column_any<B, SITE, false>>(name, grd, blk, st, g->geo, M, a);

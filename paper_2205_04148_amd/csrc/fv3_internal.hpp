@@ -90,6 +90,7 @@ struct Recorder {
     size_t pos = 0, mark = 0;
     int member = 0;
     bool short_columns = true;   // every member's column solves take the short-chunk kernel
+    int column_options = -1;     // the first member's off-centring, interface order and humidity
     bool bad = false;
 };
 
