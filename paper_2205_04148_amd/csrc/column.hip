@@ -25,7 +25,7 @@
 // 120 (site 0) and 200 us at C192 x 79.  Measured, mixed precision, against
 // the launches each replaces (height update, four solve passes of one thread
 // per column; thickness and commit kernels for site 1): C192 x 79 site 0
-// 712 -> 388 us, site 1 712 -> 455 us; C48 x 79 (15 000 columns, fewer than
+// 712 -> 384 us, site 1 712 -> 392 us; C48 x 79 (15 000 columns, fewer than
 // one wavefront per SIMD before) 250 -> 40 us and 210 -> 39 us.
 #include <algorithm>
 #include <cmath>

@@ -25,7 +25,7 @@
 // would allow 293 us for MASS at C192 x 79 mixed.  Measured there, per launch
 // (launches replaced): MASS 835 (delp, pt, w apart) -> 435 us, WIND 336
 // (vorticity fluxes, update) -> 195, HEIGHT 464 (heights, transport) -> 159,
-// four tracers 1500 -> 640; FP64: 1585 -> 861, 815 -> 365, 752 -> 295.
+// four tracers 1500 -> 572; FP64: 1585 -> 861, 815 -> 365, 752 -> 295.
 //
 // Products and sums are written as fused operations where the results are
 // pinned, so that every kernel of this file rounds alike.
