@@ -457,7 +457,7 @@ fv3_status fv3_apply_correction(fv3_state *s, const fv3_grid *g, const float *Y,
  * on the current HIP device.  Matrix products take BF16 operands (round to
  * nearest even) on the matrix cores with FP32 accumulation; parameters,
  * Adam moments and activations' derivatives are FP32.  Hidden widths must be
- * multiples of 16; input and output widths are padded to 16 internally.
+ * multiples of 16; all widths are padded to 32 internally.
  * `params` (host) are packed as W1 (in x h1, row-major), b1, W2, b2, W3, b3;
  * rows <= maxrows for every call. */
 typedef struct fv3_mlp fv3_mlp;
@@ -465,9 +465,11 @@ fv3_status fv3_mlp_create(int in, int h1, int h2, int out, int maxrows, const fl
                           fv3_mlp **net);
 fv3_status fv3_mlp_free(fv3_mlp *net);
 long fv3_mlp_param_count(const fv3_mlp *net);
-/* replace the parameters (host, packed) and reset the Adam state; synchronous */
+/* replace the parameters (host, packed) and reset the Adam state; synchronous;
+ * any device may be current */
 fv3_status fv3_mlp_set_params(fv3_mlp *net, const float *params);
-/* copy the FP32 master parameters to host (packed); synchronous */
+/* copy the FP32 master parameters to host (packed); synchronous; any device
+ * may be current */
 fv3_status fv3_mlp_get_params(const fv3_mlp *net, float *params);
 /* Y (device, rows x out) = network(X (device, rows x in)); asynchronous */
 fv3_status fv3_mlp_forward(fv3_mlp *net, const float *X, int rows, float *Y, void *stream);
