@@ -39,7 +39,6 @@ DEVI bf16_t to_bf16(float f)
     u += 0x7fffu + lsb;
     return (bf16_t)(u >> 16);
 }
-DEVI float from_bf16(bf16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
 // ------------------------------------------------------------- products
 constexpr int PADK = 32;   // widths and the transposed row count are padded to this
@@ -491,14 +490,15 @@ bool on_device(const fv3_mlp *n)
 // network's for the duration of one, then the caller's again.
 struct OnDevice {
     int prev = -1;
-    bool ok;
+    bool ok, moved = false;
     explicit OnDevice(const fv3_mlp *n)
     {
-        ok = hipGetDevice(&prev) == hipSuccess && (prev == n->device || hipSetDevice(n->device) == hipSuccess);
+        ok = hipGetDevice(&prev) == hipSuccess;
+        if (ok && prev != n->device) ok = moved = hipSetDevice(n->device) == hipSuccess;
     }
     ~OnDevice()
     {
-        if (prev >= 0) (void)hipSetDevice(prev);
+        if (moved) (void)hipSetDevice(prev);
     }
 };
 
